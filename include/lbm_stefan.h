@@ -161,7 +161,10 @@ typedef struct lbm_stefan_params {
   int32_t variant;       /* kernel variant (lbm_stefan_variant_name); -1
                             picks the library default for the lattice
                             (D1Q3 lattices the resident variant takes:
-                            that one) */
+                            that one; small 2D lattices: several steps per
+                            launch on tiles held in LDS, EEBM in FP64 up to
+                            2^23 nodes; else a one-step tiling by size).
+                            The states are the same bit for bit */
   int32_t flags;         /* LBM_FLAG_* */
   int32_t scheme;        /* LBM_SCHEME_*; 0 (zeroed params) is IREBM */
   int64_t nz;            /* dim 3: nodes along z, >= 3; ignored otherwise */
@@ -236,7 +239,8 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
 
 /*
  * Advance nsteps >= 0 time steps (one kernel launch per step on the
- * handle's stream).  Asynchronous when stats is NULL and strict is off;
+ * handle's stream, fewer where the variant or the library default takes
+ * several steps per launch).  Asynchronous when stats is NULL and strict is off;
  * otherwise waits for the stream and fills *stats (the energy is
  * recomputed from the final state).  Errors: EINVAL (nsteps < 0),
  * ENOTCONV (strict), ENAN (the energy is not finite), EDEVICE.

@@ -605,10 +605,14 @@ int lbm_stefan_forward_tape(lbm_stefan_t *h, int64_t nsteps, int64_t interval,
   for (int64_t k = 1; k <= K; ++k) {
     const int64_t n = std::min(I, nsteps - (k - 1) * I);
     const void *src = t + (k - 1) * slot;
-    for (int64_t s = 0; s < n; ++s) {
-      void *dst = s == n - 1 ? (void *)(t + k * slot) : h->buf[s & 1];
-      HIPCHK(h, launch_step(h, src, dst));
-      h->steps++;
+    int flip = 0;
+    for (int64_t s = 0; s < n;) {
+      const int m = next_launch(h, n - s);
+      s += m;
+      void *dst = s == n ? (void *)(t + k * slot) : h->buf[flip];
+      flip ^= 1;
+      HIPCHK(h, launch_steps(h, src, dst, m, h->stream));
+      h->steps += m;
       src = dst;
     }
   }
@@ -657,9 +661,14 @@ int lbm_stefan_backward_tape(lbm_stefan_t *h, const double *dL_dfront,
     const int64_t n = std::min(I, N - k * I);
     char *sg = seg[k & 1];
     hipError_t e = hipStreamWaitEvent(h->side, h->fork, 0);
-    for (int64_t j = 1; j < n && e == hipSuccess; ++j)
-      e = launch_step(h, j == 1 ? states_of(k) : sg + (j - 1) * slot,
-                      sg + j * slot, h->side);
+    // states 1 .. n - 1 of the segment, every one of them stored
+    for (int64_t j = 0; j < n - 1 && e == hipSuccess;) {
+      const int m = next_launch(h, n - 1 - j);
+      e = launch_steps(h, j == 0 ? states_of(k) : sg + j * slot,
+                       sg + (j + m) * slot, m, h->side, sg + j * slot,
+                       (int64_t)slot);
+      j += m;
+    }
     if (e == hipSuccess) e = hipEventRecord(h->join, h->side);
     return e;
   };

@@ -93,6 +93,64 @@ inline void set_tiling(StepArgs *A, const Variant &v) {
   A->per_xcd = (A->nitems + 7) / 8;
 }
 
+// LDS a block of tile_kernel may take (of 160 KB a CU)
+constexpr size_t kTileLds = 156 * 1024;
+
+// The library's choice for tile_kernel on an nx x ny lattice (q populations
+// of s bytes): steps per launch k and the side of a tile.  Measured on
+// square lattices from 60 to 2048 nodes a side (us per step, the one-step
+// kernel's best tiling -> tile_kernel):
+//   IREBM: a step is one Newton solve long, so small tiles that put a block
+//   on every CU and few halo nodes win, and the kernel stops paying where
+//   the halo's solves outweigh the launch: 60^2 8.9 -> 5.4, 151^2 8.9 -> 5.6
+//   (k 4, side 8), 201^2 9.1 -> 6.2, 301^2 9.7 -> 7.8 (3, 10), 351^2 10.0 ->
+//   8.8 (2, 12), 401^2 10.4 -> 10.8 (D2Q5 FP64 freezing; D2Q9, FP32 and the
+//   melting set-up alike).
+//   EEBM: no solve, so more steps: 101^2 4.5 -> 2.5 (6, 8), 201^2 4.8 -> 2.7
+//   (4, 8), 301^2 5.5 -> 3.3, 512^2 7.0 -> 5.5 (4, 14); larger ones are
+//   bound by traffic, which k steps divide by nearly k: FP64 1024^2 26 -> 20
+//   (2, 12), 2048^2 D2Q9 124 -> 81 (4, 24); in FP32 the one-step kernel
+//   keeps up from 512^2 on (D2Q9 7.2, D2Q5 7.3 at 701^2 against 7.7).
+inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
+                          int64_t ny) {
+  const int64_t n = nx * ny;
+  int k = 0, side = 0;
+  if (!eebm) {
+    if (n <= 30000) k = 4, side = 8;
+    else if (n <= 110000) k = 3, side = 10;
+    else if (n <= 130000) k = 2, side = 12;
+  } else {
+    if (n <= 15000) k = 6, side = 8;
+    else if (n <= 60000) k = 4, side = 8;
+    else if (n <= (s == 8 || q == 5 ? 400000 : 200000)) k = 4, side = 14;
+    else if (s == 8 && (q == 5 || n <= 1800000) && n <= (1 << 23))
+      k = 2, side = 12;
+    else if (s == 8 && n <= (1 << 23)) k = 4, side = 24;
+  }
+  TilePlan P;
+  if (k == 0) return P;
+  P.k = k;
+  P.ntx = (int32_t)((nx + side - 1) / side);
+  P.nty = (int32_t)((ny + side - 1) / side);
+  // tiles of nearly equal sizes, at least two nodes wide
+  P.rx = (int32_t)((nx + P.ntx - 1) / P.ntx) + 2 * k;
+  P.ry = (int32_t)((ny + P.nty - 1) / P.nty) + 2 * k;
+  if (P.rx * P.ry > 1024 || (size_t)P.rx * P.ry * q * s > kTileLds ||
+      nx / P.ntx < 2 || ny / P.nty < 2)
+    return TilePlan();
+  return P;
+}
+
+// The one-step tiling of the library default: one node per thread and 64 x
+// 1 blocks (index 20) while the lattice leaves the chip short of waves (one
+// node's chain per wave: 201^2 D2Q5 FP64 freezing 12.4 -> 9.2 us per step,
+// 512^2 D2Q9 FP64 14.0 -> 11.5, 1001 x 777 23.3 -> 21.5; FP32 512^2 D2Q5
+// 8.3 -> 7.5, 1001 x 777 11.5 against 13.1), 128 x 4 tiles with two nodes
+// per thread (kDefaultVariant2D) above.
+inline int one_step_default(size_t s, int64_t nodes) {
+  return nodes <= (s == 8 ? 1200000 : 400000) ? 20 : kDefaultVariant2D;
+}
+
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 inline unsigned blocks_for(int64_t n, int t) {

@@ -180,6 +180,32 @@ hipError_t launch_step2_t(const StepArgs &A, const Variant &v, bool two,
   }
 }
 
+// k steps of one small 2D lattice on tiles in LDS (tile_kernel)
+template <int Q, typename S, int MODE>
+hipError_t launch_tile_t(const StepArgs &A, const TilePlan &P, int k,
+                         char *mid, int64_t mid_stride, hipStream_t stream) {
+  if constexpr (Q == 3) {
+    return hipErrorInvalidValue;
+  } else {
+    const int64_t tiles = (int64_t)P.ntx * P.nty;
+    const int threads = (P.rx * P.ry + 63) / 64 * 64;
+    const size_t lds = (size_t)P.rx * P.ry * Q * sizeof(S);
+    if (k < 1 || k > P.k || threads > 1024 || lds > kTileLds || tiles < 1)
+      return hipErrorInvalidValue;
+    if (lds > 65536) {
+      // above the default limit of dynamic LDS (cheap, and per device)
+      const hipError_t e = hipFuncSetAttribute(
+          reinterpret_cast<const void *>(tile_kernel<Q, S, MODE>),
+          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds);
+      if (e != hipSuccess) return e;
+    }
+    dim3 grid((unsigned)(8 * ((tiles + 7) / 8))), block((unsigned)threads);
+    tile_kernel<Q, S, MODE><<<grid, block, lds, stream>>>(A, P, k, mid,
+                                                          mid_stride);
+    return hipGetLastError();
+  }
+}
+
 // one launch of a batch table (see BatchLaunch)
 template <int Q, typename S, int MODE>
 hipError_t launch_batch_t(const BatchLaunch &b, const Variant &v,
@@ -275,6 +301,16 @@ hipError_t step2_launch_mode(int q, int storage, const StepArgs &A,
 }
 
 template <int MODE>
+hipError_t tile_launch_mode(int q, int storage, const StepArgs &A,
+                            const TilePlan &P, int k, char *mid,
+                            int64_t mid_stride, hipStream_t stream) {
+  return dispatch_qs(q, storage, [&](auto qt, auto tt) {
+    QS_TYPES(qt, tt);
+    return launch_tile_t<Q, S, MODE>(A, P, k, mid, mid_stride, stream);
+  });
+}
+
+template <int MODE>
 hipError_t resident_launch_mode(int storage, const StepArgs &A,
                                 int32_t nsteps, hipStream_t stream) {
   if (storage == LBM_STORE_F32)
@@ -299,6 +335,9 @@ hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
   template hipError_t irebm::step_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::Variant &, bool,     \
       hipStream_t);                                                        \
+  template hipError_t irebm::tile_launch_mode<M>(                          \
+      int, int, const irebm::StepArgs &, const irebm::TilePlan &, int,     \
+      char *, int64_t, hipStream_t);                                       \
   template hipError_t irebm::step2_launch_mode<M>(                         \
       int, int, const irebm::StepArgs &, const irebm::Variant &, bool,     \
       hipStream_t);                                                        \
@@ -308,7 +347,10 @@ hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
 #define IREBM_INSTANTIATE_STEP1(M)                                         \
   template hipError_t irebm::step_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::Variant &, bool,     \
-      hipStream_t)
+      hipStream_t);                                                        \
+  template hipError_t irebm::tile_launch_mode<M>(                          \
+      int, int, const irebm::StepArgs &, const irebm::TilePlan &, int,     \
+      char *, int64_t, hipStream_t)
 
 #define IREBM_INSTANTIATE_BATCH(M)                                         \
   template hipError_t irebm::batch_launch_mode<M>(                         \

@@ -110,6 +110,20 @@ std::string irebm::validate_params(const lbm_stefan_params *p) {
   return "";
 }
 
+namespace {
+
+TilePlan plan_for(const lbm_stefan_params &p) {
+  if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM) return TilePlan();
+  return tile_plan(p.q, p.storage == LBM_STORE_F64 ? 8 : 4,
+                   p.scheme == LBM_SCHEME_EEBM, p.nx, p.ny);
+}
+
+int default_2d(const lbm_stefan_params &p) {
+  return one_step_default(p.storage == LBM_STORE_F64 ? 8 : 4, nodes_of(p));
+}
+
+}  // namespace
+
 irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
   Layout L;
   const int64_t n = nodes_of(*p);
@@ -135,6 +149,8 @@ irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
     const Variant *v = variants(p->q, &nv);
     for (int i = 0; i < nv; ++i)
       mt = std::max(mt, items_for(v[i], p->nx, p->ny));
+    const TilePlan tp = plan_for(*p);
+    mt = std::max(mt, (int64_t)tp.ntx * tp.nty);
   }
   L.max_items = mt;
   L.n_partials = (n + kEnergyChunk - 1) / kEnergyChunk;
@@ -382,6 +398,18 @@ hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
       return hipSuccess;
     }
   }
+  if (steps_per_launch(h) > 1) {
+    while (nsteps > 0) {
+      const int k = next_launch(h, nsteps);
+      const hipError_t e =
+          launch_steps(h, h->buf[h->cur], h->buf[h->cur ^ 1], k, h->stream);
+      if (e != hipSuccess) return e;
+      h->cur ^= 1;
+      h->steps += k;
+      nsteps -= k;
+    }
+    return hipSuccess;
+  }
   if (two_step_variant(h)) {
     for (; nsteps >= 2; nsteps -= 2) {
       const hipError_t e =
@@ -410,13 +438,35 @@ hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
   const Variant *vt = variants(h->p.q, &nv);
   // a single step under a two-step variant takes the default tiling, and
   // so does a step under the resident variant
-  const Variant &v = vt[vt[h->variant].tb    ? kDefaultVariant2D
+  const Variant &v = vt[vt[h->variant].tb    ? default_2d(h->p)
                         : vt[h->variant].res ? kDefaultVariant1D
                                              : h->variant];
   // a Dirichlet x = 0 wall is where the workloads heat: its tiles first
   A.front_first = h->p.bc[0] == LBM_BC_DIRICHLET;
   return step_launch(mode_of(h->p), h->p.q, h->p.storage, A, v,
                      v.rev && (h->steps & 1), stream ? stream : h->stream);
+}
+
+int irebm::steps_per_launch(const lbm_stefan_t *h) {
+  return h->by_default && h->plan.k > 1 ? h->plan.k : 1;
+}
+
+int irebm::next_launch(const lbm_stefan_t *h, int64_t nsteps) {
+  const int64_t k = steps_per_launch(h);
+  const int64_t launches = (nsteps + k - 1) / k;
+  return (int)((nsteps + launches - 1) / launches);
+}
+
+hipError_t irebm::launch_steps(const lbm_stefan_t *h, const void *src,
+                               void *dst, int k, hipStream_t stream,
+                               void *mid, int64_t mid_stride) {
+  if (k == 1) return launch_step(h, src, dst, stream);
+  StepArgs A;
+  fill_step_args(h, &A);
+  A.src = src;
+  A.dst = dst;
+  return tile_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->plan, k,
+                     stream, (char *)mid, mid_stride);
 }
 
 namespace {
@@ -527,7 +577,9 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
                                   : (p->q == 3 ? (resident_ok(*p)
                                                       ? kResidentVariant1D
                                                       : kDefaultVariant1D)
-                                               : kDefaultVariant2D));
+                                               : default_2d(*p)));
+  h->by_default = p->variant < 0;
+  h->plan = plan_for(*p);
   h->stream = (hipStream_t)stream;
   if (hipGetDevice(&h->device) != hipSuccess) {
     delete h;
@@ -738,6 +790,7 @@ int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant) {
     return fail(h, LBM_STEFAN_EINVAL, "unknown kernel variant");
   DeviceGuard g(h->device);
   h->variant = variant;
+  h->by_default = false;
   // the tile -> slot mapping changes with the tile shape
   HIPCHK(h, zero_stats_async(h));
   return LBM_STEFAN_OK;
@@ -775,9 +828,15 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     return fail(h, LBM_STEFAN_EDEVICE, "hipEventCreate failed");
   }
   int best = h->variant;
+  bool best_default = false;
   float best_ms = 0.0f;
   hipError_t err = hipSuccess;
-  for (int v = 0; v < nv && err == hipSuccess; ++v) {
+  // the library default's launches of several steps are one more trial,
+  // after the variants, under its one-step variant's index
+  const int trials = nv + (h->plan.k > 1 ? 1 : 0);
+  for (int trial = 0; trial < trials && err == hipSuccess; ++trial) {
+    const int v = trial < nv ? trial : default_2d(p);
+    h->by_default = trial == nv;
     // a Neumann lattice runs two-step variants as the default one, and a
     // lattice the resident kernel does not take runs that variant so too
     if (vt && vt[v].tb && has_neumann(p)) continue;
@@ -797,9 +856,10 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     float ms = 0.0f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
     ms /= (float)n;
-    if (err == hipSuccess && (v == 0 || ms < best_ms)) {
+    if (err == hipSuccess && (trial == 0 || ms < best_ms)) {
       best_ms = ms;
       best = v;
+      best_default = h->by_default;
     }
     // restore the saved state for the next trial
     h->cur = cur0;
@@ -811,6 +871,7 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   (void)hipEventDestroy(e1);
   h->cur = cur0;
   h->variant = best;
+  h->by_default = best_default;
   if (err != hipSuccess)
     return fail(h, LBM_STEFAN_EDEVICE,
                 std::string("autotune: ") + hipGetErrorString(err));

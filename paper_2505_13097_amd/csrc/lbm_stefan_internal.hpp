@@ -6,7 +6,7 @@
 
 #include <string>
 
-#include "irebm_node.hpp"
+#include "kernels.hpp"
 #include "lattice3d.hpp"
 #include "lbm_stefan.h"
 
@@ -55,6 +55,10 @@ struct lbm_stefan {
   double *small = nullptr;
   char *adj = nullptr;
   int variant = 0;
+  // the library default (params.variant = -1): small 2D lattices take
+  // several steps per launch on tiles in LDS (plan.k > 0)
+  bool by_default = false;
+  irebm::TilePlan plan;
   int64_t steps = 0;
   void *tape = nullptr;          // last forward tape
   int64_t tape_steps = 0, tape_interval = 0;
@@ -83,6 +87,16 @@ void fill_args(const lbm_stefan_params &p, double *const prof[4],
 void fill_step_args(const lbm_stefan_t *h, StepArgs *A);
 hipError_t launch_step(const lbm_stefan_t *h, const void *src, void *dst,
                        hipStream_t stream = nullptr);
+// Steps one launch takes under the library default (1: a launch a step),
+// and the steps of the next launch of nsteps (at most that many, the
+// launches as even as they come).
+int steps_per_launch(const lbm_stefan_t *h);
+int next_launch(const lbm_stefan_t *h, int64_t nsteps);
+// k steps (at most steps_per_launch) from src to dst; mid: step l < k is
+// also stored at mid + l * mid_stride bytes
+hipError_t launch_steps(const lbm_stefan_t *h, const void *src, void *dst,
+                        int k, hipStream_t stream, void *mid = nullptr,
+                        int64_t mid_stride = 0);
 // the handle's second stream (split steps, the reverse sweep's
 // recomputation) and its two events, created on first use
 hipError_t handle_side(lbm_stefan_t *h);
@@ -139,6 +153,11 @@ hipError_t step2_launch_mode(int q, int storage, const StepArgs &A,
 template <int MODE>
 hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
                              const Variant &v, hipStream_t stream);
+// k steps of a small 2D lattice on tiles in LDS (tile_kernel)
+template <int MODE>
+hipError_t tile_launch_mode(int q, int storage, const StepArgs &A,
+                            const TilePlan &P, int k, char *mid,
+                            int64_t mid_stride, hipStream_t stream);
 // nsteps steps of a small D1Q3 lattice in one resident workgroup
 // (resident1d_kernel; the lattice passes resident_ok)
 template <int MODE>
@@ -147,7 +166,10 @@ hipError_t resident_launch_mode(int storage, const StepArgs &A,
 
 #define IREBM_DECLARE_STEP1(M)                                             \
   extern template hipError_t step_launch_mode<M>(                          \
-      int, int, const StepArgs &, const Variant &, bool, hipStream_t)
+      int, int, const StepArgs &, const Variant &, bool, hipStream_t);     \
+  extern template hipError_t tile_launch_mode<M>(                          \
+      int, int, const StepArgs &, const TilePlan &, int, char *, int64_t,  \
+      hipStream_t)
 #define IREBM_DECLARE_MODE(M)                                              \
   IREBM_DECLARE_STEP1(M);                                                  \
   extern template hipError_t step2_launch_mode<M>(                         \
@@ -240,6 +262,25 @@ inline hipError_t step_launch(int mode, int q, int storage, const StepArgs &A,
     default:
       return step_launch_mode<kSafeguarded>(q, storage, A, v, reverse,
                                             stream);
+  }
+}
+
+// k steps of one small 2D lattice (tile_kernel)
+inline hipError_t tile_launch(int mode, int q, int storage, const StepArgs &A,
+                              const TilePlan &P, int k, hipStream_t stream,
+                              char *mid = nullptr, int64_t mid_stride = 0) {
+  switch (mode) {
+#define IREBM_TILE_CASE(M)                                                 \
+  case M:                                                                  \
+    return tile_launch_mode<M>(q, storage, A, P, k, mid, mid_stride, stream)
+    IREBM_TILE_CASE(kEebm);
+    IREBM_TILE_CASE(kPlain);
+    IREBM_TILE_CASE(kEebm | kNeumann);
+    IREBM_TILE_CASE(kPlain | kNeumann);
+    IREBM_TILE_CASE(kSafeguarded | kNeumann);
+    default:
+    IREBM_TILE_CASE(kSafeguarded);
+#undef IREBM_TILE_CASE
   }
 }
 

@@ -105,8 +105,9 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
     // handle)
     const Variant *vt = variants(q.q, &nv);
     int vi = q.variant;
-    if (vi < 0) vi = q.dim == 1 ? kDefaultVariant1D : kDefaultVariant2D;
-    if (vt[vi].tb) vi = kDefaultVariant2D;
+    const int dflt = one_step_default(q.storage == LBM_STORE_F64 ? 8 : 4, nodes);
+    if (vi < 0) vi = q.dim == 1 ? kDefaultVariant1D : dflt;
+    if (vt[vi].tb) vi = dflt;
     if (vt[vi].res) vi = kDefaultVariant1D;
     v2 = &vt[vi];
     s = plan_for(items_for(*v2, q.nx, q.ny), nodes);
