@@ -161,10 +161,10 @@ typedef struct lbm_stefan_params {
   int32_t variant;       /* kernel variant (lbm_stefan_variant_name); -1
                             picks the library default for the lattice
                             (D1Q3 lattices the resident variant takes:
-                            that one; small 2D lattices: several steps per
-                            launch on tiles held in LDS, EEBM in FP64 up to
-                            2^23 nodes; else a one-step tiling by size).
-                            The states are the same bit for bit */
+                            that one; 2D lattices: several steps per launch
+                            on tiles held in LDS or by sweeping waves,
+                            or a one-step tiling, by size, scheme and
+                            walls).  The states are the same bit for bit */
   int32_t flags;         /* LBM_FLAG_* */
   int32_t scheme;        /* LBM_SCHEME_*; 0 (zeroed params) is IREBM */
   int64_t nz;            /* dim 3: nodes along z, >= 3; ignored otherwise */
@@ -286,9 +286,10 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    nodes per thread, m tiles stacked along y per thread block,
    non-temporal stores, block order reversed every other step; or
    "<w>x<b>/t2/r<m>[/nt]": two time steps per launch, a w-column window
-   sweeping m rows, b rows per pass; a single trailing step then uses the
-   default variant, and a lattice with a Neumann wall runs the default
-   variant; q = 3 also "resident2048": D1Q3 lattices of at most 2048 nodes
+   sweeping m rows, b rows per pass, on lattices of about 100 columns or
+   fewer, and up to four steps per launch by waves sweeping m rows on wider
+   ones; a single trailing step then uses the default variant, and a lattice
+   with a Neumann wall runs the default variant; q = 3 also "resident2048": D1Q3 lattices of at most 2048 nodes
    with no Neumann wall run many steps per launch in one workgroup, both
    states in LDS (others run the default variant; the batched form rejects
    it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z

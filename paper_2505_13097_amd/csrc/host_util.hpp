@@ -10,6 +10,7 @@
 
 #include "kernels.hpp"
 #include "lbm_stefan.h"
+#include "sweep2d.hpp"
 
 namespace irebm {
 
@@ -97,20 +98,17 @@ inline void set_tiling(StepArgs *A, const Variant &v) {
 constexpr size_t kTileLds = 156 * 1024;
 
 // The library's choice for tile_kernel on an nx x ny lattice (q populations
-// of s bytes): steps per launch k and the side of a tile.  Measured on
-// square lattices from 60 to 2048 nodes a side (us per step, the one-step
-// kernel's best tiling -> tile_kernel):
+// of s bytes), where sweep_kernel is not taken: steps per launch k and the
+// side of a tile.  Measured on square lattices (us per step, the one-step
+// kernel's best tiling -> tile_kernel, D2Q5 FP64 freezing; D2Q9, FP32 and the
+// melting set-up alike):
 //   IREBM: a step is one Newton solve long, so small tiles that put a block
 //   on every CU and few halo nodes win, and the kernel stops paying where
 //   the halo's solves outweigh the launch: 60^2 8.9 -> 5.4, 151^2 8.9 -> 5.6
 //   (k 4, side 8), 201^2 9.1 -> 6.2, 301^2 9.7 -> 7.8 (3, 10), 351^2 10.0 ->
-//   8.8 (2, 12), 401^2 10.4 -> 10.8 (D2Q5 FP64 freezing; D2Q9, FP32 and the
-//   melting set-up alike).
+//   8.8 (2, 12), 401^2 10.4 -> 10.8.
 //   EEBM: no solve, so more steps: 101^2 4.5 -> 2.5 (6, 8), 201^2 4.8 -> 2.7
-//   (4, 8), 301^2 5.5 -> 3.3, 512^2 7.0 -> 5.5 (4, 14); larger ones are
-//   bound by traffic, which k steps divide by nearly k: FP64 1024^2 26 -> 20
-//   (2, 12), 2048^2 D2Q9 124 -> 81 (4, 24); in FP32 the one-step kernel
-//   keeps up from 512^2 on (D2Q9 7.2, D2Q5 7.3 at 701^2 against 7.7).
+//   (4, 8), 301^2 5.5 -> 3.3, 512^2 7.0 -> 5.5 (4, 14).
 inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
                           int64_t ny) {
   const int64_t n = nx * ny;
@@ -122,10 +120,7 @@ inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
   } else {
     if (n <= 15000) k = 6, side = 8;
     else if (n <= 60000) k = 4, side = 8;
-    else if (n <= (s == 8 || q == 5 ? 400000 : 200000)) k = 4, side = 14;
-    else if (s == 8 && (q == 5 || n <= 1800000) && n <= (1 << 23))
-      k = 2, side = 12;
-    else if (s == 8 && n <= (1 << 23)) k = 4, side = 24;
+    else if (n <= 400000) k = 4, side = 14;
   }
   TilePlan P;
   if (k == 0) return P;
@@ -139,6 +134,96 @@ inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
       nx / P.ntx < 2 || ny / P.nty < 2)
     return TilePlan();
   return P;
+}
+
+// bit i: an IREBM front starts at wall i: a Dirichlet wall that is hot (a
+// profile, or a temperature off phi's lower plateau), or any Dirichlet wall
+// where none is hot (a melt that freezes)
+inline int front_walls(const lbm_stefan_params &p, bool *hot) {
+  int h = 0, d = 0;
+  for (int i = 0; i < 4; ++i)
+    if (p.bc[i] == LBM_BC_DIRICHLET) {
+      d |= 1 << i;
+      if (p.wall_profile[i] || p.wall_T[i] >= p.t_m - 20.0 * p.delta)
+        h |= 1 << i;
+    }
+  *hot = h != 0;
+  return h ? h : d;
+}
+
+// The partition of a 2D lattice for sweep_kernel at up to k steps per
+// launch, segments of `rows` rows; an empty plan when the lattice is too
+// small for the frame and a strip.  The frame is two tiles deep where a
+// front starts (a strip that reaches the front solves in every row: the
+// 8192^2 cavity takes 380 us per step with one tile, 324 with two, 347 and
+// 330 with three and four), one at the other walls.
+inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
+                            bool nt) {
+  SweepPlan P;
+  const int T = frame_tile(k), w = 64 - 2 * k;
+  const int nx = (int)p.nx, ny = (int)p.ny;
+  const bool px = p.bc[0] == LBM_BC_PERIODIC, py = p.bc[2] == LBM_BC_PERIODIC;
+  bool hot;
+  const int front = p.scheme == LBM_SCHEME_IREBM ? front_walls(p, &hot) : 0;
+  auto band = [&](int i) { return front >> i & 1 ? 2 : 1; };
+  P.tile = T;
+  P.xb = nx;
+  P.yb = ny;
+  if (!px) {
+    P.nleft = band(0);
+    P.nright = band(1);
+    P.nside = (ny + T - 1) / T;
+    P.xa = P.nleft * T;
+    P.xb = nx - P.nright * T;
+  }
+  if (!py) {
+    P.nbottom = band(2);
+    P.ntop = band(3);
+    P.ya = P.nbottom * T;
+    P.yb = ny - P.ntop * T;
+  }
+  if (P.xb - P.xa < 64 || P.yb - P.ya < 16) return SweepPlan();
+  P.nacross = (P.xb - P.xa + T - 1) / T;
+  P.strips = (P.xb - P.xa + w - 1) / w;
+  P.rows = rows;
+  P.nseg = (P.yb - P.ya + rows - 1) / rows;
+  P.nt = nt ? 1 : 0;
+  P.k = k;
+  return P;
+}
+
+// sweep_kernel under the library default (an empty plan: tile_kernel or
+// single steps).  Measured (us per step, the best one-step tiling -> here):
+// IREBM heated at a wall 300^2 D2Q9 FP32 8.7 -> 6.0 (tile_kernel 7.4), 1001
+// x 777 D2Q9 FP64 21.4 -> 11.6, 2048^2 D2Q5 FP32 32.6 -> 16.0, D2Q9 FP64
+// 134 -> 46, 8192^2 D2Q9 FP32 921 -> 324; EEBM 201^2 D2Q9 FP64 6.0 -> 3.8
+// (tile_kernel 4.2), 801^2 19.1 -> 7.2, 2048^2 D2Q5 FP32 27.9 -> 9.6.  A
+// freezing IREBM lattice (no hot wall) keeps single steps: its bulk is
+// liquid, so the solves of a wave, one after the other, cost more than the
+// traffic saved (801^2 D2Q5 21.2 -> 22.4).
+// Three steps instead of four on FP32 lattices that the memory-side cache
+// holds (2048^2 D2Q9 31.9 against 34.6); rows per segment: enough waves for
+// the chip, few halo rows (8 on 512^2, 16 on 2048^2, 32 on 8192^2).
+inline SweepPlan sweep_default(const lbm_stefan_params &p) {
+  const int64_t n = p.nx * p.ny;
+  if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM) return SweepPlan();
+  const bool eebm = p.scheme == LBM_SCHEME_EEBM;
+  bool hot;
+  front_walls(p, &hot);
+  if (n <= (eebm ? 30000 : 60000) || (!eebm && !hot)) return SweepPlan();
+  const int k = !eebm && p.storage == LBM_STORE_F32 && n > 500000 &&
+                        n < 6000000 ? 3 : 4;
+  const int64_t rows = (p.ny / 128 + 3) / 4 * 4;
+  return sweep_plan(p, k, (int)(rows < 8 ? 8 : (rows > 32 ? 32 : rows)),
+                    n > (1 << 24));
+}
+
+// sweep_kernel under a two-step variant, in segments of its rows
+inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
+  if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM || !v.tb) return SweepPlan();
+  for (int i = 0; i < 4; ++i)
+    if (p.bc[i] == LBM_BC_NEUMANN) return SweepPlan();
+  return sweep_plan(p, 4, v.rows, v.nt != 0);
 }
 
 // The one-step tiling of the library default: one node per thread and 64 x

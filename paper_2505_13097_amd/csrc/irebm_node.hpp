@@ -264,6 +264,46 @@ __device__ __forceinline__ double newton(double m0, double th, double pth,
   return cand;
 }
 
+// The safeguarded solve of a node with phi(T) = 1 and phi' = 0 exactly (u >
+// 20) whose iterates stay above the band: newton() with phi = 1, the same
+// operations, so the same root, count and flag bit for bit, but without the
+// exponential, the divisions and the selects that the band needs.  (c holds
+// the latent heat, so the step from m0's side is a rounding of it, may fall
+// outside the bracket, and the bisection then takes several iterations:
+// there is no closed form as for a solid node.)  Returns false, with
+// nothing decided, when an iterate comes near the band.
+template <class AR>
+__device__ __forceinline__ bool newton_liquid(double m0, double th,
+                                              const AR &A, double &tn,
+                                              int &iters, bool &conv) {
+  const double s = A.inv_ste;
+  const double c = m0 + s;
+  double lo = c - s, hi = c;
+  double dx = hi - lo, dxold = dx;
+  double t = th, step;
+  int k = 0;
+  bool above;
+  do {
+    const double F = t + s - c;
+    lo = F < 0.0 ? t : lo;
+    hi = F > 0.0 ? t : hi;
+    const double n = t - F;
+    const bool bis = (int)(n < lo) | (int)(n > hi) |
+                     (int)(2.0 * fabs(F) > fabs(dxold));
+    dxold = dx;
+    dx = bis ? 0.5 * (hi - lo) : F;
+    const double to = bis ? 0.5 * (lo + hi) : n;
+    ++k;
+    above = (to - A.tm) * A.inv_delta > 20.5;
+    step = fabs(to - t);
+    t = to;
+  } while (above && !(step <= A.tol) && k < A.max_it);
+  iters = k;
+  conv = step <= A.tol;
+  tn = conv ? t - (t + s - c) : t;
+  return above;
+}
+
 struct NodeStats {
   int max_it = 0;
   int nonconv = 0;
@@ -449,10 +489,12 @@ struct CloseInfo {
 // or 1 (|T - T_m| > 20 delta), with no exp in the code; a Dirichlet node
 // whose wall or own temperature lies nearer the band sets *near instead
 // (its update is then left to a full kernel).
+// om: the node's own post-collision populations, om[i] (an array, or a
+// type that looks them up).
 template <int Q, int SCH = SCHEME_IREBM, bool NEU = true,
-          bool PLATEAU = false>
+          bool PLATEAU = false, class OM>
 __device__ __forceinline__ double close_node(const StepArgs &A, int x, int y,
-                                    double th, const double *om, double *q,
+                                    double th, const OM &om, double *q,
                                     uint32_t known, double mirror,
                                     CloseInfo *ci = nullptr,
                                     int *near = nullptr) {
@@ -557,39 +599,18 @@ __device__ __forceinline__ void node_masks(const StepArgs &A, int x, int y,
   }
 }
 
-// The update of one node from its loads: the next state's populations
-// into v (rounded to the storage type).  QUIET: a kernel built for quiet
-// nodes only (no Newton code, so fewer registers); a node that is not
-// quiet is counted in st.solves, v is left meaningless, and the caller
-// hands its work item to a full kernel.
-template <int Q, typename S, int MODE, bool FAST, bool QUIET = false>
-__device__ __forceinline__ void update_values(const StepArgs &A, int x, int y,
-                                              const NodeLoad<Q, S> &L,
+// The update of one node from its temperature th and its pulled and closed
+// populations q: the next state's populations into v (rounded to the
+// storage type).  QUIET: a kernel built for quiet nodes only (no Newton
+// code, so fewer registers); a node that is not quiet (or near, a wall node
+// close_node marked) is counted in st.solves, v is left meaningless, and
+// the caller hands its work item to a full kernel.
+template <int Q, typename S, int MODE, bool QUIET = false>
+__device__ __forceinline__ void update_pulled(const StepArgs &A, double th,
+                                              const double q[Q], int near,
                                               NodeStats &st, S v[Q]) {
   constexpr bool PLAIN = base_mode(MODE) == kPlain;
   constexpr bool EEBM = base_mode(MODE) == kEebm;
-  constexpr bool NEU = neumann_mode(MODE);
-  double om[Q], q[Q];
-  double th = 0.0;
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    om[j] = (double)L.own[j];
-    th += om[j];
-  }
-#pragma unroll
-  for (int i = 0; i < Q; ++i) q[i] = (double)L.pull[i];
-  int near = 0;
-  if (!FAST) {
-    if (L.known != (1u << Q) - 1u)
-      st.flux_in +=
-          close_node<Q, EEBM ? SCHEME_EEBM : SCHEME_IREBM, NEU, QUIET>(
-              A, x, y, th, om, q, L.known, L.mirror, nullptr, &near);
-    if (L.out) {
-#pragma unroll
-      for (int i = 1; i < Q; ++i)
-        if (L.out >> i & 1u) st.flux_out += om[i];
-    }
-  }
   double m0 = 0.0;
 #pragma unroll
   for (int i = 0; i < Q; ++i) m0 += q[i];
@@ -652,6 +673,37 @@ __device__ __forceinline__ void update_values(const StepArgs &A, int x, int y,
   st.max_it = it > st.max_it ? it : st.max_it;
   st.nonconv += conv ? 0 : 1;
   st.max_res = res > st.max_res ? res : st.max_res;
+}
+
+// The update of one node from its loads (update_pulled after the closures).
+template <int Q, typename S, int MODE, bool FAST, bool QUIET = false>
+__device__ __forceinline__ void update_values(const StepArgs &A, int x, int y,
+                                              const NodeLoad<Q, S> &L,
+                                              NodeStats &st, S v[Q]) {
+  constexpr bool EEBM = base_mode(MODE) == kEebm;
+  constexpr bool NEU = neumann_mode(MODE);
+  double om[Q], q[Q];
+  double th = 0.0;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    om[j] = (double)L.own[j];
+    th += om[j];
+  }
+#pragma unroll
+  for (int i = 0; i < Q; ++i) q[i] = (double)L.pull[i];
+  int near = 0;
+  if (!FAST) {
+    if (L.known != (1u << Q) - 1u)
+      st.flux_in +=
+          close_node<Q, EEBM ? SCHEME_EEBM : SCHEME_IREBM, NEU, QUIET>(
+              A, x, y, th, om, q, L.known, L.mirror, nullptr, &near);
+    if (L.out) {
+#pragma unroll
+      for (int i = 1; i < Q; ++i)
+        if (L.out >> i & 1u) st.flux_out += om[i];
+    }
+  }
+  update_pulled<Q, S, MODE, QUIET>(A, th, q, near, st, v);
 }
 
 // The update of one node from its loads; writes the next state.

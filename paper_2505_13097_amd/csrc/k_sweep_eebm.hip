@@ -1,0 +1,4 @@
+// k_sweep_eebm.hip -- sweep kernels of one node-update mode.
+#include "launch_sweep.hpp"
+
+IREBM_INSTANTIATE_SWEEP(irebm::kEebm);

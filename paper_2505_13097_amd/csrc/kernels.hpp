@@ -203,6 +203,121 @@ __device__ __forceinline__ int xcd_item_front_first(int b, int per_xcd,
   return base + (rk / w) * tiles_x + rk % w + 1;
 }
 
+// ---------------------------------------------------------------------
+// several steps on a tile held in LDS
+
+// k steps of the tile [x0, x1) x [y0, y1) of a 2D lattice, A.src -> A.dst,
+// by one block, a thread per node of the region rx x (n / rx) that holds
+// the tile and a halo of k nodes (lds: n * Q values).  The part of the
+// region that is right shrinks by one node a side and step (walls do not
+// shrink it).  The nodes of the halo are computed by the neighbours as
+// well, from the same values by the same code (update_values), so the
+// states are those of k single steps bit for bit; statistics count the
+// tile's own nodes.  The mirror of a Neumann wall node reads two cells
+// inward, which the width of a tile (at least two nodes) keeps inside the
+// region.
+// mid: when given, step l < k of the own nodes is also stored at mid + l *
+// mid_stride bytes (the reverse mode's recomputed states).
+template <int Q, typename S, int MODE>
+__device__ __forceinline__ void tile_body(const StepArgs &A, int k, int x0,
+                                          int x1, int y0, int y1, int rx,
+                                          int n, S *lds, char *mid,
+                                          int64_t mid_stride, StatSlot *slot) {
+  constexpr bool NEU = neumann_mode(MODE);
+  const int nx = A.nx, ny = A.ny;
+  const int64_t PL = A.plane;
+  const int RX = rx, N = n;
+  const int t = (int)threadIdx.x;
+  const int lx = t % RX, ly = t / RX;
+  const int x = x0 - k + lx, y = y0 - k + ly;   // before wrapping
+  const int w = x1 - x0 + 2 * k, h = y1 - y0 + 2 * k;  // used part
+  const bool px = A.periodic_x != 0, py = A.periodic_y != 0;
+  int gx = x, gy = y;
+  if (px) gx = ((x % nx) + nx) % nx;
+  if (py) gy = ((y % ny) + ny) % ny;
+  const bool node = t < N && lx < w && ly < h && gx >= 0 && gx < nx &&
+                    gy >= 0 && gy < ny;
+  const bool own = node && x >= x0 && x < x1 && y >= y0 && y < y1;
+  const int64_t at = node ? (int64_t)gy * nx + gx : 0;
+  {
+    const gptr<const S> src = to_global((const S *)A.src);
+    S v[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) v[j] = src[j * PL + at];
+    if (node) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) lds[j * N + t] = v[j];
+    }
+  }
+  __syncthreads();
+  NodeStats st;
+  NodeLoad<Q, S> L;
+  if (node) node_masks<Q>(A, gx, gy, L.known, L.out);
+  int mx = 0, my = 0;
+  bool mirror = false;
+  if (NEU && node) mirror = neumann_mirror<Q>(A, gx, gy, mx, my);
+  const int mt = mirror ? t + (mx - gx) + (my - gy) * RX : 0;
+  for (int l = 1; l <= k; ++l) {
+    // arguments re-read in every step (see step_item)
+    int z = 0;
+    asm volatile("" : "+s"(z));
+    const StepArgs &B = (&A)[z];
+    const bool act = node && lx >= l && lx < w - l && ly >= l && ly < h - l;
+    S v[Q];
+    if (act) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) L.own[j] = lds[j * N + t];
+      L.pull[0] = L.own[0];
+#pragma unroll
+      for (int i = 1; i < Q; ++i) {
+        // (an active node has its eight neighbours inside the region;
+        // those beyond a wall hold nothing and are masked)
+        const S u = lds[i * N + t - cx<Q>(i) - cy<Q>(i) * RX];
+        L.pull[i] = (L.known >> i & 1u) ? u : (S)0;
+      }
+      L.mirror = 0.0;
+      if (NEU && mirror) {
+        double m = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+          m += (double)lds[i * N + mt - cx<Q>(i) - cy<Q>(i) * RX];
+        L.mirror = m;
+      }
+      NodeStats one;
+      update_values<Q, S, MODE, false>(B, gx, gy, L, one, v);
+      if (own) {
+        st.max_it = max(st.max_it, one.max_it);
+        st.nonconv += one.nonconv;
+        st.max_res = fmax(st.max_res, one.max_res);
+        st.flux_in += one.flux_in;
+        st.flux_out += one.flux_out;
+      }
+    }
+    if (l == k) {
+      if (own) {
+        const gptr<S> dst = to_global((S *)B.dst);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) dst[j * PL + at] = v[j];
+      }
+      break;
+    }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) lds[j * N + t] = v[j];
+    }
+    if (mid && own) {
+      const gptr<S> dst = to_global((S *)(mid + l * mid_stride));
+#pragma unroll
+      for (int j = 0; j < Q; ++j) dst[j * PL + at] = v[j];
+    }
+    __syncthreads();
+  }
+  StatSlot pre{};
+  if (t == 0) pre = *slot;
+  block_stats_to_slot<false>(st, false, pre, slot);
+}
+
 namespace {
 
 
@@ -560,127 +675,26 @@ void step2_kernel(StepArgs A, int32_t nstrips, int32_t seg_rows,
 // ---------------------------------------------------------------------
 // small 2D lattices: several steps per launch on tiles held in LDS
 
-// k steps (1 <= k <= P.k) of one 2D lattice, A.src -> A.dst.  On a small
-// lattice a step is a chain of latencies: the launch, the loads, one Newton
-// solve, the stores.  A block therefore holds its tile and a halo of k
-// nodes in LDS and takes k steps on it, the region that is right shrinking
-// by one node a side and step (walls do not shrink it), so the launch and
-// the global round trip are paid once; a node is one thread's, so a step
-// is one solve long.  The nodes of the halo are computed by the neighbours
-// as well, from the same values by the same code (update_values), so the
-// states are those of k single steps bit for bit; statistics count a
-// tile's own nodes.  The mirror of a Neumann wall node reads two cells
-// inward, which the width of a tile keeps inside the region.
-// mid: when given, step l < k of the own nodes is also stored at mid + l *
-// mid_stride bytes (the reverse mode's recomputed states).
+// k steps (1 <= k <= P.k) of one small 2D lattice, A.src -> A.dst.  On a
+// small lattice a step is a chain of latencies: the launch, the loads, one
+// Newton solve, the stores.  So a block holds a tile in LDS and takes k
+// steps on it, the launch and the global round trip are paid once, and a
+// node is one thread's, so a step is one solve long.
 template <int Q, typename S, int MODE>
 __global__ __launch_bounds__(1024) void tile_kernel(StepArgs A, TilePlan P,
                                                     int32_t k, char *mid,
                                                     int64_t mid_stride) {
   extern __shared__ char tile_lds[];
-  S *lds = (S *)tile_lds;
-  constexpr bool NEU = neumann_mode(MODE);
   const int tiles = P.ntx * P.nty;
   const int per_xcd = (tiles + 7) >> 3;
   const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
   if (tile >= tiles) return;
   const int tx = tile % P.ntx, ty = tile / P.ntx;
-  const int nx = A.nx, ny = A.ny;
-  const int64_t PL = A.plane;
-  const int x0 = (int)((int64_t)tx * nx / P.ntx);
-  const int x1 = (int)((int64_t)(tx + 1) * nx / P.ntx);
-  const int y0 = (int)((int64_t)ty * ny / P.nty);
-  const int y1 = (int)((int64_t)(ty + 1) * ny / P.nty);
-  const int RX = P.rx, N = P.rx * P.ry;
-  const int t = (int)threadIdx.x;
-  const int lx = t % RX, ly = t / RX;
-  const int x = x0 - k + lx, y = y0 - k + ly;   // before wrapping
-  const int w = x1 - x0 + 2 * k, h = y1 - y0 + 2 * k;  // used part
-  const bool px = A.periodic_x != 0, py = A.periodic_y != 0;
-  int gx = x, gy = y;
-  if (px) gx = ((x % nx) + nx) % nx;
-  if (py) gy = ((y % ny) + ny) % ny;
-  const bool node = t < N && lx < w && ly < h && gx >= 0 && gx < nx &&
-                    gy >= 0 && gy < ny;
-  const bool own = node && x >= x0 && x < x1 && y >= y0 && y < y1;
-  const int64_t at = node ? (int64_t)gy * nx + gx : 0;
-  {
-    const gptr<const S> src = to_global((const S *)A.src);
-    S v[Q];
-#pragma unroll
-    for (int j = 0; j < Q; ++j) v[j] = src[j * PL + at];
-    if (node) {
-#pragma unroll
-      for (int j = 0; j < Q; ++j) lds[j * N + t] = v[j];
-    }
-  }
-  __syncthreads();
-  NodeStats st;
-  NodeLoad<Q, S> L;
-  if (node) node_masks<Q>(A, gx, gy, L.known, L.out);
-  int mx = 0, my = 0;
-  bool mirror = false;
-  if (NEU && node) mirror = neumann_mirror<Q>(A, gx, gy, mx, my);
-  const int mt = mirror ? t + (mx - gx) + (my - gy) * RX : 0;
-  for (int l = 1; l <= k; ++l) {
-    // arguments re-read in every step (see step_item)
-    int z = 0;
-    asm volatile("" : "+s"(z));
-    const StepArgs &B = (&A)[z];
-    const bool act = node && lx >= l && lx < w - l && ly >= l && ly < h - l;
-    S v[Q];
-    if (act) {
-#pragma unroll
-      for (int j = 0; j < Q; ++j) L.own[j] = lds[j * N + t];
-      L.pull[0] = L.own[0];
-#pragma unroll
-      for (int i = 1; i < Q; ++i) {
-        // (an active node has its eight neighbours inside the region;
-        // those beyond a wall hold nothing and are masked)
-        const S u = lds[i * N + t - cx<Q>(i) - cy<Q>(i) * RX];
-        L.pull[i] = (L.known >> i & 1u) ? u : (S)0;
-      }
-      L.mirror = 0.0;
-      if (NEU && mirror) {
-        double m = 0.0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i)
-          m += (double)lds[i * N + mt - cx<Q>(i) - cy<Q>(i) * RX];
-        L.mirror = m;
-      }
-      NodeStats one;
-      update_values<Q, S, MODE, false>(B, gx, gy, L, one, v);
-      if (own) {
-        st.max_it = max(st.max_it, one.max_it);
-        st.nonconv += one.nonconv;
-        st.max_res = fmax(st.max_res, one.max_res);
-        st.flux_in += one.flux_in;
-        st.flux_out += one.flux_out;
-      }
-    }
-    if (l == k) {
-      if (own) {
-        const gptr<S> dst = to_global((S *)B.dst);
-#pragma unroll
-        for (int j = 0; j < Q; ++j) dst[j * PL + at] = v[j];
-      }
-      break;
-    }
-    __syncthreads();
-    if (act) {
-#pragma unroll
-      for (int j = 0; j < Q; ++j) lds[j * N + t] = v[j];
-    }
-    if (mid && own) {
-      const gptr<S> dst = to_global((S *)(mid + l * mid_stride));
-#pragma unroll
-      for (int j = 0; j < Q; ++j) dst[j * PL + at] = v[j];
-    }
-    __syncthreads();
-  }
-  StatSlot pre{};
-  if (t == 0) pre = A.slots[tile];
-  block_stats_to_slot<false>(st, false, pre, A.slots + tile);
+  const int64_t nx = A.nx, ny = A.ny;
+  tile_body<Q, S, MODE>(A, k, (int)(tx * nx / P.ntx),
+                        (int)((tx + 1) * nx / P.ntx), (int)(ty * ny / P.nty),
+                        (int)((ty + 1) * ny / P.nty), P.rx, P.rx * P.ry,
+                        (S *)tile_lds, mid, mid_stride, A.slots + tile);
 }
 
 // ---------------------------------------------------------------------

@@ -1,0 +1,68 @@
+// launch_sweep.hpp -- launches of sweep_kernel for one node-update mode,
+// instantiated by the k_sweep_<mode>.hip units and reached through
+// sweep_launch (lbm_stefan_internal.hpp).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "host_util.hpp"
+#include "lbm_stefan_internal.hpp"
+#include "sweep2d.hpp"
+
+namespace irebm {
+namespace {
+
+template <int Q, typename S, int MODE>
+hipError_t launch_sweep_t(const StepArgs &A, const SweepPlan &P, int k,
+                          char *mid, int64_t mid_stride, hipStream_t stream) {
+  if constexpr (Q == 3) {
+    return hipErrorInvalidValue;
+  } else {
+    if (k < 2 || k > P.k) return hipErrorInvalidValue;
+    // strips as wide as k steps allow
+    SweepPlan R = P;
+    const int w = 64 - 2 * k;
+    R.strips = (P.xb - P.xa + w - 1) / w;
+    const int64_t ct = (R.tiles() + 7) / 8;
+    const int64_t cw = (((R.waves() + 7) / 8) + 3) / 4;
+    const unsigned grid = (unsigned)(8 * (ct + cw));
+#define SWEEP(K, MID) \
+  sweep_kernel<Q, S, MODE, K, MID><<<grid, 256, 0, stream>>>(A, R, mid, mid_stride)
+#define SWEEP_K(MID)           \
+  do {                         \
+    if (k == 4) SWEEP(4, MID); \
+    else if (k == 3) SWEEP(3, MID); \
+    else SWEEP(2, MID);        \
+  } while (0)
+    if (k > 4) return hipErrorInvalidValue;
+    // the states in between: the reverse mode's recomputation (IREBM)
+    if (mid) {
+      if constexpr (MODE == kSafeguarded || MODE == kPlain) SWEEP_K(true);
+      else return hipErrorInvalidValue;
+    } else {
+      SWEEP_K(false);
+    }
+#undef SWEEP_K
+#undef SWEEP
+    return hipGetLastError();
+  }
+}
+
+}  // namespace
+
+template <int MODE>
+hipError_t sweep_launch_mode(int q, int storage, const StepArgs &A,
+                             const SweepPlan &P, int k, char *mid,
+                             int64_t mid_stride, hipStream_t stream) {
+  return dispatch_qs(q, storage, [&](auto qt, auto tt) {
+    QS_TYPES(qt, tt);
+    return launch_sweep_t<Q, S, MODE>(A, P, k, mid, mid_stride, stream);
+  });
+}
+
+}  // namespace irebm
+
+#define IREBM_INSTANTIATE_SWEEP(M)                                         \
+  template hipError_t irebm::sweep_launch_mode<M>(                         \
+      int, int, const irebm::StepArgs &, const irebm::SweepPlan &, int,    \
+      char *, int64_t, hipStream_t)

@@ -151,6 +151,10 @@ irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
       mt = std::max(mt, items_for(v[i], p->nx, p->ny));
     const TilePlan tp = plan_for(*p);
     mt = std::max(mt, (int64_t)tp.ntx * tp.nty);
+    // (a launch of fewer steps has wider strips, so no more items)
+    mt = std::max(mt, sweep_default(*p).slots());
+    for (int i = 0; i < nv; ++i)
+      if (v[i].tb) mt = std::max(mt, sweep_variant(*p, v[i]).slots());
   }
   L.max_items = mt;
   L.n_partials = (n + kEnergyChunk - 1) / kEnergyChunk;
@@ -447,8 +451,21 @@ hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
                      v.rev && (h->steps & 1), stream ? stream : h->stream);
 }
 
+void irebm::plan_steps(lbm_stefan_t *h) {
+  h->plan = TilePlan();
+  h->sweep = SweepPlan();
+  if (h->p.dim != 2) return;
+  if (h->by_default) {
+    h->sweep = sweep_default(h->p);
+    if (h->sweep.k == 0) h->plan = plan_for(h->p);
+  } else {
+    int nv;
+    h->sweep = sweep_variant(h->p, variants(h->p.q, &nv)[h->variant]);
+  }
+}
+
 int irebm::steps_per_launch(const lbm_stefan_t *h) {
-  return h->by_default && h->plan.k > 1 ? h->plan.k : 1;
+  return std::max(1, std::max(h->plan.k, h->sweep.k));
 }
 
 int irebm::next_launch(const lbm_stefan_t *h, int64_t nsteps) {
@@ -465,8 +482,11 @@ hipError_t irebm::launch_steps(const lbm_stefan_t *h, const void *src,
   fill_step_args(h, &A);
   A.src = src;
   A.dst = dst;
-  return tile_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->plan, k,
-                     stream, (char *)mid, mid_stride);
+  if (h->plan.k > 0)
+    return tile_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->plan, k,
+                       stream, (char *)mid, mid_stride);
+  return sweep_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->sweep, k,
+                      stream, (char *)mid, mid_stride);
 }
 
 namespace {
@@ -579,7 +599,7 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
                                                       : kDefaultVariant1D)
                                                : default_2d(*p)));
   h->by_default = p->variant < 0;
-  h->plan = plan_for(*p);
+  plan_steps(h);
   h->stream = (hipStream_t)stream;
   if (hipGetDevice(&h->device) != hipSuccess) {
     delete h;
@@ -791,6 +811,7 @@ int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant) {
   DeviceGuard g(h->device);
   h->variant = variant;
   h->by_default = false;
+  plan_steps(h);
   // the tile -> slot mapping changes with the tile shape
   HIPCHK(h, zero_stats_async(h));
   return LBM_STEFAN_OK;
@@ -833,7 +854,7 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   hipError_t err = hipSuccess;
   // the library default's launches of several steps are one more trial,
   // after the variants, under its one-step variant's index
-  const int trials = nv + (h->plan.k > 1 ? 1 : 0);
+  const int trials = nv + (p.dim == 2 ? 1 : 0);
   for (int trial = 0; trial < trials && err == hipSuccess; ++trial) {
     const int v = trial < nv ? trial : default_2d(p);
     h->by_default = trial == nv;
@@ -843,6 +864,9 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     if (vt && vt[v].res && !resident_ok(p)) continue;
     if (vt && vt[v].tb == 2) continue;  // single lattices: same as tb = 1
     h->variant = v;
+    plan_steps(h);
+    // a default that launches single steps is its variant's trial
+    if (trial == nv && steps_per_launch(h) == 1) continue;
     // two untimed steps, then the timed trial (an even count, so that a
     // two-step variant runs its own kernel only)
     const int64_t n = steps + (steps & 1);
@@ -872,6 +896,7 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   h->cur = cur0;
   h->variant = best;
   h->by_default = best_default;
+  plan_steps(h);
   if (err != hipSuccess)
     return fail(h, LBM_STEFAN_EDEVICE,
                 std::string("autotune: ") + hipGetErrorString(err));

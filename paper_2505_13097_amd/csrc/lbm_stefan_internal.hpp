@@ -9,6 +9,7 @@
 #include "kernels.hpp"
 #include "lattice3d.hpp"
 #include "lbm_stefan.h"
+#include "sweep2d.hpp"
 
 namespace irebm {
 
@@ -55,10 +56,13 @@ struct lbm_stefan {
   double *small = nullptr;
   char *adj = nullptr;
   int variant = 0;
-  // the library default (params.variant = -1): small 2D lattices take
-  // several steps per launch on tiles in LDS (plan.k > 0)
+  // several steps per launch: the library default (params.variant = -1)
+  // takes tiles in LDS on small 2D lattices (plan.k > 0) and sweeps on large
+  // ones, the two-step variants sweep where the lattice is large enough
+  // (sweep.k > 0, set with the variant)
   bool by_default = false;
   irebm::TilePlan plan;
+  irebm::SweepPlan sweep;
   int64_t steps = 0;
   void *tape = nullptr;          // last forward tape
   int64_t tape_steps = 0, tape_interval = 0;
@@ -87,8 +91,10 @@ void fill_args(const lbm_stefan_params &p, double *const prof[4],
 void fill_step_args(const lbm_stefan_t *h, StepArgs *A);
 hipError_t launch_step(const lbm_stefan_t *h, const void *src, void *dst,
                        hipStream_t stream = nullptr);
-// Steps one launch takes under the library default (1: a launch a step),
-// and the steps of the next launch of nsteps (at most that many, the
+// the plans of the handle's variant (or of the library default)
+void plan_steps(lbm_stefan_t *h);
+// Steps one launch of tile_kernel or sweep_kernel takes under the handle's
+// variant (1: it takes neither), and the steps of the next launch of nsteps (at most that many, the
 // launches as even as they come).
 int steps_per_launch(const lbm_stefan_t *h);
 int next_launch(const lbm_stefan_t *h, int64_t nsteps);
@@ -153,6 +159,11 @@ hipError_t step2_launch_mode(int q, int storage, const StepArgs &A,
 template <int MODE>
 hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
                              const Variant &v, hipStream_t stream);
+// k steps (2 to 4, at most P.k) of a large 2D lattice (sweep_kernel)
+template <int MODE>
+hipError_t sweep_launch_mode(int q, int storage, const StepArgs &A,
+                             const SweepPlan &P, int k, char *mid,
+                             int64_t mid_stride, hipStream_t stream);
 // k steps of a small 2D lattice on tiles in LDS (tile_kernel)
 template <int MODE>
 hipError_t tile_launch_mode(int q, int storage, const StepArgs &A,
@@ -167,6 +178,9 @@ hipError_t resident_launch_mode(int storage, const StepArgs &A,
 #define IREBM_DECLARE_STEP1(M)                                             \
   extern template hipError_t step_launch_mode<M>(                          \
       int, int, const StepArgs &, const Variant &, bool, hipStream_t);     \
+  extern template hipError_t sweep_launch_mode<M>(                         \
+      int, int, const StepArgs &, const SweepPlan &, int, char *, int64_t, \
+      hipStream_t);                                                        \
   extern template hipError_t tile_launch_mode<M>(                          \
       int, int, const StepArgs &, const TilePlan &, int, char *, int64_t,  \
       hipStream_t)
@@ -262,6 +276,26 @@ inline hipError_t step_launch(int mode, int q, int storage, const StepArgs &A,
     default:
       return step_launch_mode<kSafeguarded>(q, storage, A, v, reverse,
                                             stream);
+  }
+}
+
+// k steps of one large 2D lattice (sweep_kernel)
+inline hipError_t sweep_launch(int mode, int q, int storage,
+                               const StepArgs &A, const SweepPlan &P, int k,
+                               hipStream_t stream, char *mid = nullptr,
+                               int64_t mid_stride = 0) {
+  switch (mode) {
+#define IREBM_SWEEP_CASE(M) \
+  case M:                   \
+    return sweep_launch_mode<M>(q, storage, A, P, k, mid, mid_stride, stream)
+    IREBM_SWEEP_CASE(kEebm);
+    IREBM_SWEEP_CASE(kPlain);
+    IREBM_SWEEP_CASE(kEebm | kNeumann);
+    IREBM_SWEEP_CASE(kPlain | kNeumann);
+    IREBM_SWEEP_CASE(kSafeguarded | kNeumann);
+    default:
+    IREBM_SWEEP_CASE(kSafeguarded);
+#undef IREBM_SWEEP_CASE
   }
 }
 

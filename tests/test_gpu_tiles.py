@@ -1,5 +1,6 @@
-"""Several steps per launch on tiles in LDS (the library default of small 2D
-lattices) against one-step launches: the states bit for bit, the Newton
+"""Several steps per launch (the library default of 2D lattices: tiles in LDS
+on small ones, sweeping waves with a frame of tiles on large ones; and the
+two-step variants, which sweep too) against one-step launches: the states bit for bit, the Newton
 counters equal, energies and boundary fluxes to the rounding of their sums
 (1e-12 of the sum of the magnitudes, a few thousand FP64 terms)."""
 import numpy as np
@@ -65,16 +66,71 @@ def test_tiles_equal_single_steps(size, scheme):
     print(f"{nx}x{ny} {scheme}: equal", flush=True)
 
 
-@pytest.mark.parametrize("n", [1100, 1500])
-def test_large_tiles_equal_single_steps(n):
-    """EEBM in FP64 keeps the tiles on lattices of millions of nodes (both
-    of its large tile sizes)."""
-    one = variant_names(9, "f64").index("64x1/npt1")
-    prob = _prob(n, n + 37, 9, WALLS[1], "f64", "eebm")
-    a, sa = _run(prob, (9,), -1)
-    b, sb = _run(prob, (9,), one)
-    assert np.array_equal(a, b)
-    assert sa["steps"] == sb["steps"] == 9
+# the narrowest and lowest lattices the frame leaves a strip of, one column
+# (row) less, ragged strips and segments, a strip's lanes nearly all in use
+# or nearly none
+SWEEP_SIZES = [(88, 700), (87, 700), (120, 560), (700, 40), (1700, 31),
+               (64, 1000), (63, 1000), (145, 431), (257, 251), (700, 531)]
+
+
+@pytest.mark.parametrize("scheme", ["irebm", "eebm"])
+@pytest.mark.parametrize("size", SWEEP_SIZES, ids=lambda s: f"{s[0]}x{s[1]}")
+def test_sweeps_equal_single_steps(size, scheme):
+    """Fields of three kinds: solid with a hot wall (nearly every row quiet),
+    noise across the melting band (a solve everywhere), and liquid with a
+    solid corner (rows of solid and liquid nodes with no band between)."""
+    nx, ny = size
+    rng = np.random.default_rng(7 * nx + ny)
+    names = variant_names(5, "f64")
+    one, two = names.index("64x1/npt1"), names.index("128x4/t2/r32/nt")
+    solid = -0.5 + rng.uniform(-1e-3, 1e-3, (ny, nx))
+    solid[:, :5] = np.linspace(1.0, -0.4, 5)
+    noise = rng.uniform(-0.6, 0.6, (ny, nx))
+    liquid = 0.8 + rng.uniform(-1e-3, 1e-3, (ny, nx))
+    liquid[: ny // 2, nx // 2:] = -0.7
+    cases = [(5, "f32", WALLS[0], solid, 0.005), (9, "f32", WALLS[1], solid,
+                                                   0.005),
+             (9, "f64", WALLS[2], noise, 0.05), (5, "f64", WALLS[3], noise,
+                                                 0.05),
+             (9, "f32", WALLS[4], liquid, 0.01), (5, "f64", WALLS[1], liquid,
+                                                  0.01)]
+    if scheme == "eebm":
+        cases += [(9, "f64", WALLS[5], noise, 0.05)]
+    for q, storage, bc, T0, delta in cases:
+        prob = _prob(nx, ny, q, bc, storage, scheme).with_(T0=T0, delta=delta)
+        steps = (2, 7, 12)
+        b, sb = _run(prob, steps, one)
+        for v in (-1, two):
+            a, sa = _run(prob, steps, v)
+            tag = (nx, ny, q, storage, bc, v)
+            assert np.array_equal(a, b), tag
+            for k in ("steps", "max_newton_it", "nonconverged",
+                      "max_residual"):
+                assert sa[k] == sb[k], (tag, k)
+            bar = 1e-12 * (abs(sb["energy"]) + 21 * 9 * nx * ny)
+            for k in ("energy", "flux_in", "flux_out"):
+                assert abs(sa[k] - sb[k]) <= bar, (tag, k)
+    print(f"{nx}x{ny} {scheme}: equal", flush=True)
+
+
+def test_reverse_mode_over_sweeps():
+    """The tape of a lattice whose forward steps sweep: checkpoints and every
+    recomputed state are those of single steps, so the gradients are equal
+    bit for bit."""
+    prob = _prob(300, 260, 5, WALLS[0], "f32", "irebm").with_(
+        T0=np.full((260, 300), -0.5), delta=0.005,
+        wall_profile=(1.0 + 0.1 * np.sin(np.arange(260) / 20.0), None, None,
+                      None))
+    g = np.linspace(0.5, 1.5, 260)
+    out = []
+    for v in (-1, variant_names(5, "f32").index("64x1/npt1")):
+        s = Stefan(prob, variant=v, flags=1)
+        tape = s.forward_tape(23, 6)
+        out.append((s.state(), s.backward_tape(g, tape)))
+        s.close()
+    (sa, (wa, ga, da)), (sb, (wb, gb, db)) = out
+    assert np.array_equal(sa, sb)
+    assert ga == gb and da == db and np.array_equal(wa["x-"], wb["x-"])
 
 
 def test_autotune_keeps_the_state_of_a_tiled_lattice():
