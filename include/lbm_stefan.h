@@ -287,10 +287,11 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    non-temporal stores, block order reversed every other step; or
    "<w>x<b>/t2/r<m>[/nt]": two time steps per launch, a w-column window
    sweeping m rows, b rows per pass, on lattices of about 100 columns or
-   fewer, and up to four steps per launch by waves sweeping m rows on wider
-   ones; a single trailing step then uses the default variant, and a lattice
-   with a Neumann wall runs the default variant; q = 3 also "resident2048": D1Q3 lattices of at most 2048 nodes
-   with no Neumann wall run many steps per launch in one workgroup, both
+   fewer, and up to four steps per launch by waves sweeping m rows (at most
+   32 in the batched form) on wider ones and in the batched form; a single
+   trailing step then uses the default variant, and a lattice with a Neumann
+   wall runs the default variant; q = 3 also "resident2048": D1Q3 lattices of
+   at most 2048 nodes with no Neumann wall run many steps per launch in one workgroup, both
    states in LDS (others run the default variant; the batched form rejects
    it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z
    slices swept by one block); used by autotuners. */
@@ -471,10 +472,11 @@ int lbm_stefan_batch_init(const lbm_stefan_params *params, int32_t count,
 /*
  * Schedule: kernel variant (-1: default); blocks_per_cu 0 launches one
  * block per work item (in XCD-contiguous chunks of the item table), 1..32 a
- * persistent grid of blocks_per_cu x compute units walking the table; and
+ * persistent grid of blocks_per_cu x compute units walking the table
+ * (one-step variants); and
  * graph_steps (even, 0..1e5):
  * when > 0, lbm_stefan_batch_step replays a captured hipGraph of that many
- * launches (captured on first use) and launches any remainder directly.
+ * steps (captured on first use) and launches any remainder directly.
  * Changing the variant resets statistics.
  */
 int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,

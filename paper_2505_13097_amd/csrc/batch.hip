@@ -12,13 +12,11 @@
 // the single-lattice step (step_item), so a batch member evolves exactly
 // as the same lattice run alone, IREBM or EEBM alike.  Steps can be
 // captured in a hipGraph; the autotuner picks the tile variant and the
-// grid size.  Under a split two-step variant (tb = 2, IREBM) a launch of
-// two steps is three kernels: the front strips (the first columns of each
-// instance heated at x = 0) on a stream of their own, beside the quiet
-// pass over the other items, then the full pass over the items the quiet
-// pass flagged (see batch_step2_kernel).  This unit is the
-// host side; the kernels and their launches are in launch.hpp
-// (instantiated by k_batch_<mode>.hip).
+// grid size.  Under a two-step variant a launch takes up to four steps by
+// sweeping waves, the walls and fronts of every instance as a frame of small
+// tiles in LDS (batch_sweep_kernel, sweep2d.hpp).  This unit is the host
+// side; the kernels and their launches are in launch.hpp and
+// launch_sweep.hpp (instantiated by k_batch_<mode>.hip, k_bsweep_<mode>.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,21 +39,15 @@ struct lbm_stefan_batch {
   int mode = kSafeguarded;  // node-update mode shared by the instances
   int device = 0, cus = 0;
   hipStream_t stream = nullptr, cap_stream = nullptr;
-  // split schedule: the front passes run on a stream of their own, forked
-  // from and joined back into the launching stream by two events
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
   char *ws = nullptr;
   StepArgs *descs = nullptr;
   int2 *items = nullptr;
   StatSlot *slots = nullptr;
-  int *flags = nullptr;        // split schedule: one flag per work item
-  int2 *fitems = nullptr;      // split schedule: front segments
+  SweepPlan *plans = nullptr;  // two-step variants
   double *profs = nullptr, *partials = nullptr, *small = nullptr;
   char *state[2] = {nullptr, nullptr};
   size_t state_bytes = 0;
-  bool split_ok = false;       // a split two-step schedule can run
-  int64_t nslots = 0, nfitems = 0;
+  int64_t nslots = 0, ntiles = 0;
   std::vector<size_t> off;          // instance offset in a state region
   std::vector<size_t> prof_off;     // instance offset in the profiles
   std::vector<int64_t> first_item, nitems_inst;
@@ -70,48 +62,29 @@ struct lbm_stefan_batch {
 namespace {
 
 struct BLayout {
-  size_t descs, items, slots, flags, fitems, profs, partials, small, stateA,
-      stateB, total;
+  size_t descs, items, slots, plans, profs, partials, small, stateA, stateB,
+      total;
   size_t state_bytes;
-  int64_t max_items, max_fitems, nslots, max_parts, small_len;
-  bool split_ok;
+  int64_t max_items, max_parts, small_len;
   std::vector<size_t> off, prof_off;
 };
 
-// a split two-step schedule needs Newton solves to split off (not EEBM)
-// and 2D lattices
-bool split_applies(const lbm_stefan_params &p) {
-  return p.q != 3 && p.scheme != LBM_SCHEME_EEBM;
+// work items (and statistics slots) of an instance under variant v
+int64_t batch_items(const Variant &v, const lbm_stefan_params &p) {
+  return v.tb ? batch_plan(p, v).slots() : items_for(v, p.nx, p.ny);
 }
 
-// instances whose strip 0 runs the front pass: heated through a Dirichlet
-// wall at x = 0 (a profile, or a temperature not on phi's lower plateau)
-bool front_strip(const lbm_stefan_params &p) {
-  return p.bc[0] == LBM_BC_DIRICHLET &&
-         (p.wall_profile[0] || p.wall_T[0] >= p.t_m - 20.0 * p.delta);
-}
-
-// front segments (batch_front_kernel items) of a lattice of ny rows
-int64_t front_items(const lbm_stefan_params &p) {
-  const int r = p.storage == LBM_STORE_F64 ? front_rows<double>()
-                                           : front_rows<float>();
-  return (p.ny + r - 1) / r;
-}
-
-// columns of the front strip of an instance: the whole lattice when it is
-// at most 64 columns wide (the front kernel's window), else the first
-// kFrontColumns
-int front_cols(const Variant &v, int64_t nx) {
-  (void)v;
-  return nx <= 64 ? (int)nx : kFrontColumns;
-}
-
-// two-step work items of an instance with a front strip: strips shifted
-// by (bx - 4) - front_cols columns, so one more strip column at most
-int64_t shifted_items(const Variant &v, int64_t nx, int64_t ny) {
-  const int64_t w = v.bx - 4;
-  return ((nx + w - front_cols(v, nx) + w - 1) / w) *
-         ((ny + v.rows - 1) / v.rows);
+// the variant a batch starts with (and -1 selects): sweeping waves, which
+// win on every mix measured, unless a member is an IREBM melt that freezes
+// (see sweep_default)
+int default_variant(const lbm_stefan_params *ps, int count) {
+  if (ps[0].q == 3) return kDefaultVariant1D;
+  for (int k = 0; k < count; ++k) {
+    bool hot;
+    front_walls(ps[k], &hot);
+    if (ps[k].scheme == LBM_SCHEME_IREBM && !hot) return kDefaultVariant2D;
+  }
+  return kSweepVariant2D;
 }
 
 int bfail(lbm_stefan_batch_t *b, int code, const std::string &msg) {
@@ -157,19 +130,11 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   int nv;
   const Variant *v = variants(ps[0].q, &nv);
   L.max_items = 0;
-  L.split_ok = split_applies(ps[0]);
   for (int i = 0; i < nv; ++i) {
     int64_t t = 0;
-    for (int k = 0; k < count; ++k)
-      t += v[i].tb == 2 && L.split_ok && front_strip(ps[k])
-               ? shifted_items(v[i], ps[k].nx, ps[k].ny)
-               : items_for(v[i], ps[k].nx, ps[k].ny);
+    for (int k = 0; k < count; ++k) t += batch_items(v[i], ps[k]);
     L.max_items = std::max(L.max_items, t);
   }
-  L.max_fitems = 0;
-  for (int k = 0; k < count && L.split_ok; ++k)
-    if (front_strip(ps[k])) L.max_fitems += front_items(ps[k]);
-  L.nslots = L.max_items + L.max_fitems;
   L.state_bytes = 0;
   L.off.resize(count);
   L.prof_off.resize(count);
@@ -192,11 +157,9 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   L.items = o;
   o += align256(L.max_items * sizeof(int2));
   L.slots = o;
-  o += align256(L.nslots * sizeof(StatSlot));
-  L.flags = o;
-  o += L.split_ok ? align256(L.max_items * sizeof(int)) : 0;
-  L.fitems = o;
-  o += align256(L.max_fitems * sizeof(int2));
+  o += align256(L.max_items * sizeof(StatSlot));
+  L.plans = o;
+  o += align256(count * sizeof(SweepPlan));
   L.profs = o;
   o += align256(prof_total * 8);
   L.partials = o;
@@ -211,14 +174,6 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   return L;
 }
 
-void drop_side(lbm_stefan_batch_t *b) {
-  if (b->fork) (void)hipEventDestroy(b->fork);
-  if (b->join) (void)hipEventDestroy(b->join);
-  if (b->side) (void)hipStreamDestroy(b->side);
-  b->fork = b->join = nullptr;
-  b->side = nullptr;
-}
-
 void drop_graphs(lbm_stefan_batch_t *b) {
   for (int k = 0; k < 2; ++k)
     if (b->graph[k]) {
@@ -229,16 +184,14 @@ void drop_graphs(lbm_stefan_batch_t *b) {
 
 // descriptors and item table for the current variant; uploads both and
 // zeroes the statistics (the item -> slot map changes with the items).
-// The statistics slots of instance k are contiguous: its work items, then
-// (split schedule) its front segments.
+// The statistics slots of instance k are contiguous.
 int build_schedule(lbm_stefan_batch_t *b) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
   const Variant &v = vt[b->variant];
-  const bool split = v.tb == 2 && b->split_ok;
   std::vector<StepArgs> d(b->count);
-  std::vector<int2> t, ft;
-  std::vector<int> fl;
+  std::vector<SweepPlan> pl(b->count);
+  std::vector<int2> t, wv;
   t.reserve(b->max_items);
   b->first_item.assign(b->count, 0);
   b->nitems_inst.assign(b->count, 0);
@@ -254,59 +207,39 @@ int build_schedule(lbm_stefan_batch_t *b) {
     d[k].src = b->state[0] + b->off[k];
     d[k].dst = b->state[1] + b->off[k];
     set_tiling(&d[k], v);
-    const bool front = split && front_strip(p);
-    const int w = split ? front_cols(v, p.nx) : 0;  // front strip columns
-    if (front) {
-      // strip 0 narrowed to the front strip's w columns: step n + 1 on
-      // columns [0, w + 1), step n + 2 (and the statistics) on [0, w)
-      d[k].x_lim = (int32_t)std::min<int64_t>(w + 1, p.nx);
-      d[k].x_cnt = (int32_t)std::min<int64_t>(w, p.nx);
-      d[k].x_shift = v.bx - 4 - w;
-      d[k].tiles_x = (int32_t)((p.nx + d[k].x_shift + v.bx - 5) / (v.bx - 4));
-      d[k].nitems = (int32_t)shifted_items(v, p.nx, p.ny);
-      d[k].per_xcd = (d[k].nitems + 7) / 8;
-    }
-    const int64_t nt = d[k].nitems;
+    const int64_t n = batch_items(v, p);
     d[k].slots = b->slots + sbase;
     b->first_item[k] = sbase;
-    for (int64_t i = 0; i < nt; ++i) {
-      t.push_back(make_int2(k, (int)i));
-      if (split) fl.push_back(front && i % d[k].tiles_x == 0 ? 1 : 0);
+    if (v.tb) {
+      pl[k] = batch_plan(p, v);
+      for (int64_t i = 0; i < pl[k].tiles(); ++i)
+        t.push_back(make_int2(k, (int)i));
+      for (int64_t i = 0; i < pl[k].waves(); ++i)
+        wv.push_back(make_int2(k, (int)i));
+    } else {
+      for (int64_t i = 0; i < n; ++i) t.push_back(make_int2(k, (int)i));
     }
-    const int64_t nf = front ? front_items(p) : 0;
-    for (int64_t i = 0; i < nf; ++i) ft.push_back(make_int2(k, (int)i));
-    b->nitems_inst[k] = nt + nf;
-    sbase += nt + nf;
+    b->nitems_inst[k] = n;
+    sbase += n;
   }
+  b->ntiles = (int64_t)t.size();
+  t.insert(t.end(), wv.begin(), wv.end());
   b->nitems = (int64_t)t.size();
-  b->nfitems = (int64_t)ft.size();
   BCHK(b, hipMemcpyAsync(b->descs, d.data(), d.size() * sizeof(StepArgs),
                          hipMemcpyHostToDevice, b->stream));
   BCHK(b, hipMemcpyAsync(b->items, t.data(), t.size() * sizeof(int2),
                          hipMemcpyHostToDevice, b->stream));
-  if (split) {
-    BCHK(b, hipMemcpyAsync(b->flags, fl.data(), fl.size() * sizeof(int),
-                           hipMemcpyHostToDevice, b->stream));
-    if (!ft.empty())
-      BCHK(b, hipMemcpyAsync(b->fitems, ft.data(), ft.size() * sizeof(int2),
-                             hipMemcpyHostToDevice, b->stream));
-  }
+  BCHK(b, hipMemcpyAsync(b->plans, pl.data(), pl.size() * sizeof(SweepPlan),
+                         hipMemcpyHostToDevice, b->stream));
   BCHK(b, zero_async(b->slots, b->nslots * sizeof(StatSlot), b->stream));
-  if (split && !b->side) {
-    BCHK(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
-    BCHK(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
-    BCHK(b, hipEventCreateWithFlags(&b->join, hipEventDisableTiming));
-  }
   BCHK(b, hipStreamSynchronize(b->stream));
   drop_graphs(b);
   return LBM_STEFAN_OK;
 }
 
-// one launch from buffer `parity`: one step, or two under a two-step
-// variant (one if two = false); two steps of a split schedule are the
-// front kernel, the quiet pass and the full pass over flagged items
+// one launch of k steps (at most steps_per_launch) from buffer `parity`
 hipError_t launch_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
-                        int parity, bool two = true) {
+                        int parity, int k) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
   const Variant &v = vt[b->variant];
@@ -317,38 +250,27 @@ hipError_t launch_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
   L.cus = b->cus;
   L.blocks_per_cu = b->blocks_per_cu;
   L.parity = parity;
-  L.two = two;
-  if (!(v.tb == 2 && b->split_ok && two))
-    return batch_launch(b->mode, b->q, b->storage, L, v, stream);
-  // the front kernel (latency-bound: the Newton solves) on the side
-  // stream, the quiet pass (bandwidth-bound) beside it; the full pass over
-  // flagged items after both
-  const bool fr = b->nfitems > 0;
-  if (fr) {
-    hipError_t e = hipEventRecord(b->fork, stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->fork, 0);
-    if (e != hipSuccess) return e;
-    BatchLaunch F = L;
-    F.items = b->fitems;
-    F.nitems = b->nfitems;
-    F.front = true;
-    e = batch_launch(b->mode, b->q, b->storage, F, v, b->side);
-    if (e == hipSuccess) e = hipEventRecord(b->join, b->side);
-    if (e != hipSuccess) return e;
-  }
-  L.flags = b->flags;
-  L.split = 1;
-  hipError_t e = batch_launch(b->mode, b->q, b->storage, L, v, stream);
-  if (e == hipSuccess && fr) e = hipStreamWaitEvent(stream, b->join, 0);
-  if (e != hipSuccess) return e;
-  L.split = 2;
-  return batch_launch(b->mode, b->q, b->storage, L, v, stream);
+  if (!v.tb) return batch_launch(b->mode, b->q, b->storage, L, v, stream);
+  L.plans = b->plans;
+  L.ntiles = b->ntiles;
+  return batch_sweep(b->mode, b->q, b->storage, L, k, stream);
 }
 
-// time steps one launch advances under the current variant
+// time steps one launch advances at most under the current variant
 int steps_per_launch(const lbm_stefan_batch_t *b) {
   int nv;
-  return variants(b->q, &nv)[b->variant].tb ? 2 : 1;
+  return variants(b->q, &nv)[b->variant].tb ? 4 : 1;
+}
+
+// launches of nsteps, and the steps of the first of them (as even as they
+// come)
+int64_t launches_of(const lbm_stefan_batch_t *b, int64_t nsteps) {
+  const int64_t k = steps_per_launch(b);
+  return (nsteps + k - 1) / k;
+}
+int first_launch(const lbm_stefan_batch_t *b, int64_t nsteps) {
+  const int64_t n = launches_of(b, nsteps);
+  return (int)((nsteps + n - 1) / n);
 }
 
 // graph of the launches of graph_steps steps starting at parity `par`
@@ -358,9 +280,12 @@ int ensure_graph(lbm_stefan_batch_t *b, int par) {
     BCHK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   BCHK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t le = hipSuccess;
-  const int launches = b->graph_steps / steps_per_launch(b);
-  for (int s = 0; s < launches && le == hipSuccess; ++s)
-    le = launch_batch(b, b->cap_stream, par ^ (s & 1));
+  int p = par;
+  for (int64_t left = b->graph_steps; left > 0 && le == hipSuccess; p ^= 1) {
+    const int k = first_launch(b, left);
+    le = launch_batch(b, b->cap_stream, p, k);
+    left -= k;
+  }
   hipGraph_t g = nullptr;
   const hipError_t ee = hipStreamEndCapture(b->cap_stream, &g);
   if (le != hipSuccess || ee != hipSuccess) {
@@ -415,7 +340,6 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
   auto bail = [&](int code) {
     set_global_error(b->err);
     drop_graphs(b);
-    drop_side(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     delete b;
     return code;
@@ -430,18 +354,14 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
       hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount,
                             b->device) != hipSuccess)
     return bail(bfail(b, LBM_STEFAN_EDEVICE, "device query failed"));
-  b->variant = b->q == 3 ? kDefaultVariant1D : kDefaultVariant2D;
+  b->variant = default_variant(ps, count);
   char *ws = (char *)workspace;
   b->ws = ws;
   b->descs = (StepArgs *)(ws + L.descs);
   b->items = (int2 *)(ws + L.items);
   b->slots = (StatSlot *)(ws + L.slots);
-  b->split_ok = L.split_ok;
-  b->nslots = L.nslots;
-  if (L.split_ok) {
-    b->flags = (int *)(ws + L.flags);
-    b->fitems = (int2 *)(ws + L.fitems);
-  }
+  b->nslots = L.max_items;
+  b->plans = (SweepPlan *)(ws + L.plans);
   b->profs = (double *)(ws + L.profs);
   b->partials = (double *)(ws + L.partials);
   b->small = (double *)(ws + L.small);
@@ -510,9 +430,8 @@ int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,
   if (graph_steps < 0 || graph_steps % 2 || graph_steps > 100000)
     return bfail(b, LBM_STEFAN_EINVAL,
                  "graph_steps must be even and in 0..100000");
-  const int nvar = variant < 0 ? (b->q == 3 ? kDefaultVariant1D
-                                            : kDefaultVariant2D)
-                               : variant;
+  const int nvar =
+      variant < 0 ? default_variant(b->ps.data(), b->count) : variant;
   DeviceGuard g(b->device);
   b->blocks_per_cu = blocks_per_cu;
   b->graph_steps = graph_steps;
@@ -528,7 +447,6 @@ int lbm_stefan_batch_step(lbm_stefan_batch_t *b, int64_t nsteps) {
   if (!b) return bfail(nullptr, LBM_STEFAN_EINVAL, "batch is NULL");
   if (nsteps < 0) return bfail(b, LBM_STEFAN_EINVAL, "nsteps < 0");
   DeviceGuard g(b->device);
-  const int spl = steps_per_launch(b);
   int64_t left = nsteps;
   if (b->graph_steps > 0) {
     while (left >= b->graph_steps) {
@@ -537,13 +455,15 @@ int lbm_stefan_batch_step(lbm_stefan_batch_t *b, int64_t nsteps) {
       BCHK(b, hipGraphLaunch(b->graph[b->cur], b->stream));
       left -= b->graph_steps;
       b->steps += b->graph_steps;
-      b->cur ^= (b->graph_steps / spl) & 1;
+      b->cur ^= (int)(launches_of(b, b->graph_steps) & 1);
     }
   }
-  for (; left > 0; left -= std::min<int64_t>(left, spl)) {
-    BCHK(b, launch_batch(b, b->stream, b->cur, left >= 2));
+  while (left > 0) {
+    const int k = first_launch(b, left);
+    BCHK(b, launch_batch(b, b->stream, b->cur, k));
     b->cur ^= 1;
-    b->steps += std::min<int64_t>(left, spl);
+    b->steps += k;
+    left -= k;
   }
   return LBM_STEFAN_OK;
 }
@@ -683,9 +603,9 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
       b->variant = v;
       rc = build_schedule(b);
     }
-    // a two-step launch covers two steps; the persistent grid is for
+    // a sweeping launch covers four steps; the persistent grid is for
     // one-step variants only
-    const int spl = vt[v].tb ? 2 : 1;
+    const int spl = steps_per_launch(b);
     const int launches = (steps + spl - 1) / spl;
     for (int bpc : bpcs) {
       if (rc != LBM_STEFAN_OK || err != hipSuccess) break;
@@ -693,7 +613,7 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
       b->blocks_per_cu = bpc;
       for (int s = 0; s < launches + 2 && err == hipSuccess; ++s) {
         if (s == 2) err = hipEventRecord(e0, b->stream);
-        if (err == hipSuccess) err = launch_batch(b, b->stream, b->cur);
+        if (err == hipSuccess) err = launch_batch(b, b->stream, b->cur, spl);
         b->cur ^= 1;
       }
       if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
@@ -739,9 +659,7 @@ int lbm_stefan_batch_destroy(lbm_stefan_batch_t *b) {
   if (!b) return LBM_STEFAN_OK;
   DeviceGuard g(b->device);
   hipError_t e = hipStreamSynchronize(b->stream);
-  if (e == hipSuccess && b->side) e = hipStreamSynchronize(b->side);
   drop_graphs(b);
-  drop_side(b);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   delete b;
   if (e != hipSuccess) return bfail(nullptr, LBM_STEFAN_EDEVICE, hipGetErrorString(e));

@@ -21,11 +21,11 @@ namespace irebm {
 // that the rows written last (still in the memory-side cache) are read
 // first.  tb: two steps per launch (step2_kernel): a window of bx columns
 // (bx - 4 written), by rows per pass, `rows` rows per block, non-temporal
-// stores.  res: D1Q3 lattices of at most kResident1D nodes run many steps
+// stores; where the lattice is large enough, and in the batched form, up to
+// four steps by sweeping waves instead (sweep_kernel, segments of `rows`
+// rows).  res: D1Q3 lattices of at most kResident1D nodes run many steps
 // per launch in one workgroup (resident1d_kernel); others take the default
-// one-step tiling.  tb = 2: the same two-step kernel, run in the batched
-// form with the front split (batch_step2_kernel: quiet pass, front strips,
-// full pass over flagged items); single lattices run it as tb = 1.
+// one-step tiling.  tb = 2: as tb = 1, more segment lengths.
 struct Variant {
   int bx, by, npt, nt, rev, rows, tb, res;
 };
@@ -61,9 +61,8 @@ inline const Variant *variants(int q, int *n) {
 constexpr int kDefaultVariant1D = 0;
 constexpr int kResidentVariant1D = 4;
 constexpr int kDefaultVariant2D = 3;
-// split two-step schedule: the front strip of an instance heated at x = 0
-// is its first kFrontColumns columns (batch_front_kernel: at most 63)
-constexpr int kFrontColumns = 60;
+// 128x2/t2s/r32/nt: the batched form's default (sweeping waves)
+constexpr int kSweepVariant2D = 32;
 
 inline int64_t tiles_x_for(const Variant &v, int64_t nx) {
   const int64_t tw = (int64_t)v.bx * v.npt;
@@ -156,7 +155,10 @@ inline int front_walls(const lbm_stefan_params &p, bool *hot) {
 // small for the frame and a strip.  The frame is two tiles deep where a
 // front starts (a strip that reaches the front solves in every row: the
 // 8192^2 cavity takes 380 us per step with one tile, 324 with two, 347 and
-// 330 with three and four), one at the other walls.
+// 330 with three and four), one at the other walls.  The strip next to it
+// goes in segments of 8 rows: the batch named at batch_plan, its fronts past
+// the frame, takes 622 us with segments as everywhere, 560 with 16, 505 with
+// 8 and 520 with 4; lattices whose front is inside the frame do not change.
 inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
                             bool nt) {
   SweepPlan P;
@@ -184,8 +186,13 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
   }
   if (P.xb - P.xa < 64 || P.yb - P.ya < 16) return SweepPlan();
   P.nacross = (P.xb - P.xa + T - 1) / T;
-  P.strips = (P.xb - P.xa + w - 1) / w;
+  P.fl = front & 1;
+  P.fr = front >> 1 & 1;
+  P.cut(w);
   P.rows = rows;
+  P.frows = 8;
+  if (P.frows > rows) P.frows = rows;
+  P.fseg = (P.yb - P.ya + P.frows - 1) / P.frows;
   P.nseg = (P.yb - P.ya + rows - 1) / rows;
   P.nt = nt ? 1 : 0;
   P.k = k;
@@ -216,6 +223,24 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   const int64_t rows = (p.ny / 128 + 3) / 4 * 4;
   return sweep_plan(p, k, (int)(rows < 8 ? 8 : (rows > 32 ? 32 : rows)),
                     n > (1 << 24));
+}
+
+// An instance of a batch under a two-step variant: its plan, or tiles alone
+// where no strip fits.  Segments of at most 32 rows: 48 FP32 D2Q5 lattices of
+// 64^2 to 1024^2 take 505 us per four steps with 32 and 64 rows, 560 with 16
+// and 128 (two-step launches of step2_kernel, split by quiet and solving
+// items, took 1040).
+inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v) {
+  SweepPlan P = sweep_plan(p, 4, v.rows < 32 ? v.rows : 32, v.nt != 0);
+  if (P.k > 0) return P;
+  P.k = 4;
+  P.tile = frame_tile(4);
+  P.nleft = (int32_t)((p.nx + P.tile - 1) / P.tile);
+  P.nside = (int32_t)((p.ny + P.tile - 1) / P.tile);
+  P.xa = P.xb = (int32_t)p.nx;
+  P.yb = (int32_t)p.ny;
+  P.nacross = P.strips = P.rows = 1;
+  return P;
 }
 
 // sweep_kernel under a two-step variant, in segments of its rows

@@ -101,9 +101,6 @@ struct StepArgs {
   const void *src;      // current state planes
   void *dst;            // next state planes
   int32_t nx, ny;
-  int32_t x_lim, x_cnt; // kernels built with LIM (the batched two-step
-                        // front pass): columns x < x_lim are computed, and
-                        // those with x < x_cnt counted in the statistics
   int64_t plane;        // nx * ny
   int32_t tiles_x, tiles_y;  // tile grid
   int32_t group;             // tile rows per work item (one block each)
@@ -113,8 +110,6 @@ struct StepArgs {
   int32_t periodic_x, periodic_y;
   int32_t scheme;       // SCHEME_IREBM or SCHEME_EEBM
   int32_t neu;          // bit k: wall k (x-, x+, y-, y+) is a Neumann wall
-  int32_t x_shift;      // two-step kernels: strip s covers the columns from
-                        // s (bx - 4) - x_shift on (a narrow first strip)
   double a;             // 1 - 1/tau
   double inv_tau;       // 1/tau
   double wtau[9];       // w_i / tau

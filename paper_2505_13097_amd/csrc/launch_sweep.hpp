@@ -1,6 +1,7 @@
-// launch_sweep.hpp -- launches of sweep_kernel for one node-update mode,
-// instantiated by the k_sweep_<mode>.hip units and reached through
-// sweep_launch (lbm_stefan_internal.hpp).
+// launch_sweep.hpp -- launches of sweep_kernel and batch_sweep_kernel for one
+// node-update mode, instantiated by the k_sweep_<mode>.hip and
+// k_bsweep_<mode>.hip units and reached through sweep_launch and
+// batch_sweep (lbm_stefan_internal.hpp).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,8 +22,7 @@ hipError_t launch_sweep_t(const StepArgs &A, const SweepPlan &P, int k,
     if (k < 2 || k > P.k) return hipErrorInvalidValue;
     // strips as wide as k steps allow
     SweepPlan R = P;
-    const int w = 64 - 2 * k;
-    R.strips = (P.xb - P.xa + w - 1) / w;
+    R.cut(64 - 2 * k);
     const int64_t ct = (R.tiles() + 7) / 8;
     const int64_t cw = (((R.waves() + 7) / 8) + 3) / 4;
     const unsigned grid = (unsigned)(8 * (ct + cw));
@@ -48,7 +48,40 @@ hipError_t launch_sweep_t(const StepArgs &A, const SweepPlan &P, int k,
   }
 }
 
+// k steps (1 to 4) of a batch (see BatchLaunch)
+template <int Q, typename S, int MODE>
+hipError_t launch_batch_sweep_t(const BatchLaunch &b, int k,
+                                hipStream_t stream) {
+  if constexpr (Q == 3) {
+    return hipErrorInvalidValue;
+  } else {
+    const int64_t ct = (b.ntiles + 7) / 8;
+    const int64_t cw = (((b.nitems - b.ntiles + 7) / 8) + 3) / 4;
+    const unsigned grid = (unsigned)(8 * (ct + cw));
+#define BSWEEP(K)                                                         \
+  batch_sweep_kernel<Q, S, MODE, K><<<grid, 256, 0, stream>>>(            \
+      b.descs, b.plans, b.items, (int32_t)b.ntiles, b.items + b.ntiles,   \
+      (int32_t)(b.nitems - b.ntiles), b.parity)
+    if (k == 4) BSWEEP(4);
+    else if (k == 3) BSWEEP(3);
+    else if (k == 2) BSWEEP(2);
+    else if (k == 1) BSWEEP(1);
+    else return hipErrorInvalidValue;
+#undef BSWEEP
+    return hipGetLastError();
+  }
+}
+
 }  // namespace
+
+template <int MODE>
+hipError_t batch_sweep_mode(int q, int storage, const BatchLaunch &b, int k,
+                            hipStream_t stream) {
+  return dispatch_qs(q, storage, [&](auto qt, auto tt) {
+    QS_TYPES(qt, tt);
+    return launch_batch_sweep_t<Q, S, MODE>(b, k, stream);
+  });
+}
 
 template <int MODE>
 hipError_t sweep_launch_mode(int q, int storage, const StepArgs &A,
@@ -66,3 +99,7 @@ hipError_t sweep_launch_mode(int q, int storage, const StepArgs &A,
   template hipError_t irebm::sweep_launch_mode<M>(                         \
       int, int, const irebm::StepArgs &, const irebm::SweepPlan &, int,    \
       char *, int64_t, hipStream_t)
+
+#define IREBM_INSTANTIATE_BATCH_SWEEP(M)                                   \
+  template hipError_t irebm::batch_sweep_mode<M>(                          \
+      int, int, const irebm::BatchLaunch &, int, hipStream_t)

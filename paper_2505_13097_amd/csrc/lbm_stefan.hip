@@ -199,7 +199,6 @@ void irebm::fill_args(const lbm_stefan_params &p, double *const prof[4],
   std::memset(A, 0, sizeof(*A));
   A->nx = (int32_t)p.nx;
   A->ny = (int32_t)p.ny;
-  A->x_lim = A->x_cnt = (int32_t)p.nx;
   A->plane = p.nx * p.ny;
   A->periodic_x = p.bc[0] == LBM_BC_PERIODIC;
   A->periodic_y = p.dim == 2 && p.bc[2] == LBM_BC_PERIODIC;

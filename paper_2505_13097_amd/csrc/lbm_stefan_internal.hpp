@@ -140,13 +140,10 @@ struct BatchLaunch {
   int cus, blocks_per_cu; // persistent grid of cus * blocks_per_cu blocks
                           // when blocks_per_cu > 0, else one per item
   int parity;             // 0: src -> dst of each descriptor, 1: dst -> src
-  bool two;               // two steps under a two-step variant (else one)
-  int split = 0;          // two-step kernels: 0 every item, 1 the quiet
-                          // pass over items flagged 0, 2 the full pass over
-                          // items flagged 2 (batch_step2_kernel)
-  int *flags = nullptr;   // device: one flag per work item (split > 0)
-  bool front = false;     // the front strips' kernel (items: instance,
-                          // segment of front rows)
+  // sweeping schedules: the instances' plans; items lists the frame's tiles
+  // first (ntiles of them), then the waves
+  const SweepPlan *plans = nullptr;
+  int64_t ntiles = 0;
 };
 
 template <int MODE>
@@ -159,6 +156,10 @@ hipError_t step2_launch_mode(int q, int storage, const StepArgs &A,
 template <int MODE>
 hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
                              const Variant &v, hipStream_t stream);
+// k steps (1 to 4) of a batch by batch_sweep_kernel
+template <int MODE>
+hipError_t batch_sweep_mode(int q, int storage, const BatchLaunch &b, int k,
+                            hipStream_t stream);
 // k steps (2 to 4, at most P.k) of a large 2D lattice (sweep_kernel)
 template <int MODE>
 hipError_t sweep_launch_mode(int q, int storage, const StepArgs &A,
@@ -190,6 +191,8 @@ hipError_t resident_launch_mode(int storage, const StepArgs &A,
       int, int, const StepArgs &, const Variant &, bool, hipStream_t);     \
   extern template hipError_t resident_launch_mode<M>(                      \
       int, const StepArgs &, int32_t, hipStream_t);                       \
+  extern template hipError_t batch_sweep_mode<M>(                          \
+      int, int, const BatchLaunch &, int, hipStream_t);                    \
   extern template hipError_t batch_launch_mode<M>(                         \
       int, int, const BatchLaunch &, const Variant &, hipStream_t)
 IREBM_DECLARE_MODE(kSafeguarded);
@@ -361,6 +364,15 @@ inline hipError_t batch_launch(int mode, int q, int storage,
   if (mode == kEebm) return batch_launch_mode<kEebm>(q, storage, b, v, stream);
   if (mode == kPlain) return batch_launch_mode<kPlain>(q, storage, b, v, stream);
   return batch_launch_mode<kSafeguarded>(q, storage, b, v, stream);
+}
+
+inline hipError_t batch_sweep(int mode, int q, int storage,
+                              const BatchLaunch &b, int k,
+                              hipStream_t stream) {
+  if (mode == kEebm) return batch_sweep_mode<kEebm>(q, storage, b, k, stream);
+  if (mode == kPlain)
+    return batch_sweep_mode<kPlain>(q, storage, b, k, stream);
+  return batch_sweep_mode<kSafeguarded>(q, storage, b, k, stream);
 }
 
 }  // namespace irebm

@@ -271,7 +271,10 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
 // Work of one lattice at up to k steps per launch: the frame's tiles, a
 // block of 256 threads each, then the strips of [xa, xb) x [ya, yb) in
 // segments of `rows` rows, a wave each, strip-fastest, so that neighbouring
-// strips share halo lines in an L2.  Each XCD takes one contiguous part of
+// strips share halo lines in an L2.  The strip next to a side band where a
+// front starts (nfl, nfr: the first, the last) is cut into shorter segments
+// and goes first: a front that has left the band puts a solve into every row
+// of it, one after the other.  Each XCD takes one contiguous part of
 // either list, the frame's (which hold the solves and take longest) first.
 struct SweepPlan {
   int32_t k = 0;                       // 0: the lattice takes another kernel
@@ -283,12 +286,22 @@ struct SweepPlan {
   int32_t nbottom = 0, ntop = 0;       // tile rows of the other bands
   int32_t nacross = 0;                 // their tile columns, over [xa, xb)
   int32_t strips = 0, rows = 0, nseg = 0;
+  int32_t fl = 0, fr = 0;              // a front starts at x = 0, at nx - 1
+  int32_t nfl = 0, nfr = 0, frows = 1, fseg = 0;
   int32_t nt = 0;
+  // strips of w columns
+  void cut(int w) {
+    strips = (xb - xa + w - 1) / w;
+    nfl = fl && strips > 0 ? 1 : 0;
+    nfr = fr && strips > nfl ? 1 : 0;
+  }
   __host__ __device__ int64_t tiles() const {
     return (int64_t)(nleft + nright) * nside +
            (int64_t)(nbottom + ntop) * nacross;
   }
-  __host__ __device__ int64_t waves() const { return (int64_t)strips * nseg; }
+  __host__ __device__ int64_t waves() const {
+    return (int64_t)(nfl + nfr) * fseg + (int64_t)(strips - nfl - nfr) * nseg;
+  }
   __host__ __device__ int64_t slots() const { return tiles() + waves(); }
 };
 
@@ -312,6 +325,27 @@ __device__ __forceinline__ void frame_tile_of(const SweepPlan &P, int nx,
   }
 }
 
+// the wave k of the strips of w columns: its own nodes
+__device__ __forceinline__ void sweep_wave_of(const SweepPlan &P, int k, int w,
+                                              int &x0, int &x1, int &y0,
+                                              int &y1) {
+  const int nf = P.nfl + P.nfr, m = P.strips - nf;
+  int strip, rows;
+  if (k < nf * P.fseg) {
+    strip = k % nf < P.nfl ? 0 : P.strips - 1;
+    rows = P.frows;
+    y0 = P.ya + k / nf * rows;
+  } else {
+    k -= nf * P.fseg;
+    strip = P.nfl + k % m;
+    rows = P.rows;
+    y0 = P.ya + k / m * rows;
+  }
+  x0 = P.xa + strip * w;
+  x1 = min(x0 + w, P.xb);
+  y1 = min(y0 + rows, P.yb);
+}
+
 namespace {
 
 // waves per SIMD asked for: what the registers allow without spilling
@@ -332,9 +366,10 @@ void sweep_kernel(StepArgs A, SweepPlan P, char *mid, int64_t mid_stride) {
     if (t >= nt) return;
     int x0, x1, y0, y1;
     frame_tile_of(P, A.nx, A.ny, t, x0, x1, y0, y1);
-    tile_body<Q, S, MODE>(A, K, x0, x1, y0, y1, kFrameSide,
-                          kFrameSide * kFrameSide, lds,
-                          MID ? mid : nullptr, mid_stride,
+    tile_body<Q, S, MODE>(A, to_global((const S *)A.src),
+                          to_global((S *)A.dst), K, x0, x1, y0, y1, kFrameSide,
+                          kFrameSide * kFrameSide,
+                          t < (P.nleft + P.nright) * P.nside, lds, MID ? mid : nullptr, mid_stride,
                           A.slots + t);
     return;
   }
@@ -342,13 +377,59 @@ void sweep_kernel(StepArgs A, SweepPlan P, char *mid, int64_t mid_stride) {
                 __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int k = xcd * cw + i;
   if (i >= cw || k >= nw) return;
-  const int strip = k % P.strips, seg = k / P.strips;
-  const int x0 = P.xa + strip * (64 - 2 * K);
-  const int y0 = P.ya + seg * P.rows;
+  int x0, x1, y0, y1;
+  sweep_wave_of(P, k, 64 - 2 * K, x0, x1, y0, y1);
   sweep_body<Q, S, base_mode(MODE), K, MID>(
-      A, to_global((const S *)A.src), to_global((S *)A.dst), x0,
-      min(x0 + 64 - 2 * K, P.xb), y0, min(y0 + P.rows, P.yb), P.nt != 0,
-      mid, mid_stride, A.slots + nt + k);
+      A, to_global((const S *)A.src), to_global((S *)A.dst), x0, x1, y0, y1,
+      P.nt != 0, mid, mid_stride, A.slots + nt + k);
+}
+
+// The same over a batch of lattices (descriptor, plan): tiles and waves are
+// listed in two tables of (instance, item), each cut into one contiguous
+// part per XCD; strips are as wide as K = 4 allows at every K, so that the
+// tables do not depend on it.
+template <int Q, typename S, int MODE, int K>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(sweep_waves(Q, sizeof(S), K))))
+void batch_sweep_kernel(const StepArgs *__restrict__ descs,
+                        const SweepPlan *__restrict__ plans,
+                        const int2 *__restrict__ tiles, int32_t nt,
+                        const int2 *__restrict__ waves, int32_t nw,
+                        int32_t parity) {
+  __shared__ S lds[Q * kFrameSide * kFrameSide];
+  const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
+  const int ct = (nt + 7) >> 3, cw = (((nw + 7) >> 3) + 3) & ~3;
+  if (j < ct) {
+    const int i = xcd * ct + j;
+    if (i >= nt) return;
+    const int2 e = tiles[i];
+    const int inst = __builtin_amdgcn_readfirstlane(e.x);
+    const int t = __builtin_amdgcn_readfirstlane(e.y);
+    const StepArgs &A = descs[inst];
+    int x0, x1, y0, y1;
+    frame_tile_of(plans[inst], A.nx, A.ny, t, x0, x1, y0, y1);
+    tile_body<Q, S, MODE>(A, to_global((const S *)(parity ? A.dst : A.src)),
+                          to_global((S *)(parity ? A.src : A.dst)), K, x0, x1,
+                          y0, y1, kFrameSide, kFrameSide * kFrameSide,
+                          t < (plans[inst].nleft + plans[inst].nright) *
+                                  plans[inst].nside,
+                          lds, nullptr, 0, A.slots + t);
+    return;
+  }
+  const int i = (j - ct) * 4 +
+                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (i >= cw || xcd * cw + i >= nw) return;
+  const int2 e = waves[xcd * cw + i];
+  const int inst = __builtin_amdgcn_readfirstlane(e.x);
+  const int k = __builtin_amdgcn_readfirstlane(e.y);
+  const StepArgs &A = descs[inst];
+  const SweepPlan &P = plans[inst];
+  int x0, x1, y0, y1;
+  sweep_wave_of(P, k, 64 - 2 * P.k, x0, x1, y0, y1);
+  sweep_body<Q, S, MODE, K, false>(
+      A, to_global((const S *)(parity ? A.dst : A.src)),
+      to_global((S *)(parity ? A.src : A.dst)), x0, x1, y0, y1, P.nt != 0,
+      nullptr, 0, A.slots + (int)P.tiles() + k);
 }
 
 }  // namespace

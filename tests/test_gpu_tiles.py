@@ -1,7 +1,7 @@
 """Several steps per launch (the library default of 2D lattices: tiles in LDS
 on small ones, sweeping waves with a frame of tiles on large ones; and the
-two-step variants, which sweep too) against one-step launches: the states bit for bit, the Newton
-counters equal, energies and boundary fluxes to the rounding of their sums
+two-step variants, which sweep too) against one-step launches: the states bit
+for bit, the Newton counters equal, energies and boundary fluxes to the rounding of their sums
 (1e-12 of the sum of the magnitudes, a few thousand FP64 terms)."""
 import numpy as np
 import pytest
@@ -145,3 +145,48 @@ def test_autotune_keeps_the_state_of_a_tiled_lattice():
     after = g.state()
     g.close()
     assert np.array_equal(after, _run(prob, (13,), 0)[0])
+
+
+@pytest.mark.parametrize("scheme", ["irebm", "eebm"])
+def test_batch_sweeps_equal_single_steps(scheme):
+    """The batched form: lattices of tiles alone next to ones with strips,
+    periodic ones narrower than a halo, in launches of every length, eager
+    and in graphs of an odd and an even number of launches."""
+    from paper_2505_13097_amd import StefanBatch
+    rng = np.random.default_rng(5)
+    for q, storage in ((5, "f32"), (9, "f64"), (5, "f64"), (9, "f32")):
+        probs = []
+        for (nx, ny), bc in zip([(3, 3), (5, 40), (88, 88), (87, 120),
+                                 (40, 900), (300, 64), (200, 331)],
+                                [WALLS[3], WALLS[4], WALLS[1], WALLS[0],
+                                 WALLS[2], WALLS[3], WALLS[1]]):
+            x = _prob(nx, ny, q, bc, storage, scheme)
+            if nx > 199:
+                x = x.with_(T0=-0.5 + rng.uniform(-1e-3, 1e-3, (ny, nx)))
+            probs.append(x)
+        names = variant_names(q, storage)
+        for v, graph in ((-1, 0), (names.index("128x2/t2s/r96/nt"), 20),
+                         (names.index("128x4/t2s/r32/nt"), 6)):
+            a = StefanBatch(probs)
+            a.set_schedule(v, 0, graph)
+            ref = StefanBatch(probs)
+            ref.set_schedule(names.index("64x1/npt1"))
+            done = 0
+            for n in (1, 2, 3, 43, 4):
+                a.step(n)
+                ref.step(n)
+                done += n
+                for k in range(len(probs)):
+                    assert np.array_equal(a.temperature(k),
+                                          ref.temperature(k)), \
+                        (q, storage, v, n, k)
+            for k, (sa, sb) in enumerate(zip(a.stats(), ref.stats())):
+                tag = (q, storage, v, k)
+                for f in ("max_newton_it", "nonconverged", "max_residual"):
+                    assert sa[f] == sb[f], (tag, f)
+                bar = 1e-12 * (abs(sb["energy"]) + done * 9 * probs[k].nodes)
+                for f in ("energy", "flux_in", "flux_out"):
+                    assert abs(sa[f] - sb[f]) <= bar, (tag, f)
+            a.close()
+            ref.close()
+        print(f"batch q{q} {storage} {scheme}: equal", flush=True)
