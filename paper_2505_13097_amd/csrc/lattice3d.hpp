@@ -716,11 +716,31 @@ inline const Variant3 *variants3(int *n) {
       {128, 1, 2, 32, 1}, {128, 1, 2, 16, 0}, {64, 1, 2, 16, 1},
       {64, 2, 2, 8, 1},
       {128, 1, 2, 4, 1, 1}, {128, 1, 2, 8, 1, 1}, {64, 4, 1, 8, 1, 1},
-      {64, 2, 2, 8, 1, 1},  {64, 4, 1, 16, 1, 1}};
+      {64, 2, 2, 8, 1, 1},  {64, 4, 1, 16, 1, 1},
+      {64, 1, 1, 1, 0},     {64, 1, 1, 2, 0}};
   *n = (int)(sizeof(v) / sizeof(Variant3));
   return v;
 }
-constexpr int kDefaultVariant3D = 0;
+// The library default.  Up to 400k nodes one wave per block and one slice
+// (index 21): the chip is short of waves, and a wave that sweeps 8 slices
+// takes 8 solves one after the other (us per step, 64x4/npt1/z8/nt -> here:
+// 24^3 D3Q7 FP64 freezing 57.6 -> 9.4, 61^3 45 -> 17, D3Q19 88 -> 31).  While
+// the memory-side cache holds both states, one wave, two slices and plain
+// stores (index 22; 101^3 D3Q7 FP64 freezing 63.7 -> 46.2, melting 54 -> 34,
+// 128^3 FP32 melting 50 -> 43, 161^3 FP32 96 -> 80; 141^3 FP64, 157 MB, 103
+// against 106).  Beyond that, D3Q19 up to 8M nodes one slice per block of
+// four waves (index 3; 101^3 FP64 109 -> 90, 128^3 FP32 120 -> 103, FP64 164
+// -> 145, 161^3 FP32 258 -> 245, 200^3 FP64 587 -> 583; not EEBM in FP32,
+// 128^3 83 against 94), and 8 slices per block on anything larger (256^3
+// D3Q7 FP32 248, with one slice 318: the slices share their neighbours in
+// the caches).
+constexpr int kLargeVariant3D = 0;
+inline int default_3d(int q, size_t s, bool eebm, int64_t nodes) {
+  if (nodes <= 400000) return 21;
+  if (nodes * q * (int64_t)s <= 130000000) return 22;
+  return q == 19 && nodes <= 8000000 && !(eebm && s == 4) ? 3
+                                                          : kLargeVariant3D;
+}
 // split step: the front strip is the first kFront3Columns columns, run
 // with the tiling of variant kFront3Variant (64 x 4, 32 slices per item:
 // fewer, longer front blocks beside the quiet pass; on the 512^3 D3Q7

@@ -592,7 +592,9 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
   // default: the resident kernel for the small 1D lattices it takes
   h->variant = p->variant >= 0
                    ? p->variant
-                   : (p->dim == 3 ? kDefaultVariant3D
+                   : (p->dim == 3 ? default_3d(p->q, p->storage == LBM_STORE_F64 ? 8 : 4,
+                                              p->scheme == LBM_SCHEME_EEBM,
+                                              nodes_of(*p))
                                   : (p->q == 3 ? (resident_ok(*p)
                                                       ? kResidentVariant1D
                                                       : kDefaultVariant1D)

@@ -190,3 +190,21 @@ def test_batch_sweeps_equal_single_steps(scheme):
             a.close()
             ref.close()
         print(f"batch q{q} {storage} {scheme}: equal", flush=True)
+
+
+def test_noalloc_3d_takes_thin_lattices_whose_default_tiling_has_many_blocks():
+    """3 x 1000 x 1000 D3Q7: one wave per row would need more statistics
+    slots than the fixed scratch holds, so larger blocks run; same state as
+    a handle's step, on both sides of the rule's first line too."""
+    from paper_2505_13097_amd import step_noalloc
+    for n in ((3, 1000, 1000), (101, 63, 63), (101, 63, 62)):
+        prob = synth.cavity_3d(n=n[0], ny=n[1], nz=n[2], q=7, storage="f32",
+                               scheme="irebm")
+        g = Stefan(prob)
+        src = torch.from_numpy(g.state()).cuda()
+        dst = torch.empty_like(src)
+        step_noalloc(prob, src, dst)
+        g.step(1)
+        assert np.array_equal(dst.cpu().numpy().reshape(-1),
+                              g.state().reshape(-1)), n
+        g.close()
