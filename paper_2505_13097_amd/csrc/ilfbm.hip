@@ -10,14 +10,15 @@
 // closes the unknown populations (Section 4.2 on the streamed populations,
 // Dirichlet target T_D), and forms H^(k) = M0(f^(k)) + l^(k-1)/Ste and
 // l^(k) = clamp(Ste (H^(k) - T_m), 0, 1).  The source term reaches across
-// nodes, so each iteration is one pass over the lattice: one kernel
-// launch, which also writes the collision of f^(k) (the next state, in
-// case k is the last iteration) and per-block max |l^(k) - l^(k-1)| and
-// boundary fluxes.  A one-block check kernel reduces them in a fixed
-// order and sets a device flag once max |l^(k) - l^(k-1)| <= tol; every
-// later launch of the step sees the flag and returns, so the buffers keep
-// the last iteration's results.  The host reads the flag after every few
-// launches.  Tolerance and cap: the params' newton_tol and newton_max_it.
+// nodes; but Omega0 and l do not change during the inner loop, so a block
+// holds the pulled Omega0 of a tile and its halo in registers and takes
+// kTileIt iterations per launch on it, l - l^(k-1) in LDS
+// (ilfbm_tile_kernel).  Every iteration with a change above tol sets a flag
+// of its own; a launch whose predecessor has an unset one returns.  The host
+// reads the flags after every few launches, and the launch that holds the
+// last iteration is run once more up to it, now writing the next state, the
+// boundary fluxes and the largest change.  Tolerance and cap: the params'
+// newton_tol and newton_max_it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,22 +34,34 @@ using namespace irebm;
 
 namespace {
 
-constexpr int kBlock = 256;      // threads per block of the inner kernel
-constexpr int kBurst = 4;        // launches between two host checks
+constexpr int kTileIt = 8;       // inner iterations per launch, at most
+constexpr int kTileThreads = 1024;
+constexpr int kTileRow = 32;     // 2D tiles: 32 x 32 with the halo
+constexpr int kBurst = 8;        // launches between two host checks
+constexpr int kSets = 2 * kBurst;
 
 // device control block of one step's inner loop
 struct IlfCtrl {
-  int32_t done, kfinal;
+  // of a step's last iteration, summed over its tiles
   double dl, flux_in, flux_out;
+  // launch j, iteration m: open[j % kSets][m] is set when l changed by more
+  // than tol somewhere
+  int32_t open[kSets][kTileIt];
 };
+
+// tiles of the lattice: own nodes per tile along x and y at most
+constexpr int tile_x(int q) {
+  return q == 3 ? kTileThreads - 2 * kTileIt : kTileRow - 2 * kTileIt;
+}
+constexpr int tile_y(int q) {
+  return q == 3 ? 1 : kTileThreads / kTileRow - 2 * kTileIt;
+}
 
 struct IlfArgs {
   StepArgs A;            // lattice; A.src = Omega0, A.dst = next state
   const double *l;       // liquid fraction of the state
   const double *lprev;   // l^(k-1)
   double *lout;          // l^(k)
-  double *pend;          // per block: max |dl|, flux in, flux out
-  IlfCtrl *ctrl;
   double ste;
 };
 
@@ -124,36 +137,184 @@ __device__ __forceinline__ void ilfbm_node(const IlfArgs &G, int64_t k,
   }
 }
 
-template <int Q, typename S>
-__global__ __launch_bounds__(kBlock) void ilfbm_iter_kernel(IlfArgs G) {
-  if (G.ctrl->done) return;          // an earlier iteration converged
-  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// kk (at most kTileIt) inner iterations on the tiles of the lattice, G.lprev
+// -> G.lout.  The region a block holds shrinks by one node a side and
+// iteration, as in tile_body; nodes of a halo are computed by their
+// neighbours as well, by the same code from the same values.  open: this
+// launch's flags; prev: those of the launch before (null for the first);
+// clear: a set that a later launch will use.  FINAL: the last iteration also
+// writes the next state to G.A.dst and per tile (pend) the largest change
+// and the boundary fluxes.
+//
+// A launch per iteration and one to check it took 14 us per iteration of a
+// 201^2 D2Q9 FP64 lattice, latency of launches and global memory all of it.
+// 8 iterations of a block take 20 us, most of it the closures of the wall
+// nodes (29 us while those reloaded their Omega0 in every iteration), and a
+// step of 114 iterations 450 us with the host reads, before 1600.
+template <int Q, typename S, bool FINAL>
+__global__ __launch_bounds__(kTileThreads) void ilfbm_tile_kernel(
+    IlfArgs G, int32_t ntx, int32_t nty, int32_t kk, const int32_t *prev,
+    int32_t *open, int32_t *clear, double tol, double *pend) {
+  constexpr int RX = Q == 3 ? kTileThreads : kTileRow;
+  __shared__ double lds[2][kTileThreads];
+  __shared__ int32_t s_open[kTileIt];
+  const int t = (int)threadIdx.x;
+  if (!FINAL && prev) {
+    int all = 1;
+    for (int m = 0; m < kTileIt; ++m) all &= prev[m];
+    if (!all) return;                // an earlier iteration converged
+  }
+  const int tiles = ntx * nty, per_xcd = (tiles + 7) >> 3;
+  const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (!FINAL && blockIdx.x == 0 && t < kTileIt) clear[t] = 0;
+  if (tile >= tiles) return;
+  const StepArgs &A = G.A;
+  const int nx = A.nx, ny = A.ny;
+  const int64_t PL = A.plane;
+  const gptr<const S> src = to_global((const S *)A.src);
+  const int tx = tile % ntx, ty = tile / ntx;
+  const int x0 = (int)((int64_t)tx * nx / ntx);
+  const int x1 = (int)((int64_t)(tx + 1) * nx / ntx);
+  const int y0 = (int)((int64_t)ty * ny / nty);
+  const int y1 = (int)((int64_t)(ty + 1) * ny / nty);
+  const int hy = Q == 3 ? 0 : kk;    // halo rows (D1Q3: one row, no y)
+  const int lx = t % RX, ly = t / RX;
+  const int x = x0 - kk + lx, y = y0 - hy + ly;
+  const int w = x1 - x0 + 2 * kk, h = y1 - y0 + 2 * hy;
+  int gx = x, gy = y;
+  if (A.periodic_x) gx = ((x % nx) + nx) % nx;
+  if (A.periodic_y) gy = ((y % ny) + ny) % ny;
+  const bool node = lx < w && ly < h && gx >= 0 && gx < nx && gy >= 0 &&
+                    gy < ny;
+  const bool own = node && x >= x0 && x < x1 && y >= y0 && y < y1;
+  const int64_t at = node ? (int64_t)gy * nx + gx : 0;
+  // static over the inner loop: the pulled Omega0, l, masks, and on an edge
+  // node its own Omega0 and what its mirror node pulls
+  const double lo = G.l[at];
+  double lp = G.lprev[at];
+  lds[0][t] = lo - lp;
+  if (t < kTileIt) s_open[t] = 0;
+  uint32_t known = 0, out = 0;
+  S p[Q], own_om[Q], pm[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) p[i] = own_om[i] = pm[i] = (S)0;
+  if (node) {
+    node_masks<Q>(A, gx, gy, known, out);
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      if (known >> i & 1u) p[i] = src[i * PL + source_node<Q>(A, gx, gy, i)];
+  }
+  const bool edge = node && (known != (1u << Q) - 1u || out);
+  bool mirrored = false;
+  int mt = 0;
+  if (edge) {
+    int mx, my;
+    mirrored = known != (1u << Q) - 1u && neumann_mirror<Q>(A, gx, gy, mx, my);
+    if (mirrored) mt = t + (mx - gx) + (my - gy) * RX;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      own_om[i] = src[i * PL + at];
+      if (mirrored) pm[i] = src[i * PL + source_node<Q>(A, mx, my, i)];
+    }
+  }
   double dl = 0.0, fin = 0.0, fout = 0.0;
-  if (k < G.A.plane) ilfbm_node<Q, S>(G, k, dl, fin, fout);
-  __shared__ double s_dl[kBlock / 64];
-  dl = wave_max(dl);
-  if ((threadIdx.x & 63) == 0) s_dl[threadIdx.x >> 6] = dl;
-  const double bfin = block_sum_256(fin);
-  const double bfout = block_sum_256(fout);
-  if (threadIdx.x == 0) {
-    double m = s_dl[0];
-    for (int w = 1; w < kBlock / 64; ++w) m = fmax(m, s_dl[w]);
-    G.pend[3 * blockIdx.x] = m;
-    G.pend[3 * blockIdx.x + 1] = bfin;
-    G.pend[3 * blockIdx.x + 2] = bfout;
+  for (int m = 1; m <= kk; ++m) {
+    __syncthreads();
+    const double *D = lds[(m - 1) & 1];
+    const bool act = node && lx >= m && lx < w - m &&
+                     (Q == 3 || (ly >= m && ly < h - m));
+    bool big = false;
+    if (act) {
+      double q[Q];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const double o = (double)p[i] + wt<Q>(i) * A.inv_ste *
+                                            D[t - cx<Q>(i) - cy<Q>(i) * RX];
+        q[i] = (known >> i & 1u) ? o : 0.0;
+      }
+      if (edge) {
+        double om[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j)
+          om[j] = (double)own_om[j] + wt<Q>(j) * A.inv_ste * D[t];
+        if (known != (1u << Q) - 1u) {
+          double mirror = 0.0;
+          if (mirrored) {
+            // M0 of the populations streamed into the mirror node; every
+            // source is a lattice node (no bounce-back beside Neumann walls)
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+              mirror += (double)pm[i] + wt<Q>(i) * A.inv_ste *
+                                            D[mt - cx<Q>(i) - cy<Q>(i) * RX];
+          }
+          const double f = close_node<Q, SCHEME_ILFBM, true>(
+              A, gx, gy, 0.0, om, q, known, mirror);
+          if (FINAL && own && m == kk) fin += f;
+        }
+        if (FINAL && own && m == kk) {
+#pragma unroll
+          for (int i = 1; i < Q; ++i)
+            if (out >> i & 1u) fout += om[i];
+        }
+      }
+      double m0 = 0.0;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) m0 += q[i];
+      const double H = m0 + lp * A.inv_ste;
+      double ln = G.ste * (H - A.tm);
+      ln = ln < 0.0 ? 0.0 : (ln > 1.0 ? 1.0 : ln);
+      const double ch = fabs(ln - lp);
+      big = own && ch > tol;
+      lp = ln;
+      lds[m & 1][t] = lo - ln;
+      if (m == kk && own) {
+        G.lout[at] = ln;
+        if (FINAL) {
+          dl = fmax(dl, ch);
+          // the collision of f^(k): the next state
+          const gptr<S> dst = to_global((S *)A.dst);
+#pragma unroll
+          for (int i = 0; i < Q; ++i)
+            dst[i * PL + at] = (S)(A.a * q[i] + A.wtau[wclass<Q>(i)] * m0);
+        }
+      }
+    }
+    if (!FINAL && __any(big) && (t & 63) == 0) s_open[m - 1] = 1;
+  }
+  __syncthreads();
+  if constexpr (!FINAL) {
+    if (t < kk && s_open[t]) open[t] = 1;
+  } else {
+    // (lds is free: the barrier above)
+    double *sh = &lds[0][0];
+    dl = wave_max(dl);
+    fin = wave_sum(fin);
+    fout = wave_sum(fout);
+    if ((t & 63) == 0) {
+      sh[3 * (t >> 6)] = dl;
+      sh[3 * (t >> 6) + 1] = fin;
+      sh[3 * (t >> 6) + 2] = fout;
+    }
+    __syncthreads();
+    if (t == 0) {
+      for (int v = 1; v < kTileThreads / 64; ++v) {
+        dl = fmax(dl, sh[3 * v]);
+        fin += sh[3 * v + 1];
+        fout += sh[3 * v + 2];
+      }
+      pend[3 * tile] = dl;
+      pend[3 * tile + 1] = fin;
+      pend[3 * tile + 2] = fout;
+    }
   }
 }
 
-// iteration k's convergence test: max and sums over the blocks in a fixed
-// order; sets done once max |dl| <= tol
-__global__ __launch_bounds__(256) void ilfbm_check_kernel(const double *pend,
-                                                          int64_t nblocks,
-                                                          IlfCtrl *ctrl,
-                                                          int32_t k,
-                                                          double tol) {
-  if (ctrl->done) return;
+// largest change and fluxes of a step, over its tiles in a fixed order
+__global__ __launch_bounds__(256) void ilfbm_sum_kernel(const double *pend,
+                                                        int64_t ntiles,
+                                                        IlfCtrl *ctrl) {
   double m = 0.0, fin = 0.0, fout = 0.0;
-  for (int64_t b = threadIdx.x; b < nblocks; b += 256) {
+  for (int64_t b = threadIdx.x; b < ntiles; b += 256) {
     m = fmax(m, pend[3 * b]);
     fin += pend[3 * b + 1];
     fout += pend[3 * b + 2];
@@ -164,28 +325,27 @@ __global__ __launch_bounds__(256) void ilfbm_check_kernel(const double *pend,
   const double sfin = block_sum_256(fin);
   const double sfout = block_sum_256(fout);
   if (threadIdx.x == 0) {
-    m = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
-    ctrl->dl = m;
+    ctrl->dl = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
     ctrl->flux_in = sfin;
     ctrl->flux_out = sfout;
-    ctrl->kfinal = k;
-    if (m <= tol) ctrl->done = 1;
   }
 }
 
-// Small lattices (at most kResidentNodes nodes): one workgroup runs
+// Small D1Q3 lattices (at most kResidentNodes nodes): one workgroup runs
 // `nsteps` whole steps in one launch, block barriers in place of launches
-// and host reads.  Node updates and convergence decisions are those of
+// and host reads.  (256 nodes, 48 iterations a step: 110 us per step either
+// way, 2000 nodes 280 here against 112 in tiles; a 2D iteration takes 14 us
+// here at any size, 24^2 D2Q9 1736 us per step against 486.)  Node updates and convergence decisions are those of
 // the multi-launch path (same ilfbm_node, exact max), so the states are
 // the same; only the flux sums are reduced in another order.  L[0] is the
 // state's l plane, L[1] and L[2] the inner-loop planes; planes and buffers
 // rotate in registers, and the final assignment and statistics are
 // written to `res` for the host.
 constexpr int kResident = 1024;         // threads of the resident block
-constexpr int64_t kResidentNodes = 16384;
+constexpr int64_t kResidentNodes = 512;
 
 struct IlfResident {
-  IlfArgs G;            // lattice, ste; l/lprev/lout/pend/ctrl unused
+  IlfArgs G;            // lattice, ste; l/lprev/lout unused
   void *buf[2];
   double *L[3];
   int32_t cur, nsteps, cap;
@@ -286,15 +446,12 @@ __global__ __launch_bounds__(kResident) void ilfbm_resident_kernel(
 }
 
 __global__ void ilfbm_reset_kernel(IlfCtrl *ctrl) {
-  ctrl->done = 0;
-  ctrl->kfinal = 0;
-  ctrl->dl = 0.0;
-  ctrl->flux_in = 0.0;
-  ctrl->flux_out = 0.0;
+  ctrl->open[threadIdx.x / kTileIt][threadIdx.x % kTileIt] = 0;
 }
 
-int64_t iter_blocks(const lbm_stefan_params *p) {
-  return (p->nx * p->ny + kBlock - 1) / kBlock;
+int64_t tiles_of(int64_t n, int side) { return (n + side - 1) / side; }
+int64_t iter_tiles(const lbm_stefan_params *p) {
+  return tiles_of(p->nx, tile_x(p->q)) * tiles_of(p->ny, tile_y(p->q));
 }
 
 }  // namespace
@@ -302,8 +459,8 @@ int64_t iter_blocks(const lbm_stefan_params *p) {
 size_t irebm::ilfbm_bytes(const lbm_stefan_params *p) {
   if (p->scheme != LBM_SCHEME_ILFBM) return 0;
   const int64_t n = p->nx * p->ny;
-  return 3 * align256((size_t)n * 8) + align256((size_t)iter_blocks(p) * 24) +
-         256;
+  return 3 * align256((size_t)n * 8) + align256((size_t)iter_tiles(p) * 24) +
+         align256(sizeof(IlfCtrl));
 }
 
 void irebm::ilfbm_attach(lbm_stefan_t *h, char *base) {
@@ -313,7 +470,7 @@ void irebm::ilfbm_attach(lbm_stefan_t *h, char *base) {
   h->lscr[0] = (double *)(base + plane);
   h->lscr[1] = (double *)(base + 2 * plane);
   h->pend = (double *)(base + 3 * plane);
-  h->ctrl = base + 3 * plane + align256((size_t)iter_blocks(&h->p) * 24);
+  h->ctrl = base + 3 * plane + align256((size_t)iter_tiles(&h->p) * 24);
   ilfbm_reset_stats(h);
 }
 
@@ -334,24 +491,22 @@ hipError_t ilfbm_advance_resident(lbm_stefan_t *h, int64_t nsteps) {
   IlfResident R;
   fill_step_args(h, &R.G.A);
   R.G.ste = p.ste;
-  R.G.pend = nullptr;
-  R.G.ctrl = nullptr;
   R.buf[0] = h->buf[0];
   R.buf[1] = h->buf[1];
   R.cap = p.newton_max_it;
   R.tol = p.newton_tol;
-  R.res = h->pend;                    // >= 24 bytes: reuse the pending area
+  R.res = h->pend;                    // >= 256 bytes: reuse the pending area
   for (int64_t left = nsteps; left > 0;) {
     const int32_t chunk = (int32_t)std::min(left, kChunk);
     double *Lp[3] = {h->lf, h->lscr[0], h->lscr[1]};
     for (int j = 0; j < 3; ++j) R.L[j] = Lp[j];
     R.cur = h->cur;
     R.nsteps = chunk;
-    hipError_t e = dispatch_qs(p.q, p.storage, [&](auto qt, auto tt) {
-      QS_TYPES(qt, tt);
-      ilfbm_resident_kernel<Q, S><<<1, kResident, 0, h->stream>>>(R);
-      return hipGetLastError();
-    });
+    if (p.storage == LBM_STORE_F32)
+      ilfbm_resident_kernel<3, float><<<1, kResident, 0, h->stream>>>(R);
+    else
+      ilfbm_resident_kernel<3, double><<<1, kResident, 0, h->stream>>>(R);
+    hipError_t e = hipGetLastError();
     double res[9];
     if (e == hipSuccess)
       e = hipMemcpyAsync(res, h->pend, sizeof(res), hipMemcpyDeviceToHost,
@@ -377,59 +532,90 @@ hipError_t ilfbm_advance_resident(lbm_stefan_t *h, int64_t nsteps) {
 
 hipError_t irebm::ilfbm_advance(lbm_stefan_t *h, int64_t nsteps) {
   const lbm_stefan_params &p = h->p;
-  if (p.nx * p.ny <= kResidentNodes) return ilfbm_advance_resident(h, nsteps);
-  const int64_t nb = iter_blocks(&p);
+  if (p.q == 3 && p.nx <= kResidentNodes)
+    return ilfbm_advance_resident(h, nsteps);
+  const int32_t ntx = (int32_t)tiles_of(p.nx, tile_x(p.q));
+  const int32_t nty = (int32_t)tiles_of(p.ny, tile_y(p.q));
+  const int64_t tiles = (int64_t)ntx * nty;
+  const unsigned grid = (unsigned)(8 * ((tiles + 7) / 8));
   IlfCtrl *ctrl = (IlfCtrl *)h->ctrl;
   IlfArgs G;
   fill_step_args(h, &G.A);
-  G.pend = h->pend;
-  G.ctrl = ctrl;
   G.ste = p.ste;
   const int cap = p.newton_max_it;
+  IlfCtrl hc{};
+  bool pending = false, capped = false;   // a step's sums are still on their way
+  auto take = [&] {
+    if (!pending) return;
+    if (capped) h->ilf_max_res = std::max(h->ilf_max_res, hc.dl);
+    h->ilf_fin += hc.flux_in;
+    h->ilf_fout += hc.flux_out;
+    pending = false;
+  };
+  auto read = [&] {
+    hipError_t e = hipMemcpyAsync(&hc, ctrl, sizeof(hc), hipMemcpyDeviceToHost,
+                                  h->stream);
+    return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
+  };
   for (int64_t s = 0; s < nsteps; ++s) {
     G.A.src = h->buf[h->cur];
     G.A.dst = h->buf[h->cur ^ 1];
     G.l = h->lf;
-    ilfbm_reset_kernel<<<1, 1, 0, h->stream>>>(ctrl);
+    // launch j: iterations j kTileIt + 1 to (j + 1) kTileIt, at most cap
+    auto launch = [&](int64_t j, int kk, bool final) {
+      G.lprev = j == 0 ? h->lf : h->lscr[(j - 1) & 1];
+      G.lout = h->lscr[j & 1];
+      int32_t *open = ctrl->open[j % kSets];
+      const int32_t *prev = j == 0 ? nullptr : ctrl->open[(j - 1) % kSets];
+      int32_t *clear = ctrl->open[(j + kBurst) % kSets];
+      return dispatch_qs(p.q, p.storage, [&](auto qt, auto tt) {
+        QS_TYPES(qt, tt);
+        if (final)
+          ilfbm_tile_kernel<Q, S, true><<<grid, kTileThreads, 0, h->stream>>>(
+              G, ntx, nty, kk, prev, open, clear, p.newton_tol, h->pend);
+        else
+          ilfbm_tile_kernel<Q, S, false><<<grid, kTileThreads, 0, h->stream>>>(
+              G, ntx, nty, kk, prev, open, clear, p.newton_tol, h->pend);
+        return hipGetLastError();
+      });
+    };
+    ilfbm_reset_kernel<<<1, kSets * kTileIt, 0, h->stream>>>(ctrl);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    IlfCtrl hc{};
-    int k = 0;
-    while (k < cap) {
-      const int burst = std::min(kBurst, cap - k);
-      for (int b = 0; b < burst; ++b) {
-        ++k;
-        G.lprev = k == 1 ? h->lf : h->lscr[(k - 1) & 1];
-        G.lout = h->lscr[k & 1];
-        e = dispatch_qs(p.q, p.storage, [&](auto qt, auto tt) {
-          QS_TYPES(qt, tt);
-          ilfbm_iter_kernel<Q, S><<<(unsigned)nb, kBlock, 0, h->stream>>>(G);
-          return hipGetLastError();
-        });
-        if (e != hipSuccess) return e;
-        ilfbm_check_kernel<<<1, 256, 0, h->stream>>>(h->pend, nb, ctrl, k,
-                                                     p.newton_tol);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    int64_t kf = 0;                  // the last iteration, once known
+    bool done = false;
+    for (int64_t j = 0; e == hipSuccess && !done && kf < cap;) {
+      const int64_t j0 = j;
+      for (; j < j0 + kBurst && j * kTileIt < cap && e == hipSuccess; ++j)
+        e = launch(j, (int)std::min<int64_t>(kTileIt, cap - j * kTileIt),
+                   false);
+      if (e == hipSuccess) e = read();
+      if (e != hipSuccess) break;
+      take();
+      for (int64_t k = j0 * kTileIt; k < cap && k < j * kTileIt && !done; ++k) {
+        kf = k + 1;
+        done = !hc.open[k / kTileIt % kSets][k % kTileIt];
       }
-      e = hipMemcpyAsync(&hc, ctrl, sizeof(hc), hipMemcpyDeviceToHost,
-                         h->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-      if (e != hipSuccess) return e;
-      if (hc.done) break;
     }
-    // the last iteration run: kfinal (converged) or the cap
-    const int kf = hc.done ? hc.kfinal : k;
-    std::swap(h->lf, h->lscr[kf & 1]);
+    if (e != hipSuccess) return e;
+    // the launch that holds it again, up to it
+    const int64_t jf = (kf - 1) / kTileIt;
+    e = launch(jf, (int)(kf - jf * kTileIt), true);
+    if (e != hipSuccess) return e;
+    ilfbm_sum_kernel<<<1, 256, 0, h->stream>>>(h->pend, tiles, ctrl);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    std::swap(h->lf, h->lscr[jf & 1]);
     h->cur ^= 1;
     h->steps++;
-    h->ilf_max_it = std::max(h->ilf_max_it, kf);
-    if (!hc.done) {
-      h->ilf_nonconv++;
-      h->ilf_max_res = std::max(h->ilf_max_res, hc.dl);
-    }
-    h->ilf_fin += hc.flux_in;
-    h->ilf_fout += hc.flux_out;
+    h->ilf_max_it = std::max(h->ilf_max_it, (int32_t)kf);
+    if (!done) h->ilf_nonconv++;
+    pending = true;
+    capped = !done;
+  }
+  if (pending) {
+    hipError_t e = read();
+    if (e != hipSuccess) return e;
+    take();
   }
   return hipSuccess;
 }

@@ -208,3 +208,42 @@ def test_noalloc_3d_takes_thin_lattices_whose_default_tiling_has_many_blocks():
         assert np.array_equal(dst.cpu().numpy().reshape(-1),
                               g.state().reshape(-1)), n
         g.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_ilfbm_tiles_repeat_a_periodic_lattice(storage):
+    """ILFBM on lattices repeated along a periodic axis: other tiles (and for
+    D1Q3 another kernel), the same arithmetic at every node, so the states and
+    liquid fractions repeat bit for bit, converged and capped alike."""
+    rng = np.random.default_rng(11)
+    cases = [(3, (500, 1), (P, P, P, P), 300)]
+    for q, max_it in ((5, 13), (9, 300), (9, 8)):
+        for nx, ny in ((3, 3), (16, 8), (17, 9), (33, 40), (100, 17)):
+            for x in ((D, D), (D, N), (B, D), (P, P)):
+                cases.append((q, (nx, ny), x + (P, P), max_it))
+    for q, (nx, ny), bc, max_it in cases:
+        prob = synth.Problem(
+            dim=1 if q == 3 else 2, q=q, nx=nx, ny=ny, tau=0.7, ste=0.3,
+            delta=0.05, bc=bc, wall_T=(0.6, -0.4, 0.0, 0.0), tol=1e-12,
+            max_it=max_it, storage=storage, scheme="ilfbm",
+            T0=rng.uniform(-0.3, 0.3, (ny, nx)))
+        rep = (1, 2) if q == 3 else (2, 1)
+        two = prob.with_(nx=nx * rep[1], ny=ny * rep[0], dx=prob.dx,
+                         T0=np.tile(prob.T0, rep))
+        got = []
+        for x in (prob, two):
+            g = Stefan(x)
+            g.step(2)
+            st = g.step(1, stats=True)
+            got.append((g.state().reshape(q, x.ny, x.nx),
+                        g.liquid().reshape(x.ny, x.nx), st))
+            g.close()
+        (a, la, sa), (b, lb, sb) = got
+        tag = (q, nx, ny, bc, max_it)
+        assert np.array_equal(np.tile(a, (1,) + rep), b), tag
+        assert np.array_equal(np.tile(la, rep), lb), tag
+        for k in ("max_newton_it", "nonconverged", "max_residual"):
+            assert sa[k] == sb[k], (tag, k, sa[k], sb[k])
+        for k in ("flux_in", "flux_out"):
+            assert abs(2 * sa[k] - sb[k]) <= 1e-12 * (1 + 9 * 3 * 2 * nx * ny), \
+                (tag, k)
