@@ -135,12 +135,12 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
     for (int k = 0; k < count; ++k) t += batch_items(v[i], ps[k]);
     L.max_items = std::max(L.max_items, t);
   }
+  L.max_parts = std::max<int64_t>(1, stats_partials(L.max_items));
   L.state_bytes = 0;
   L.off.resize(count);
   L.prof_off.resize(count);
   size_t prof_total = 0;
   int64_t max_ny = 16;
-  L.max_parts = 1;
   for (int k = 0; k < count; ++k) {
     const int64_t n = ps[k].nx * ps[k].ny;
     L.off[k] = L.state_bytes;
@@ -481,9 +481,9 @@ int lbm_stefan_batch_stats(lbm_stefan_batch_t *b, lbm_stefan_stats *out) {
   std::vector<double> hs((size_t)b->count * 16);
   for (int k = 0; k < b->count; ++k) {
     const lbm_stefan_params &p = b->ps[k];
-    stats_kernel<<<1, 256, 0, b->stream>>>(b->slots + b->first_item[k],
-                                           b->nitems_inst[k], b->small + 16 * k);
-    BCHK(b, hipGetLastError());
+    BCHK(b, stats_async(b->slots + b->first_item[k], b->nitems_inst[k],
+                        b->partials, stats_partials(b->nitems_inst[k]),
+                        b->small + 16 * k, b->stream));
     BCHK(b, energy_async(p, b->state[b->cur] + b->off[k], b->partials,
                          b->small + 16 * k + 8, b->stream));
   }

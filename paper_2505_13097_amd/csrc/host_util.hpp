@@ -261,6 +261,11 @@ inline int one_step_default(size_t s, int64_t nodes) {
   return nodes <= (s == 8 ? 1200000 : 400000) ? 20 : kDefaultVariant2D;
 }
 
+// doubles of scratch that stats_async needs for n slots
+inline int64_t stats_partials(int64_t n) {
+  return 5 * ((n + kStatsChunk - 1) / kStatsChunk);
+}
+
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 inline unsigned blocks_for(int64_t n, int t) {

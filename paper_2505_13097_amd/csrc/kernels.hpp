@@ -765,12 +765,41 @@ __global__ __launch_bounds__(256) void sum_kernel(const double *partial,
   if (threadIdx.x == 0) *out = s;
 }
 
-// out: max_it, nonconv, max_res, flux_in, flux_out (as doubles)
+// max_it, nonconv, max_res, flux_in, flux_out (as doubles) over the block
+__device__ __forceinline__ void stats_out(double it, double nc, double res,
+                                          double fin, double fout,
+                                          double *out) {
+  __shared__ double s_m[8];
+  it = wave_max(it);
+  res = wave_max(res);
+  if ((threadIdx.x & 63) == 0) {
+    s_m[threadIdx.x >> 6] = it;
+    s_m[4 + (threadIdx.x >> 6)] = res;
+  }
+  const double snc = block_sum_256(nc);
+  const double sfin = block_sum_256(fin);
+  const double sfout = block_sum_256(fout);
+  if (threadIdx.x == 0) {
+    out[0] = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
+    out[1] = snc;
+    out[2] = fmax(fmax(s_m[4], s_m[5]), fmax(s_m[6], s_m[7]));
+    out[3] = sfin;
+    out[4] = sfout;
+  }
+}
+
+// Slots [chunk blockIdx.x, chunk (blockIdx.x + 1)): one block over all of
+// them is a chain of loads (12k slots 18 us, 500k 600 us), so lattices of
+// many slots are summed in chunks of kStatsChunk, then merged; slots that
+// hold nothing do not change the result.
+constexpr int kStatsChunk = 2048;
 __global__ __launch_bounds__(256) void stats_kernel(const StatSlot *slots,
-                                                    int64_t n, double *out) {
+                                                    int64_t n, int64_t chunk,
+                                                    double *out) {
+  const int64_t b0 = chunk * blockIdx.x, b1 = b0 + chunk < n ? b0 + chunk : n;
   int it = 0;
   double nc = 0.0, res = 0.0, fin = 0.0, fout = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += 256) {
+  for (int64_t k = b0 + threadIdx.x; k < b1; k += 256) {
     const StatSlot s = slots[k];
     it = max(it, s.max_it);
     nc += (double)s.nonconv;
@@ -778,24 +807,37 @@ __global__ __launch_bounds__(256) void stats_kernel(const StatSlot *slots,
     fin += s.flux_in;
     fout += s.flux_out;
   }
-  __shared__ int s_it[4];
-  __shared__ double s_res[4];
-  it = wave_max_i(it);
-  res = wave_max(res);
-  if ((threadIdx.x & 63) == 0) {
-    s_it[threadIdx.x >> 6] = it;
-    s_res[threadIdx.x >> 6] = res;
+  stats_out((double)it, nc, res, fin, fout, out + 5 * blockIdx.x);
+}
+
+__global__ __launch_bounds__(256) void stats_merge_kernel(const double *part,
+                                                          int64_t n,
+                                                          double *out) {
+  double it = 0.0, nc = 0.0, res = 0.0, fin = 0.0, fout = 0.0;
+  for (int64_t k = threadIdx.x; k < n; k += 256) {
+    it = fmax(it, part[5 * k]);
+    nc += part[5 * k + 1];
+    res = fmax(res, part[5 * k + 2]);
+    fin += part[5 * k + 3];
+    fout += part[5 * k + 4];
   }
-  const double snc = block_sum_256(nc);
-  const double sfin = block_sum_256(fin);
-  const double sfout = block_sum_256(fout);
-  if (threadIdx.x == 0) {
-    out[0] = (double)max(max(s_it[0], s_it[1]), max(s_it[2], s_it[3]));
-    out[1] = snc;
-    out[2] = fmax(fmax(s_res[0], s_res[1]), fmax(s_res[2], s_res[3]));
-    out[3] = sfin;
-    out[4] = sfout;
+  stats_out(it, nc, res, fin, fout, out);
+}
+
+// statistics of n slots into out; part: room doubles of scratch
+inline hipError_t stats_async(const StatSlot *slots, int64_t n, double *part,
+                              int64_t room, double *out, hipStream_t stream) {
+  const int64_t blocks = (n + kStatsChunk - 1) / kStatsChunk;
+  if (blocks <= 1 || 5 * blocks > room) {
+    stats_kernel<<<1, 256, 0, stream>>>(slots, n, n, out);
+    return hipGetLastError();
   }
+  stats_kernel<<<(unsigned)blocks, 256, 0, stream>>>(slots, n, kStatsChunk,
+                                                     part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  stats_merge_kernel<<<1, 256, 0, stream>>>(part, blocks, out);
+  return hipGetLastError();
 }
 
 // front of row blockIdx.x: dx * trapezoid sum of phi(T), of the sharp

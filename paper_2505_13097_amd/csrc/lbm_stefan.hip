@@ -157,7 +157,9 @@ irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
       if (v[i].tb) mt = std::max(mt, sweep_variant(*p, v[i]).slots());
   }
   L.max_items = mt;
-  L.n_partials = (n + kEnergyChunk - 1) / kEnergyChunk;
+  // energy partials, or those of the statistics
+  L.n_partials = std::max((n + kEnergyChunk - 1) / kEnergyChunk,
+                          stats_partials(mt));
   size_t off = 0;
   L.off_buf[0] = off;
   off += L.buf_bytes;
@@ -523,8 +525,8 @@ hipError_t irebm::zero_stats_async(lbm_stefan_t *h) {
 }
 
 int irebm::read_stats(lbm_stefan_t *h, lbm_stefan_stats *st) {
-  stats_kernel<<<1, 256, 0, h->stream>>>(h->slots, h->max_items, h->small);
-  HIPCHK(h, hipGetLastError());
+  HIPCHK(h, stats_async(h->slots, h->max_items, h->partials,
+                        stats_partials(h->max_items), h->small, h->stream));
   HIPCHK(h, handle_energy_async(h, h->buf[h->cur]));
   double hs[kSmallCount];
   HIPCHK(h, hipMemcpyAsync(hs, h->small, sizeof(hs), hipMemcpyDeviceToHost,

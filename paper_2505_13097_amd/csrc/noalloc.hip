@@ -159,8 +159,8 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
   if (!stats && !q.strict) return LBM_STEFAN_OK;
   // statistics of this step: the per-item slots, then the energy of dst
   double *small = (double *)(base + s.off_small);
-  stats_kernel<<<1, 256, 0, st>>>((const StatSlot *)base, s.nslots, small);
-  he = hipGetLastError();
+  he = stats_async((const StatSlot *)base, s.nslots,
+                   (double *)(base + s.off_parts), s.nparts, small, st);
   if (he == hipSuccess)
     he = energy_async(q, dst, (double *)(base + s.off_parts),
                       small + kSmallEnergy, st);
