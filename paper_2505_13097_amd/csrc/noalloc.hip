@@ -135,8 +135,10 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
     return nfail(LBM_STEFAN_EDEVICE,
                  std::string("hipGetSymbolAddress: ") + hipGetErrorString(he));
   const int mode = mode_of(q);
-  // the slots accumulate: clear them (a fill kernel), then the step
-  he = zero_async(base, s.nslots * sizeof(StatSlot), st);
+  // the slots accumulate: clear them (a fill kernel) where they are read,
+  // then the step (96 x 64 D2Q5: 11.6 us with the fill, 8.3 without)
+  const bool read = stats || q.strict;
+  if (read) he = zero_async(base, s.nslots * sizeof(StatSlot), st);
   if (q.dim == 3) {
     StepArgs3 A;
     fill_args3(q, &A);
@@ -156,7 +158,7 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
   if (he != hipSuccess)
     return nfail(LBM_STEFAN_EDEVICE,
                  std::string("step: ") + hipGetErrorString(he));
-  if (!stats && !q.strict) return LBM_STEFAN_OK;
+  if (!read) return LBM_STEFAN_OK;
   // statistics of this step: the per-item slots, then the energy of dst
   double *small = (double *)(base + s.off_small);
   he = stats_async((const StatSlot *)base, s.nslots,
