@@ -50,8 +50,9 @@ def workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
-KERNEL_SOURCES = ("irebm_node.hpp", "kernels.hpp", "host_util.hpp",
-                  "launch.hpp", "k_step_safeguarded.hip")
+KERNEL_SOURCES = ("irebm_node.hpp", "kernels.hpp", "sweep2d.hpp",
+                  "host_util.hpp", "launch.hpp", "launch_sweep.hpp",
+                  "k_step_safeguarded.hip", "k_sweep_safeguarded.hip")
 
 
 def kernel_source_hash():
@@ -1368,6 +1369,10 @@ def main():
     spl = steps_per_launch(vname, args.steps)
     if args.steps % 2 and spl == 2:
         raise SystemExit("--steps must be even for a two-step variant")
+    # two-step variants sweep lattices of this width, four steps a launch
+    sweeps = spl == 2 and prob.nx >= 128 and prob.ny >= 128
+    if sweeps:
+        spl = 4
     launches = -(-args.steps // spl)
     launch_ms = r["gpu_ms"] / launches
     bpn = bytes_per_node(prob)
@@ -1418,6 +1423,7 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": measured_traffic(prob.name, vname),
             "kernel": ("resident1d_kernel" if resident else
+                       "sweep_kernel" if sweeps else
                        "step2_kernel" if spl == 2 else "step_kernel"),
             "steps_per_launch": spl,
             "bytes_per_lattice_update": bpn,
