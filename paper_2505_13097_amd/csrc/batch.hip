@@ -44,6 +44,8 @@ struct lbm_stefan_batch {
   int2 *items = nullptr;
   StatSlot *slots = nullptr;
   SweepPlan *plans = nullptr;  // two-step variants
+  BatchQuery *query = nullptr; // count + 1 entries
+  int64_t nparts = 0;          // energy chunks of all instances
   double *profs = nullptr, *partials = nullptr, *small = nullptr;
   char *state[2] = {nullptr, nullptr};
   size_t state_bytes = 0;
@@ -62,7 +64,7 @@ struct lbm_stefan_batch {
 namespace {
 
 struct BLayout {
-  size_t descs, items, slots, plans, profs, partials, small, stateA, stateB,
+  size_t descs, items, slots, plans, query, profs, partials, small, stateA, stateB,
       total;
   size_t state_bytes;
   int64_t max_items, max_parts, small_len;
@@ -135,7 +137,7 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
     for (int k = 0; k < count; ++k) t += batch_items(v[i], ps[k]);
     L.max_items = std::max(L.max_items, t);
   }
-  L.max_parts = std::max<int64_t>(1, stats_partials(L.max_items));
+  L.max_parts = 0;
   L.state_bytes = 0;
   L.off.resize(count);
   L.prof_off.resize(count);
@@ -148,8 +150,9 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
     L.prof_off[k] = prof_total;
     prof_total += 4 * (size_t)std::max(ps[k].nx, ps[k].ny);
     max_ny = std::max(max_ny, ps[k].ny);
-    L.max_parts = std::max(L.max_parts, (n + kEnergyChunk - 1) / kEnergyChunk);
+    L.max_parts += (n + kEnergyChunk - 1) / kEnergyChunk;
   }
+  L.max_parts = std::max(L.max_parts, stats_partials(L.max_items));
   L.small_len = 16 * (int64_t)count + max_ny + 16;
   size_t o = 0;
   L.descs = o;
@@ -160,6 +163,8 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   o += align256(L.max_items * sizeof(StatSlot));
   L.plans = o;
   o += align256(count * sizeof(SweepPlan));
+  L.query = o;
+  o += align256((count + 1) * sizeof(BatchQuery));
   L.profs = o;
   o += align256(prof_total * 8);
   L.partials = o;
@@ -191,11 +196,13 @@ int build_schedule(lbm_stefan_batch_t *b) {
   const Variant &v = vt[b->variant];
   std::vector<StepArgs> d(b->count);
   std::vector<SweepPlan> pl(b->count);
+  std::vector<BatchQuery> qu(b->count + 1);
   std::vector<int2> t, wv;
   t.reserve(b->max_items);
   b->first_item.assign(b->count, 0);
   b->nitems_inst.assign(b->count, 0);
   int64_t sbase = 0;
+  b->nparts = 0;
   for (int k = 0; k < b->count; ++k) {
     const lbm_stefan_params &p = b->ps[k];
     double *prof[4];
@@ -221,7 +228,12 @@ int build_schedule(lbm_stefan_batch_t *b) {
     }
     b->nitems_inst[k] = n;
     sbase += n;
+    qu[k].part = b->nparts;
+    qu[k].nslots = n;
+    b->nparts += (p.nx * p.ny + kEnergyChunk - 1) / kEnergyChunk;
   }
+  qu[b->count].part = b->nparts;
+  qu[b->count].nslots = 0;
   b->ntiles = (int64_t)t.size();
   t.insert(t.end(), wv.begin(), wv.end());
   b->nitems = (int64_t)t.size();
@@ -230,6 +242,8 @@ int build_schedule(lbm_stefan_batch_t *b) {
   BCHK(b, hipMemcpyAsync(b->items, t.data(), t.size() * sizeof(int2),
                          hipMemcpyHostToDevice, b->stream));
   BCHK(b, hipMemcpyAsync(b->plans, pl.data(), pl.size() * sizeof(SweepPlan),
+                         hipMemcpyHostToDevice, b->stream));
+  BCHK(b, hipMemcpyAsync(b->query, qu.data(), qu.size() * sizeof(BatchQuery),
                          hipMemcpyHostToDevice, b->stream));
   BCHK(b, zero_async(b->slots, b->nslots * sizeof(StatSlot), b->stream));
   BCHK(b, hipStreamSynchronize(b->stream));
@@ -362,6 +376,7 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
   b->slots = (StatSlot *)(ws + L.slots);
   b->nslots = L.max_items;
   b->plans = (SweepPlan *)(ws + L.plans);
+  b->query = (BatchQuery *)(ws + L.query);
   b->profs = (double *)(ws + L.profs);
   b->partials = (double *)(ws + L.partials);
   b->small = (double *)(ws + L.small);
@@ -479,14 +494,21 @@ int lbm_stefan_batch_stats(lbm_stefan_batch_t *b, lbm_stefan_stats *out) {
   if (!b || !out) return bfail(b, LBM_STEFAN_EINVAL, "NULL argument");
   DeviceGuard g(b->device);
   std::vector<double> hs((size_t)b->count * 16);
-  for (int k = 0; k < b->count; ++k) {
-    const lbm_stefan_params &p = b->ps[k];
-    BCHK(b, stats_async(b->slots + b->first_item[k], b->nitems_inst[k],
-                        b->partials, stats_partials(b->nitems_inst[k]),
-                        b->small + 16 * k, b->stream));
-    BCHK(b, energy_async(p, b->state[b->cur] + b->off[k], b->partials,
-                         b->small + 16 * k + 8, b->stream));
-  }
+  BCHK(b, dispatch_qs(b->q, b->storage, [&](auto qt, auto tt) {
+         QS_TYPES(qt, tt);
+         batch_energy_kernel<Q, S><<<(unsigned)b->nparts, 256, 0, b->stream>>>(
+             b->descs, b->query, b->count, b->cur, b->mode == kEebm,
+             b->partials);
+         return hipGetLastError();
+       }));
+  batch_stats_kernel<<<(unsigned)b->count, 256, 0, b->stream>>>(
+      b->descs, b->query, b->partials, b->small);
+  BCHK(b, hipGetLastError());
+  for (int k = 0; k < b->count; ++k)
+    if (b->nitems_inst[k] > kStatsChunk)
+      BCHK(b, stats_async(b->slots + b->first_item[k], b->nitems_inst[k],
+                          b->partials, stats_partials(b->nitems_inst[k]),
+                          b->small + 16 * k, b->stream));
   BCHK(b, hipMemcpyAsync(hs.data(), b->small, hs.size() * 8,
                          hipMemcpyDeviceToHost, b->stream));
   BCHK(b, hipStreamSynchronize(b->stream));

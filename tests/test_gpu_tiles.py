@@ -157,9 +157,10 @@ def test_batch_sweeps_equal_single_steps(scheme):
     for q, storage in ((5, "f32"), (9, "f64"), (5, "f64"), (9, "f32")):
         probs = []
         for (nx, ny), bc in zip([(3, 3), (5, 40), (88, 88), (87, 120),
-                                 (40, 900), (300, 64), (200, 331)],
+                                 (40, 900), (300, 64), (200, 331),
+                                 (700, 300)],
                                 [WALLS[3], WALLS[4], WALLS[1], WALLS[0],
-                                 WALLS[2], WALLS[3], WALLS[1]]):
+                                 WALLS[2], WALLS[3], WALLS[1], WALLS[1]]):
             x = _prob(nx, ny, q, bc, storage, scheme)
             if nx > 199:
                 x = x.with_(T0=-0.5 + rng.uniform(-1e-3, 1e-3, (ny, nx)))
