@@ -76,11 +76,15 @@ int64_t batch_items(const Variant &v, const lbm_stefan_params &p) {
   return v.tb ? batch_plan(p, v).slots() : items_for(v, p.nx, p.ny);
 }
 
-// the variant a batch starts with (and -1 selects): sweeping waves, which
-// win on every mix measured, unless a member is an IREBM melt that freezes
-// (see sweep_default)
+// the variant a batch starts with (and -1 selects): sweeping waves, unless
+// the batch is small or a member is an IREBM melt that freezes (see
+// kSweepNodes, sweep_default)
 int default_variant(const lbm_stefan_params *ps, int count) {
   if (ps[0].q == 3) return kDefaultVariant1D;
+  int64_t nodes = 0;
+  for (int k = 0; k < count; ++k) nodes += ps[k].nx * ps[k].ny;
+  if (ps[0].scheme == LBM_SCHEME_IREBM && nodes <= kSweepNodes)
+    return kDefaultVariant2D;
   for (int k = 0; k < count; ++k) {
     bool hot;
     front_walls(ps[k], &hot);

@@ -199,9 +199,23 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
   return P;
 }
 
+// IREBM lattices of fewer nodes do not sweep: where the front has spread over
+// the lattice every row of a wave solves, and on a lattice that does not fill
+// the chip that chain (44 solves per four steps at 8 rows per segment) sets
+// the time: a heated lattice that has melted took 2.6 times the single steps,
+// while at 800^2 all liquid costs 1.06 times and all solid half.
+constexpr int64_t kSweepNodes = 600000;
+
+// rows per segment: enough waves for the chip, few halo rows (8 on 512^2, 16
+// on 2048^2, 32 on 8192^2)
+inline int sweep_rows(int64_t ny) {
+  const int64_t rows = (ny / 128 + 3) / 4 * 4;
+  return (int)(rows < 8 ? 8 : (rows > 32 ? 32 : rows));
+}
+
 // sweep_kernel under the library default (an empty plan: tile_kernel or
 // single steps).  Measured (us per step, the best one-step tiling -> here):
-// IREBM heated at a wall 300^2 D2Q9 FP32 8.7 -> 6.0 (tile_kernel 7.4), 1001
+// IREBM heated at a wall 1001
 // x 777 D2Q9 FP64 21.4 -> 11.6, 2048^2 D2Q5 FP32 32.6 -> 16.0, D2Q9 FP64
 // 134 -> 46, 8192^2 D2Q9 FP32 921 -> 324; EEBM 201^2 D2Q9 FP64 6.0 -> 3.8
 // (tile_kernel 4.2), 801^2 19.1 -> 7.2, 2048^2 D2Q5 FP32 27.9 -> 9.6.  A
@@ -209,20 +223,17 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
 // liquid, so the solves of a wave, one after the other, cost more than the
 // traffic saved (801^2 D2Q5 21.2 -> 22.4).
 // Three steps instead of four on FP32 lattices that the memory-side cache
-// holds (2048^2 D2Q9 31.9 against 34.6); rows per segment: enough waves for
-// the chip, few halo rows (8 on 512^2, 16 on 2048^2, 32 on 8192^2).
+// holds (2048^2 D2Q9 31.9 against 34.6).
 inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   const int64_t n = p.nx * p.ny;
   if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM) return SweepPlan();
   const bool eebm = p.scheme == LBM_SCHEME_EEBM;
   bool hot;
   front_walls(p, &hot);
-  if (n <= (eebm ? 30000 : 60000) || (!eebm && !hot)) return SweepPlan();
+  if (n <= (eebm ? 30000 : kSweepNodes) || (!eebm && !hot)) return SweepPlan();
   const int k = !eebm && p.storage == LBM_STORE_F32 && n > 500000 &&
                         n < 6000000 ? 3 : 4;
-  const int64_t rows = (p.ny / 128 + 3) / 4 * 4;
-  return sweep_plan(p, k, (int)(rows < 8 ? 8 : (rows > 32 ? 32 : rows)),
-                    n > (1 << 24));
+  return sweep_plan(p, k, sweep_rows(p.ny), n > (1 << 24));
 }
 
 // An instance of a batch under a two-step variant: its plan, or tiles alone
@@ -243,12 +254,15 @@ inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v) {
   return P;
 }
 
-// sweep_kernel under a two-step variant, in segments of its rows
+// sweep_kernel under a two-step variant, in segments of at most its rows
 inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
   if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM || !v.tb) return SweepPlan();
   for (int i = 0; i < 4; ++i)
     if (p.bc[i] == LBM_BC_NEUMANN) return SweepPlan();
-  return sweep_plan(p, 4, v.rows, v.nt != 0);
+  if (p.scheme == LBM_SCHEME_IREBM && p.nx * p.ny <= kSweepNodes)
+    return SweepPlan();
+  const int rows = sweep_rows(p.ny);
+  return sweep_plan(p, 4, v.rows < rows ? v.rows : rows, v.nt != 0);
 }
 
 // The one-step tiling of the library default: one node per thread and 64 x
