@@ -78,12 +78,12 @@ int64_t batch_items(const Variant &v, const lbm_stefan_params &p) {
 
 // the variant a batch starts with (and -1 selects): sweeping waves, unless
 // the batch is small or a member is an IREBM melt that freezes (see
-// kSweepNodes, sweep_default)
+// sweep_nodes, sweep_default)
 int default_variant(const lbm_stefan_params *ps, int count) {
   if (ps[0].q == 3) return kDefaultVariant1D;
   int64_t nodes = 0;
   for (int k = 0; k < count; ++k) nodes += ps[k].nx * ps[k].ny;
-  if (ps[0].scheme == LBM_SCHEME_IREBM && nodes <= kSweepNodes)
+  if (ps[0].scheme == LBM_SCHEME_IREBM && nodes <= sweep_nodes(ps[0].storage))
     return kDefaultVariant2D;
   for (int k = 0; k < count; ++k) {
     bool hot;

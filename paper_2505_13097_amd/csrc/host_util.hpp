@@ -156,11 +156,14 @@ inline int front_walls(const lbm_stefan_params &p, bool *hot) {
 // front starts (a strip that reaches the front solves in every row: the
 // 8192^2 cavity takes 380 us per step with one tile, 324 with two, 347 and
 // 330 with three and four), one at the other walls.  The strip next to it
-// goes in segments of 8 rows: the batch named at batch_plan, its fronts past
-// the frame, takes 622 us with segments as everywhere, 560 with 16, 505 with
-// 8 and 520 with 4; lattices whose front is inside the frame do not change.
+// goes in segments of `frows` rows, for a front that has left the frame:
+// 8 in a batch (the one named at batch_plan takes 622 us with segments as
+// everywhere, 505 with 8, 520 with 4), 2 in a single lattice (us per step
+// with the front in the frame / past it, 8 rows against 2: 2048^2 D2Q5 FP32
+// 17.7 / 41.7 against 18.6 / 29.3, single steps 31; 900 x 700 D2Q9 FP64
+// 10.1 / 44 against 10.2 / 24, single steps 20).
 inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
-                            bool nt) {
+                            int frows, bool nt) {
   SweepPlan P;
   const int T = frame_tile(k), w = 64 - 2 * k;
   const int nx = (int)p.nx, ny = (int)p.ny;
@@ -190,8 +193,7 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
   P.fr = front >> 1 & 1;
   P.cut(w);
   P.rows = rows;
-  P.frows = 8;
-  if (P.frows > rows) P.frows = rows;
+  P.frows = frows < rows ? frows : rows;
   P.fseg = (P.yb - P.ya + P.frows - 1) / P.frows;
   P.nseg = (P.yb - P.ya + rows - 1) / rows;
   P.nt = nt ? 1 : 0;
@@ -201,10 +203,12 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
 
 // IREBM lattices of fewer nodes do not sweep: where the front has spread over
 // the lattice every row of a wave solves, and on a lattice that does not fill
-// the chip that chain (44 solves per four steps at 8 rows per segment) sets
-// the time: a heated lattice that has melted took 2.6 times the single steps,
-// while at 800^2 all liquid costs 1.06 times and all solid half.
-constexpr int64_t kSweepNodes = 600000;
+// the chip that chain sets the time (512^2, melted: 2.6 times the single
+// steps; 1001 x 777 D2Q5 FP32: 7.3 us per step against 11.5 with the front in
+// the frame, 14.0 past it).
+inline int64_t sweep_nodes(int storage) {
+  return storage == LBM_STORE_F64 ? 600000 : 1500000;
+}
 
 // rows per segment: enough waves for the chip, few halo rows (8 on 512^2, 16
 // on 2048^2, 32 on 8192^2)
@@ -230,10 +234,10 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   const bool eebm = p.scheme == LBM_SCHEME_EEBM;
   bool hot;
   front_walls(p, &hot);
-  if (n <= (eebm ? 30000 : kSweepNodes) || (!eebm && !hot)) return SweepPlan();
+  if (n <= (eebm ? 30000 : sweep_nodes(p.storage)) || (!eebm && !hot)) return SweepPlan();
   const int k = !eebm && p.storage == LBM_STORE_F32 && n > 500000 &&
                         n < 6000000 ? 3 : 4;
-  return sweep_plan(p, k, sweep_rows(p.ny), n > (1 << 24));
+  return sweep_plan(p, k, sweep_rows(p.ny), 2, n > (1 << 24));
 }
 
 // An instance of a batch under a two-step variant: its plan, or tiles alone
@@ -242,7 +246,7 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
 // and 128 (two-step launches of step2_kernel, split by quiet and solving
 // items, took 1040).
 inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v) {
-  SweepPlan P = sweep_plan(p, 4, v.rows < 32 ? v.rows : 32, v.nt != 0);
+  SweepPlan P = sweep_plan(p, 4, v.rows < 32 ? v.rows : 32, 8, v.nt != 0);
   if (P.k > 0) return P;
   P.k = 4;
   P.tile = frame_tile(4);
@@ -259,10 +263,10 @@ inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
   if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM || !v.tb) return SweepPlan();
   for (int i = 0; i < 4; ++i)
     if (p.bc[i] == LBM_BC_NEUMANN) return SweepPlan();
-  if (p.scheme == LBM_SCHEME_IREBM && p.nx * p.ny <= kSweepNodes)
+  if (p.scheme == LBM_SCHEME_IREBM && p.nx * p.ny <= sweep_nodes(p.storage))
     return SweepPlan();
   const int rows = sweep_rows(p.ny);
-  return sweep_plan(p, 4, v.rows < rows ? v.rows : rows, v.nt != 0);
+  return sweep_plan(p, 4, v.rows < rows ? v.rows : rows, 2, v.nt != 0);
 }
 
 // The one-step tiling of the library default: one node per thread and 64 x

@@ -71,7 +71,8 @@ def test_tiles_equal_single_steps(size, scheme):
 # or nearly none
 SWEEP_SIZES = [(88, 700), (87, 700), (120, 560), (700, 40), (1700, 31),
                (64, 1000), (63, 1000), (145, 431), (257, 251), (700, 531),
-               (88, 6830), (20000, 31), (907, 701)]
+               (88, 6830), (20000, 31), (907, 701),
+               (2111, 719)]
 
 
 @pytest.mark.parametrize("scheme", ["irebm", "eebm"])
