@@ -158,10 +158,8 @@ inline int front_walls(const lbm_stefan_params &p, bool *hot) {
 // 330 with three and four), one at the other walls.  The strip next to it
 // goes in segments of `frows` rows, for a front that has left the frame:
 // 8 in a batch (the one named at batch_plan takes 622 us with segments as
-// everywhere, 505 with 8, 520 with 4), 2 in a single lattice (us per step
-// with the front in the frame / past it, 8 rows against 2: 2048^2 D2Q5 FP32
-// 17.7 / 41.7 against 18.6 / 29.3, single steps 31; 900 x 700 D2Q9 FP64
-// 10.1 / 44 against 10.2 / 24, single steps 20).
+// everywhere, 505 with 8, 520 with 4), 2 in a single lattice that sweeps
+// wherever its front is (route_lattice).
 inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
                             int frows, bool nt) {
   SweepPlan P;
@@ -201,11 +199,44 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
   return P;
 }
 
-// IREBM lattices of fewer nodes do not sweep: where the front has spread over
-// the lattice every row of a wave solves, and on a lattice that does not fill
-// the chip that chain sets the time (512^2, melted: 2.6 times the single
-// steps; 1001 x 777 D2Q5 FP32: 7.3 us per step against 11.5 with the front in
-// the frame, 14.0 past it).
+// Where a front stands off the walls, the waves that hold it solve in every
+// row, one after the other, about 6 us a row at the slowest lane: a chain of
+// k rows + k (k - 1) of them per launch, against k single steps that each
+// pass over the state at 5 TB/s.  us per step, sweeps with the front in the
+// frame / at column 100 / half way / single steps, half way: 900 x 700 D2Q9
+// FP64 10 / 40 / 47 / 21, 2048^2 D2Q5 FP32 18 / 58 / 71 / 38, 4096^2 68 / 142
+// / 199 / 151, 2048^2 D2Q9 FP64 50 / 98 / 129 / 134, 8192^2 D2Q9 FP32 344 /
+// 464 / 601 / 925.  So a lattice on which such a chain costs more than the
+// single steps leaves the sweeps where a wave holds more rows with solves
+// than they pay for (RouteCtl), and one on which it does not sweeps always.
+// The strip next to a wall where a front starts goes in segments of `frows`
+// rows where they are short enough for that.
+inline void route_lattice(SweepPlan *P, const lbm_stefan_params &p, int frows) {
+  if (P->k == 0 || p.scheme != LBM_SCHEME_IREBM) return;
+  const double step_us = 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) *
+                         (double)p.nx * (double)p.ny / 5e6;
+  P->chain_max = (int32_t)(P->k * step_us / 6.0 < 1e6 ? P->k * step_us / 6.0
+                                                      : 1e6);
+  P->gated = P->k * P->rows + P->k * (P->k - 1) > P->chain_max;
+  if (P->k * frows + P->k * (P->k - 1) > P->chain_max) {
+    P->fl = P->fr = 0;
+    P->cut(64 - 2 * P->k);
+  } else {
+    P->frows = frows < P->rows ? frows : P->rows;
+    P->fseg = (P->yb - P->ya + P->frows - 1) / P->frows;
+  }
+}
+
+// nodes above which the two routes' launches go on streams of their own
+// (advance_routed)
+constexpr int64_t kRouteBeside = 2000000;
+
+// IREBM lattices (and batches) of fewer nodes do not sweep: the launches of
+// the route not taken are too large a part of a step (front half way, default
+// with them / single steps: 900 x 700 D2Q9 FP64 24.6 / 23.6 us, 1001 x 777
+// D2Q5 FP32 14.1 / 13.2), and in a batch of small lattices most nodes lie in
+// the frame (48 FP32 D2Q5 lattices of 64^2 to 256^2, 1.4M nodes, 28.6 us per
+// step, 37.6 in sweeps).
 inline int64_t sweep_nodes(int storage) {
   return storage == LBM_STORE_F64 ? 600000 : 1500000;
 }
@@ -235,9 +266,11 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   bool hot;
   front_walls(p, &hot);
   if (n <= (eebm ? 30000 : sweep_nodes(p.storage)) || (!eebm && !hot)) return SweepPlan();
-  const int k = !eebm && p.storage == LBM_STORE_F32 && n > 500000 &&
-                        n < 6000000 ? 3 : 4;
-  return sweep_plan(p, k, sweep_rows(p.ny), 2, n > (1 << 24));
+  const int k = !eebm && p.storage == LBM_STORE_F32 && n < 6000000 ? 3 : 4;
+  SweepPlan P = sweep_plan(p, k, sweep_rows(p.ny), sweep_rows(p.ny),
+                           n > (1 << 24));
+  route_lattice(&P, p, 2);
+  return P;
 }
 
 // An instance of a batch under a two-step variant: its plan, or tiles alone
@@ -265,8 +298,10 @@ inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
     if (p.bc[i] == LBM_BC_NEUMANN) return SweepPlan();
   if (p.scheme == LBM_SCHEME_IREBM && p.nx * p.ny <= sweep_nodes(p.storage))
     return SweepPlan();
-  const int rows = sweep_rows(p.ny);
-  return sweep_plan(p, 4, v.rows < rows ? v.rows : rows, 2, v.nt != 0);
+  const int rows = v.rows < sweep_rows(p.ny) ? v.rows : sweep_rows(p.ny);
+  SweepPlan P = sweep_plan(p, 4, rows, rows, v.nt != 0);
+  route_lattice(&P, p, 2);
+  return P;
 }
 
 // The one-step tiling of the library default: one node per thread and 64 x

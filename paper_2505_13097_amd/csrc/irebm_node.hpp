@@ -96,6 +96,19 @@ struct StatSlot {
   double flux_out;
 };
 
+// How a lattice (or a batch) that sweeps is advanced, decided on the device:
+// the launches of a group of steps are issued twice, as sweeps of several
+// steps and as single steps, and those of one kind leave at once.  A sweep
+// counts the rows that took a solve; where they are too many for it the
+// groups that follow go by single steps, which give the same states.
+struct RouteCtl {
+  int32_t route;  // of the group under way: 0 sweeps, 1 single steps
+  int32_t chain;  // most rows with a solve in one wave of a sweep
+  int32_t age;    // groups of single steps since the last sweep
+  int32_t pad;
+  unsigned long long units;  // the cost of such rows over all waves
+};
+
 // Everything one step of one lattice needs; passed by value.
 struct StepArgs {
   const void *src;      // current state planes
@@ -120,7 +133,13 @@ struct StepArgs {
   double wall_T[4];
   const double *prof[4];
   StatSlot *slots;
+  RouteCtl *ctl;        // null: the launch always runs
 };
+
+// may this launch (of sweeps, route 0, or single steps, 1) run?
+__device__ __forceinline__ bool on_route(const RouteCtl *ctl, int route) {
+  return !ctl || *to_global(&ctl->route) == route;
+}
 
 // ---- regularized liquid fraction (Section 4.1)
 // phi(T) = (1 + tanh(u))/2 = 1/(1 + exp(-2u)), u = (T - T_m)/delta, and

@@ -328,6 +328,7 @@ namespace {
 // one time step of one lattice, one block per work item (XCD-aware order)
 template <int Q, typename S, int NPT, int MODE, bool NT>
 __global__ __launch_bounds__(256) void step_kernel(StepArgs A) {
+  if (!on_route(A.ctl, 1)) return;
   const int b = blockIdx.x;
   if ((b & 7) * A.per_xcd + (b >> 3) >= A.nitems) return;
   const int t = A.front_first && !A.reverse

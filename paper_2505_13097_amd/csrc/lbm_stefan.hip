@@ -181,6 +181,8 @@ irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
   L.adjoint = (p->flags & LBM_FLAG_ADJOINT) != 0;
   L.off_adj = off;
   if (L.adjoint) off += adjoint_bytes(p, mt);
+  L.off_route = off;
+  off += align256(sizeof(RouteCtl));
   L.off_lf = off;
   off += ilfbm_bytes(p);
   L.total = off;
@@ -349,6 +351,83 @@ hipError_t irebm::handle_side(lbm_stefan_t *h) {
   return e;
 }
 
+namespace {
+
+// nsteps steps of a lattice whose sweeps are gated: groups that are issued as
+// sweeps and as single steps, one kind of which leaves at once (RouteCtl).
+// Both end in the same buffer, so the sweeps of a group are as many as its
+// steps, or an even number fewer.  A launch that leaves at once costs 1 us and
+// 0.9 ns a block, so on large lattices the single steps are issued on the
+// handle's second stream, beside the sweeps (us per step, one stream / two,
+// front in the frame: 4096^2 D2Q5 FP32 73.6 / 67.7, 2048^2 22.7 / 20.2, past
+// it 33.4 / 34.0; 1001 x 777 D2Q9 FP64 12.9 / 12.2 and 24.2 / 25.0: there on
+// one).
+hipError_t advance_routed(lbm_stefan_t *h, int64_t nsteps) {
+  const int64_t K = h->sweep.k;
+  hipError_t e = hipSuccess;
+  while (nsteps > 0 && e == hipSuccess) {
+    const int64_t n = nsteps >= 32 * K ? 16 * K : nsteps;
+    int64_t m = (n + K - 1) / K;
+    m += (m ^ n) & 1;
+    if (n / m < 2) {
+      // (too few steps for sweeps of two or more)
+      e = launch_step(h, h->buf[h->cur], h->buf[h->cur ^ 1]);
+      h->cur ^= 1;
+      h->steps++;
+      nsteps--;
+      continue;
+    }
+    const bool beside = nodes_of(h->p) > kRouteBeside;
+    if (beside) e = hipEventRecord(h->fork, h->stream);
+    if (beside && e == hipSuccess) e = hipStreamWaitEvent(h->side, h->fork, 0);
+    int b = h->cur, c = h->cur;
+    for (int64_t i = 0, left = n; i < m && e == hipSuccess; ++i, b ^= 1) {
+      const int64_t k = (left + m - i - 1) / (m - i);
+      e = launch_steps(h, h->buf[b], h->buf[b ^ 1], (int)k, h->stream, nullptr,
+                       0, h->route);
+      for (int64_t j = 0; j < k && e == hipSuccess; ++j, c ^= 1)
+        e = launch_step(h, h->buf[c], h->buf[c ^ 1],
+                        beside ? h->side : h->stream, h->route);
+      left -= k;
+    }
+    if (beside && e == hipSuccess) e = hipEventRecord(h->join, h->side);
+    if (beside && e == hipSuccess)
+      e = hipStreamWaitEvent(h->stream, h->join, 0);
+    if (e != hipSuccess) break;
+    route_decide_kernel<<<1, 1, 0, h->stream>>>(h->route, 0,
+                                                h->sweep.chain_max, ~0ull);
+    e = hipGetLastError();
+    h->cur ^= n & 1;
+    h->steps += n;
+    nsteps -= n;
+  }
+  return e;
+}
+
+}  // namespace
+
+hipError_t irebm::scan_route(lbm_stefan_t *h) {
+  if (!h->sweep.gated) return hipSuccess;
+  const SweepPlan &P = h->sweep;
+  if (nodes_of(h->p) > kRouteBeside) {
+    const hipError_t e = handle_side(h);
+    if (e != hipSuccess) return e;
+  }
+  StepArgs A;
+  fill_step_args(h, &A);
+  A.src = h->buf[h->cur];
+  // (the counts are zero: the last group's decision left them so)
+  const hipError_t e = dispatch_qs(h->p.q, h->p.storage, [&](auto qt, auto tt) {
+    QS_TYPES(qt, tt);
+    route_scan_kernel<Q, S><<<(unsigned)((P.waves() + 3) / 4), 256, 0,
+                              h->stream>>>(A, P, h->route);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  route_decide_kernel<<<1, 1, 0, h->stream>>>(h->route, 1, P.chain_max, ~0ull);
+  return hipGetLastError();
+}
+
 hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
   if (h->p.scheme == LBM_SCHEME_ILFBM) return ilfbm_advance(h, nsteps);
   if (h->p.dim == 3) {
@@ -403,6 +482,7 @@ hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
       return hipSuccess;
     }
   }
+  if (h->sweep.gated) return advance_routed(h, nsteps);
   if (steps_per_launch(h) > 1) {
     while (nsteps > 0) {
       const int k = next_launch(h, nsteps);
@@ -434,16 +514,20 @@ hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
 }
 
 hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
-                              void *dst, hipStream_t stream) {
+                              void *dst, hipStream_t stream,
+                              RouteCtl *ctl) {
   StepArgs A;
   fill_step_args(h, &A);
+  A.ctl = ctl;
   A.src = src;
   A.dst = dst;
   int nv;
   const Variant *vt = variants(h->p.q, &nv);
   // a single step under a two-step variant takes the default tiling, and
   // so does a step under the resident variant
-  const Variant &v = vt[vt[h->variant].tb    ? default_2d(h->p)
+  // (beside sweeps the tiling of fewest blocks: they cost as empty launches)
+  const Variant &v = vt[ctl                  ? kDefaultVariant2D
+                        : vt[h->variant].tb  ? default_2d(h->p)
                         : vt[h->variant].res ? kDefaultVariant1D
                                              : h->variant];
   // a Dirichlet x = 0 wall is where the workloads heat: its tiles first
@@ -466,7 +550,7 @@ void irebm::plan_steps(lbm_stefan_t *h) {
 }
 
 int irebm::steps_per_launch(const lbm_stefan_t *h) {
-  return std::max(1, std::max(h->plan.k, h->sweep.k));
+  return std::max(1, std::max(h->plan.k, h->sweep.gated ? 1 : h->sweep.k));
 }
 
 int irebm::next_launch(const lbm_stefan_t *h, int64_t nsteps) {
@@ -477,10 +561,12 @@ int irebm::next_launch(const lbm_stefan_t *h, int64_t nsteps) {
 
 hipError_t irebm::launch_steps(const lbm_stefan_t *h, const void *src,
                                void *dst, int k, hipStream_t stream,
-                               void *mid, int64_t mid_stride) {
-  if (k == 1) return launch_step(h, src, dst, stream);
+                               void *mid, int64_t mid_stride,
+                               RouteCtl *ctl) {
+  if (k == 1) return launch_step(h, src, dst, stream, ctl);
   StepArgs A;
   fill_step_args(h, &A);
+  A.ctl = ctl;
   A.src = src;
   A.dst = dst;
   if (h->plan.k > 0)
@@ -620,6 +706,7 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
   h->partials = (double *)(ws + L.off_partials);
   h->small = (double *)(ws + L.off_small);
   h->adj = ws + L.off_adj;
+  h->route = (RouteCtl *)(ws + L.off_route);
   const int64_t n = nodes_of(*p);
   for (int k = 0; k < 4; ++k) {
     h->prof[k] = (double *)(ws + L.off_prof[k]);
@@ -658,8 +745,10 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
     if (p->scheme == LBM_SCHEME_ILFBM) ilfbm_attach(h, ws + L.off_lf);
     ie = init_async(p->q, p->storage, A, T0d, h->stream, h->lf);
   }
-  if (ie != hipSuccess || zero_stats_async(h) != hipSuccess ||
-      hipStreamSynchronize(h->stream) != hipSuccess)
+  if (ie == hipSuccess)
+    ie = zero_async(h->route, sizeof(RouteCtl), h->stream);
+  if (ie != hipSuccess || scan_route(h) != hipSuccess ||
+      zero_stats_async(h) != hipSuccess || hipStreamSynchronize(h->stream) != hipSuccess)
     return bail(fail(h, LBM_STEFAN_EDEVICE, "init kernels failed"));
   *out = h;
   return LBM_STEFAN_OK;
@@ -753,6 +842,7 @@ int lbm_stefan_set_state(lbm_stefan_t *h, const void *state, int32_t on_device) 
                            on_device ? hipMemcpyDeviceToDevice
                                      : hipMemcpyHostToDevice,
                            h->stream));
+  HIPCHK(h, scan_route(h));
   if (!on_device) HIPCHK(h, hipStreamSynchronize(h->stream));
   return LBM_STEFAN_OK;
 }
@@ -815,6 +905,7 @@ int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant) {
   h->variant = variant;
   h->by_default = false;
   plan_steps(h);
+  HIPCHK(h, scan_route(h));
   // the tile -> slot mapping changes with the tile shape
   HIPCHK(h, zero_stats_async(h));
   return LBM_STEFAN_OK;
@@ -874,7 +965,8 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     // two-step variant runs its own kernel only)
     const int64_t n = steps + (steps & 1);
     const int64_t steps0 = h->steps;
-    err = advance(h, 2);
+    err = scan_route(h);
+    if (err == hipSuccess) err = advance(h, 2);
     if (err == hipSuccess) err = hipEventRecord(e0, h->stream);
     if (err == hipSuccess) err = advance(h, n);
     h->steps = steps0;
@@ -903,6 +995,7 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   if (err != hipSuccess)
     return fail(h, LBM_STEFAN_EDEVICE,
                 std::string("autotune: ") + hipGetErrorString(err));
+  HIPCHK(h, scan_route(h));
   HIPCHK(h, zero_stats_async(h));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   if (best_variant) *best_variant = best;

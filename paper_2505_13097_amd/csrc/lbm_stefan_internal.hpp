@@ -20,6 +20,7 @@ struct Layout {
   size_t off_prof[4] = {0, 0, 0, 0};
   size_t off_slots = 0, off_partials = 0, off_small = 0, off_adj = 0;
   size_t off_flags = 0; // 3D split step: one flag per quiet-pass item
+  size_t off_route = 0; // RouteCtl
   size_t off_lf = 0;    // ILFBM: three liquid fraction planes, the per-
                         // block pending values and the control block
   size_t total = 0;
@@ -63,6 +64,7 @@ struct lbm_stefan {
   bool by_default = false;
   irebm::TilePlan plan;
   irebm::SweepPlan sweep;
+  irebm::RouteCtl *route = nullptr;
   int64_t steps = 0;
   void *tape = nullptr;          // last forward tape
   int64_t tape_steps = 0, tape_interval = 0;
@@ -90,19 +92,23 @@ void fill_args(const lbm_stefan_params &p, double *const prof[4],
                StepArgs *A);
 void fill_step_args(const lbm_stefan_t *h, StepArgs *A);
 hipError_t launch_step(const lbm_stefan_t *h, const void *src, void *dst,
-                       hipStream_t stream = nullptr);
+                       hipStream_t stream = nullptr,
+                       RouteCtl *ctl = nullptr);
+// the route of the handle's current state (sweeps that are gated)
+hipError_t scan_route(lbm_stefan_t *h);
 // the plans of the handle's variant (or of the library default)
 void plan_steps(lbm_stefan_t *h);
 // Steps one launch of tile_kernel or sweep_kernel takes under the handle's
-// variant (1: it takes neither), and the steps of the next launch of nsteps (at most that many, the
-// launches as even as they come).
+// variant (1: it takes neither, or sweeps by groups), and the steps of the
+// next launch of nsteps (at most that many, the launches as even as they
+// come).
 int steps_per_launch(const lbm_stefan_t *h);
 int next_launch(const lbm_stefan_t *h, int64_t nsteps);
 // k steps (at most steps_per_launch) from src to dst; mid: step l < k is
 // also stored at mid + l * mid_stride bytes
 hipError_t launch_steps(const lbm_stefan_t *h, const void *src, void *dst,
                         int k, hipStream_t stream, void *mid = nullptr,
-                        int64_t mid_stride = 0);
+                        int64_t mid_stride = 0, RouteCtl *ctl = nullptr);
 // the handle's second stream (split steps, the reverse sweep's
 // recomputation) and its two events, created on first use
 hipError_t handle_side(lbm_stefan_t *h);

@@ -64,6 +64,13 @@ struct SweepRow {
   S mid[3], up[UP], up1[UP];
   double th;
 };
+// what nband rows with a node in or near the band and nliquid rows of solid
+// and liquid nodes cost the chip, in units of 0.45 ns (measured on batches of
+// 12 to 400 lattices: 0.45 ns a liquid row, 0.7 to 2.2 ns one with the band)
+__host__ __device__ constexpr int route_units(int nband, int nliquid) {
+  return 5 * nband + nliquid;
+}
+
 // index of direction i among those kept (rest, +x, -x; the upward ones)
 constexpr int sweep_mid(int i) { return i == 0 ? 0 : (i == 1 ? 1 : 2); }
 constexpr int sweep_up(int i) { return i == 2 ? 0 : (i == 5 ? 1 : 2); }
@@ -72,7 +79,8 @@ constexpr int sweep_up(int i) { return i == 2 ? 0 : (i == 5 ? 1 : 2); }
 // from src to dst.  The K columns and rows around them are lattice nodes
 // (the frame, or wrapped on a periodic axis).  nt: stores bypass the
 // caches.  MID: level l < K is also stored at mid + l * mid_stride bytes
-// (the reverse mode's recomputed states).
+// (the reverse mode's recomputed states).  A.ctl: when given, takes the rows
+// that held a solve.
 template <int Q, typename S, int MODE, int K, bool MID>
 __device__ __forceinline__ void sweep_body(const StepArgs &A,
                                            gptr<const S> __restrict__ src,
@@ -121,6 +129,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
   const int re = y1 - 1 + K;   // last row loaded
   NodeStats st;
   uint64_t saw = 0, saw2 = 0;  // quiet nodes; those of two iterations
+  int rows_solved = 0;  // those in the band times 2^16, those above it only
 #pragma unroll
   for (int j = 0; j < Q; ++j) v[j] = (S)0;
   load(y0 - K, pf);
@@ -212,6 +221,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
                 above = newton_liquid(m0, th, A, tn, it, conv);
               if (__builtin_amdgcn_ballot_w64(!above) == 0) {
                 solve = false;
+                rows_solved += 1;
                 const bool two = !(fabs(d) <= A.tol);
                 saw |= __builtin_amdgcn_ballot_w64(valid && quiet);
                 saw2 |= __builtin_amdgcn_ballot_w64(valid && quiet && two);
@@ -229,6 +239,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
             }
           }
           if (!solve) continue;
+          rows_solved += 1 << 16;
           // a row with a solve in or near the band (the arguments read
           // again: see step_item)
           int z = 0;
@@ -264,6 +275,16 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
       s.nonconv += nc;
       s.max_res = fmax(s.max_res, res);
       *slot = s;
+      // (read here: held through the sweep it would cost registers)
+      int z = 0;
+      asm volatile("" : "+s"(z));
+      RouteCtl *ctl = (&A)[z].ctl;
+      if (ctl && rows_solved > 0) {
+        const int nband = rows_solved >> 16, nliquid = rows_solved & 0xffff;
+        atomicMax(&ctl->chain, nband + nliquid);
+        atomicAdd(&ctl->units,
+                  (unsigned long long)route_units(nband, nliquid));
+      }
     }
   }
 }
@@ -289,6 +310,9 @@ struct SweepPlan {
   int32_t fl = 0, fr = 0;              // a front starts at x = 0, at nx - 1
   int32_t nfl = 0, nfr = 0, frows = 1, fseg = 0;
   int32_t nt = 0;
+  // 1: the lattice (the batch) goes by single steps where a sweep holds a
+  // wave of more than chain_max rows with solves
+  int32_t gated = 0, chain_max = 0;
   // strips of w columns
   void cut(int w) {
     strips = (xb - xa + w - 1) / w;
@@ -358,6 +382,7 @@ __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(sweep_waves(Q, sizeof(S), K))))
 void sweep_kernel(StepArgs A, SweepPlan P, char *mid, int64_t mid_stride) {
   __shared__ S lds[Q * kFrameSide * kFrameSide];
+  if (!on_route(A.ctl, 0)) return;
   const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
   const int nt = (int)P.tiles(), nw = (int)P.waves();
   const int ct = (nt + 7) >> 3, cw = (((nw + 7) >> 3) + 3) & ~3;
@@ -395,8 +420,9 @@ void batch_sweep_kernel(const StepArgs *__restrict__ descs,
                         const SweepPlan *__restrict__ plans,
                         const int2 *__restrict__ tiles, int32_t nt,
                         const int2 *__restrict__ waves, int32_t nw,
-                        int32_t parity) {
+                        int32_t parity, RouteCtl *ctl) {
   __shared__ S lds[Q * kFrameSide * kFrameSide];
+  if (!on_route(ctl, 0)) return;
   const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
   const int ct = (nt + 7) >> 3, cw = (((nw + 7) >> 3) + 3) & ~3;
   if (j < ct) {
@@ -430,6 +456,92 @@ void batch_sweep_kernel(const StepArgs *__restrict__ descs,
       A, to_global((const S *)(parity ? A.dst : A.src)),
       to_global((S *)(parity ? A.src : A.dst)), x0, x1, y0, y1, P.nt != 0,
       nullptr, 0, A.slots + (int)P.tiles() + k);
+}
+
+// ---------------------------------------------------------------------
+// the route of a state that the lattice was given
+
+// What a sweep of K steps over rows [y0, y1) of columns [x0, x1) of `src`
+// would count, from its temperatures: the rows off phi's lower plateau, at
+// every level.
+template <int Q, typename S>
+__device__ __forceinline__ void route_scan(const StepArgs &A, const S *src,
+                                           int x0, int x1, int y0, int y1,
+                                           int K, RouteCtl *ctl) {
+  const int lane = (int)(threadIdx.x & 63);
+  const int x = min(x0 + lane, x1 - 1);
+  int nband = 0, nliquid = 0;
+  for (int y = y0; y < y1; ++y) {
+    double T = 0.0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+      T += (double)src[j * A.plane + (int64_t)y * A.nx + x];
+    const double u = (T - A.tm) * A.inv_delta;
+    if (__builtin_amdgcn_ballot_w64(!(u < -20.0)) == 0) continue;
+    if (__builtin_amdgcn_ballot_w64(!(u < -20.0) && !(u > 20.0)) == 0)
+      ++nliquid;
+    else
+      ++nband;
+  }
+  if (lane == 0 && nband + nliquid > 0) {
+    // the rows around them too: level l has 2 (K - l) more
+    atomicMax(&ctl->chain, K * (nband + nliquid) + K * (K - 1));
+    atomicAdd(&ctl->units,
+              (unsigned long long)route_units(K * nband, K * nliquid));
+  }
+}
+
+template <int Q, typename S>
+__global__ __launch_bounds__(256) void route_scan_kernel(StepArgs A,
+                                                         SweepPlan P,
+                                                         RouteCtl *ctl) {
+  const int k = (int)blockIdx.x * 4 +
+                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (k >= P.waves()) return;
+  int x0, x1, y0, y1;
+  sweep_wave_of(P, k, 64 - 2 * P.k, x0, x1, y0, y1);
+  route_scan<Q, S>(A, (const S *)A.src, x0, x1, y0, y1, P.k, ctl);
+}
+
+// the same over a batch's waves
+template <int Q, typename S>
+__global__ __launch_bounds__(256) void batch_route_scan_kernel(
+    const StepArgs *__restrict__ descs, const SweepPlan *__restrict__ plans,
+    const int2 *__restrict__ waves, int32_t nw, int32_t parity,
+    RouteCtl *ctl) {
+  const int i = (int)blockIdx.x * 4 +
+                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (i >= nw) return;
+  const int2 e = waves[i];
+  const int inst = __builtin_amdgcn_readfirstlane(e.x);
+  const int k = __builtin_amdgcn_readfirstlane(e.y);
+  const StepArgs &A = descs[inst];
+  const SweepPlan &P = plans[inst];
+  int x0, x1, y0, y1;
+  sweep_wave_of(P, k, 64 - 2 * P.k, x0, x1, y0, y1);
+  route_scan<Q, S>(A, (const S *)(parity ? A.dst : A.src), x0, x1, y0, y1,
+                   P.k, ctl);
+}
+
+// groups of single steps after which a sweep is tried again (of up to 32 K
+// steps each: a try in a state that does not suit a sweep costs 1% or so)
+constexpr int kRouteRetry = 128;
+
+// The route of the next group, from what the last one's sweeps counted (scan:
+// from what the scan of a new state counted), after all of its launches.
+__global__ void route_decide_kernel(RouteCtl *ctl, int32_t scan,
+                                    int32_t chain_max,
+                                    unsigned long long units_max) {
+  RouteCtl c = *ctl;
+  if (scan || c.route == 0) {
+    c.route = c.chain > chain_max || c.units > units_max;
+    c.age = 0;
+  } else if (++c.age >= kRouteRetry) {
+    c.route = 0;
+  }
+  c.chain = 0;
+  c.units = 0;
+  *ctl = c;
 }
 
 }  // namespace

@@ -1,0 +1,166 @@
+"""Lattices whose sweeps are gated: where the front stands off the walls they
+go by single steps, decided on the device.  The states are those of single
+steps bit for bit on either route and across a change of it, and no position
+of the front is slower than single steps by more than the launches of the
+other route cost."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2505_13097_amd import Stefan, variant_names
+
+pytestmark = pytest.mark.gpu
+
+D, B, P = "dirichlet", "bounceback", "periodic"
+
+
+def _prob(nx, ny, q, storage, T0=None, side=B, **kw):
+    p = dict(tau=0.7, ste=0.2, delta=1.5 / (nx - 1))
+    p.update(kw)
+    return synth.Problem(dim=2, q=q, nx=nx, ny=ny, bc=(D, D, side, side),
+                         wall_T=(1.0, -0.5, 0.0, 0.0), tol=1e-12, max_it=40,
+                         storage=storage, scheme="irebm", T0=T0, **p)
+
+
+def _field(nx, ny, at, wiggle=0.0):
+    """hot to column `at`, solid beyond"""
+    x, y = np.arange(nx)[None, :], np.arange(ny)[:, None]
+    a = at * (1.0 + wiggle * np.sin(2 * np.pi * y / ny))
+    T = np.where(x < a, 1 - x / a, -0.5 * (1 - np.exp(-(x - a) / 16.0)))
+    T = T + np.random.default_rng(1).uniform(-1e-3, 1e-3, (ny, nx))
+    T[:, 0], T[:, -1] = 1.0, -0.5
+    return T
+
+
+def _us(g, state, steps=40):
+    best = 1e9
+    for _ in range(4):
+        g.set_state(state)
+        g.step(steps)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        g.step(steps)
+        e[1].record()
+        torch.cuda.synchronize()
+        best = min(best, e[0].elapsed_time(e[1]) / steps * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("nx,ny,q,storage", [
+    (900, 700, 9, "f64"), (1300, 1300, 9, "f32"), (2048, 2048, 5, "f32")])
+def test_no_front_position_is_slower_than_single_steps(nx, ny, q, storage):
+    """The bar: 1.25 times the better one-step tiling.  An empty launch per
+    step is 1 to 2 us of the 12 to 40 that a step takes."""
+    names = variant_names(q, storage)
+    one = [names.index("64x1/npt1"), names.index("128x4/npt2")]
+    slow = []
+    for at in (8, 40, 100, nx // 2, 2 * nx):
+        prob = _prob(nx, ny, q, storage, _field(nx, ny, at))
+        t = []
+        for v in [-1] + one:
+            g = Stefan(prob, variant=v)
+            t.append(_us(g, torch.from_numpy(g.state()).cuda()))
+            g.close()
+        print(f"{nx}x{ny} q{q} {storage} front at {at}: default {t[0]:.1f} "
+              f"us per step, single steps {t[1]:.1f}, {t[2]:.1f}", flush=True)
+        if t[0] > 1.25 * min(t[1:]):
+            slow.append((at, t))
+    assert not slow, slow
+
+
+def _equal(prob, steps, variants, newton=None):
+    names = variant_names(prob.q, prob.storage)
+    if newton:
+        prob = prob.with_(newton_mode=newton)
+    out = []
+    for v in [names.index("64x1/npt1")] + variants:
+        g = Stefan(prob, variant=v)
+        for n in steps:
+            g.step(n)
+        out.append((g.state(), g.stats()))
+        g.close()
+    b, sb = out[0]
+    for (a, sa), v in zip(out[1:], variants):
+        tag = (prob.q, prob.storage, v)
+        assert np.array_equal(a, b), tag
+        for k in ("steps", "max_newton_it", "nonconverged", "max_residual"):
+            assert sa[k] == sb[k], (tag, k)
+        bar = 1e-12 * (abs(sb["energy"]) + sum(steps) * 9 * prob.nodes)
+        for k in ("energy", "flux_in", "flux_out"):
+            assert abs(sa[k] - sb[k]) <= bar, (tag, k)
+
+
+# groups of every length: sweeps of two to four steps, the single steps left
+# over, whole groups in a row
+STEPS = (1, 2, 3, 4, 5, 7, 11, 13, 64, 70)
+
+
+@pytest.mark.parametrize("at", [8, 14, 100, 400, 1600])
+@pytest.mark.parametrize("q,storage", [(9, "f64"), (5, "f32")])
+def test_routes_equal_single_steps(q, storage, at):
+    """in the frame, leaving it, past it, half way, all liquid"""
+    nx, ny = (811, 747) if storage == "f64" else (1501, 1403)
+    prob = _prob(nx, ny, q, storage, _field(nx, ny, at, 0.1))
+    two = variant_names(q, storage).index("128x4/t2/r32/nt")
+    _equal(prob, STEPS, [-1, two])
+
+
+def test_a_sweep_is_tried_again():
+    """4200 steps: past the groups of single steps after which a state whose
+    front stands off the walls is swept again"""
+    prob = _prob(811, 747, 5, "f64", _field(811, 747, 100))
+    _equal(prob, (4200, 9), [-1])
+
+
+def test_set_state_decides_anew():
+    """states of either kind given to one handle in turn"""
+    nx, ny = 811, 747
+    names = variant_names(9, "f64")
+    probs = [_prob(nx, ny, 9, "f64", _field(nx, ny, at)) for at in (8, 300)]
+    states = []
+    for p in probs:
+        g = Stefan(p)
+        states.append(g.state())
+        g.close()
+    a = Stefan(probs[0])
+    b = Stefan(probs[0], variant=names.index("64x1/npt1"))
+    for k in (1, 0, 1, 1, 0):
+        for g in (a, b):
+            if k:
+                g.set_state(torch.from_numpy(states[k]).cuda())
+            else:
+                g.set_state(states[k])
+            g.step(21)
+        assert np.array_equal(a.state(), b.state()), k
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("at", [8, 100])
+@pytest.mark.parametrize("nx,ny", [(1301, 1203), (1501, 1403)])
+def test_captured_steps_replay(nx, ny, at):
+    """a graph of 40 steps, replayed with eager steps between; both routes'
+    launches on one stream, and on two"""
+    prob = _prob(nx, ny, 5, "f32", _field(nx, ny, at))
+    s = torch.cuda.Stream()
+    ref = Stefan(prob, variant=variant_names(5, "f32").index("64x1/npt1"))
+    with torch.cuda.stream(s):
+        a = Stefan(prob, stream=s)
+        a.step(40)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            a.step(40)
+        ref.step(40)
+        for k in range(4):
+            graph.replay()
+            ref.step(40)
+            s.synchronize()
+            assert np.array_equal(a.state(), ref.state()), k
+            a.step(6)
+            ref.step(6)
+            s.synchronize()
+    assert np.array_equal(a.state(), ref.state())
+    a.close()
+    ref.close()
