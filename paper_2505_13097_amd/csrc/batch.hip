@@ -14,7 +14,8 @@
 // captured in a hipGraph; the autotuner picks the tile variant and the
 // grid size.  Under a two-step variant a launch takes up to four steps by
 // sweeping waves, the walls and fronts of every instance as a frame of small
-// tiles in LDS (batch_sweep_kernel, sweep2d.hpp).  This unit is the host
+// tiles in LDS (batch_sweep_kernel, sweep2d.hpp); where too many of their
+// rows hold solves, single steps instead (RouteCtl).  This unit is the host
 // side; the kernels and their launches are in launch.hpp and
 // launch_sweep.hpp (instantiated by k_batch_<mode>.hip, k_bsweep_<mode>.hip).
 #include <hip/hip_runtime.h>
@@ -39,16 +40,26 @@ struct lbm_stefan_batch {
   int mode = kSafeguarded;  // node-update mode shared by the instances
   int device = 0, cus = 0;
   hipStream_t stream = nullptr, cap_stream = nullptr;
+  // sweeps of IREBM lattices: the single steps' launches on a stream of
+  // their own, forked from and joined back into the launching stream
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
   char *ws = nullptr;
   StepArgs *descs = nullptr;
   int2 *items = nullptr;
   StatSlot *slots = nullptr;
   SweepPlan *plans = nullptr;  // two-step variants
   BatchQuery *query = nullptr; // count + 1 entries
+  RouteCtl *route = nullptr;
+  int2 *singles = nullptr;     // the single steps' items beside sweeps
+  int64_t nsingles = 0;
+  int32_t chain_max = 0;       // what sweeps may hold (RouteCtl)
+  unsigned long long units_max = 0;
   int64_t nparts = 0;          // energy chunks of all instances
   double *profs = nullptr, *partials = nullptr, *small = nullptr;
   char *state[2] = {nullptr, nullptr};
   size_t state_bytes = 0;
+  int graph_flip = 0;          // does a graph end in the other buffer?
   int64_t nslots = 0, ntiles = 0;
   std::vector<size_t> off;          // instance offset in a state region
   std::vector<size_t> prof_off;     // instance offset in the profiles
@@ -64,8 +75,8 @@ struct lbm_stefan_batch {
 namespace {
 
 struct BLayout {
-  size_t descs, items, slots, plans, query, profs, partials, small, stateA, stateB,
-      total;
+  size_t descs, items, singles, slots, plans, query, route, profs, partials,
+      small, stateA, stateB, total;
   size_t state_bytes;
   int64_t max_items, max_parts, small_len;
   std::vector<size_t> off, prof_off;
@@ -74,6 +85,19 @@ struct BLayout {
 // work items (and statistics slots) of an instance under variant v
 int64_t batch_items(const Variant &v, const lbm_stefan_params &p) {
   return v.tb ? batch_plan(p, v).slots() : items_for(v, p.nx, p.ny);
+}
+
+// do batches of p sweep by groups (RouteCtl)?
+bool routed(const Variant &v, const lbm_stefan_params &p) {
+  return v.tb && p.scheme == LBM_SCHEME_IREBM;
+}
+// statistics slots of an instance under variant v
+int64_t batch_slots(const Variant &v, const lbm_stefan_params &p) {
+  int nv;
+  const int64_t n = batch_items(v, p);
+  if (!routed(v, p)) return n;
+  return std::max(n, items_for(variants(p.q, &nv)[kDefaultVariant2D], p.nx,
+                               p.ny));
 }
 
 // the variant a batch starts with (and -1 selects): sweeping waves, unless
@@ -138,7 +162,7 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   L.max_items = 0;
   for (int i = 0; i < nv; ++i) {
     int64_t t = 0;
-    for (int k = 0; k < count; ++k) t += batch_items(v[i], ps[k]);
+    for (int k = 0; k < count; ++k) t += batch_slots(v[i], ps[k]);
     L.max_items = std::max(L.max_items, t);
   }
   L.max_parts = 0;
@@ -163,12 +187,18 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   o += align256(count * sizeof(StepArgs));
   L.items = o;
   o += align256(L.max_items * sizeof(int2));
+  L.singles = o;
+  for (int k = 0; k < count && ps[0].q != 3; ++k)
+    o += items_for(v[kDefaultVariant2D], ps[k].nx, ps[k].ny) * sizeof(int2);
+  o = align256(o);
   L.slots = o;
   o += align256(L.max_items * sizeof(StatSlot));
   L.plans = o;
   o += align256(count * sizeof(SweepPlan));
   L.query = o;
   o += align256((count + 1) * sizeof(BatchQuery));
+  L.route = o;
+  o += align256(sizeof(RouteCtl));
   L.profs = o;
   o += align256(prof_total * 8);
   L.partials = o;
@@ -183,12 +213,36 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   return L;
 }
 
+void drop_side(lbm_stefan_batch_t *b) {
+  if (b->fork) (void)hipEventDestroy(b->fork);
+  if (b->join) (void)hipEventDestroy(b->join);
+  if (b->side) (void)hipStreamDestroy(b->side);
+  b->fork = b->join = nullptr;
+  b->side = nullptr;
+}
+
 void drop_graphs(lbm_stefan_batch_t *b) {
   for (int k = 0; k < 2; ++k)
     if (b->graph[k]) {
       (void)hipGraphExecDestroy(b->graph[k]);
       b->graph[k] = nullptr;
     }
+}
+
+// What the sweeps of up to K steps may hold before the batch goes by single
+// steps, which pass over the states (`bytes` in and out) at 4 TB/s.  A wave
+// takes 6 us a row with solves (route_lattice); all such rows together may
+// come to 0.65 of those steps' time (route_units; at 0.5 the first batch below
+// leaves the sweeps at column 64, at 0.9 it never does).  us per step, single steps / sweeps with the
+// front at column 8, 24, 64, 100, half way: 48 FP32 D2Q5 lattices of 64^2 to
+// 1024^2 272 / 121, 158, 213, 267, 310; 12 D2Q9 ones of 512^2 to 1024^2 150 /
+// 65, 89, 146, 171, 189; 400 D2Q5 ones of 64^2 to 256^2 188 to 231 / 178, 241,
+// 361, 343, 364; 24 FP64 D2Q9 ones of 64^2 to 1024^2 384 / 156, 167, 203, 288,
+// 376.
+void set_batch_route(lbm_stefan_batch_t *b, int K, double bytes) {
+  const double us = K * bytes / 4e6;
+  b->chain_max = (int32_t)std::min(us / 6.0, 1e6);
+  b->units_max = (unsigned long long)(0.65 * us * 1e3 / 0.45);
 }
 
 // descriptors and item table for the current variant; uploads both and
@@ -198,15 +252,17 @@ int build_schedule(lbm_stefan_batch_t *b) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
   const Variant &v = vt[b->variant];
+  const bool two = routed(v, b->ps[0]);   // (also laid out for single steps)
   std::vector<StepArgs> d(b->count);
   std::vector<SweepPlan> pl(b->count);
   std::vector<BatchQuery> qu(b->count + 1);
-  std::vector<int2> t, wv;
+  std::vector<int2> t, wv, sg;
   t.reserve(b->max_items);
   b->first_item.assign(b->count, 0);
   b->nitems_inst.assign(b->count, 0);
   int64_t sbase = 0;
   b->nparts = 0;
+  double bytes = 0.0;
   for (int k = 0; k < b->count; ++k) {
     const lbm_stefan_params &p = b->ps[k];
     double *prof[4];
@@ -217,8 +273,11 @@ int build_schedule(lbm_stefan_batch_t *b) {
     fill_args(p, prof, &d[k]);
     d[k].src = b->state[0] + b->off[k];
     d[k].dst = b->state[1] + b->off[k];
-    set_tiling(&d[k], v);
-    const int64_t n = batch_items(v, p);
+    set_tiling(&d[k], two ? vt[kDefaultVariant2D] : v);
+    d[k].ctl = two ? b->route : nullptr;
+    bytes += 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) * p.nx * p.ny;
+    for (int i = 0; two && i < d[k].nitems; ++i) sg.push_back(make_int2(k, i));
+    const int64_t n = batch_slots(v, p);
     d[k].slots = b->slots + sbase;
     b->first_item[k] = sbase;
     if (v.tb) {
@@ -241,10 +300,21 @@ int build_schedule(lbm_stefan_batch_t *b) {
   b->ntiles = (int64_t)t.size();
   t.insert(t.end(), wv.begin(), wv.end());
   b->nitems = (int64_t)t.size();
+  b->nsingles = (int64_t)sg.size();
+  set_batch_route(b, 4, bytes);
   BCHK(b, hipMemcpyAsync(b->descs, d.data(), d.size() * sizeof(StepArgs),
                          hipMemcpyHostToDevice, b->stream));
   BCHK(b, hipMemcpyAsync(b->items, t.data(), t.size() * sizeof(int2),
                          hipMemcpyHostToDevice, b->stream));
+  if (two)
+    BCHK(b, hipMemcpyAsync(b->singles, sg.data(), sg.size() * sizeof(int2),
+                           hipMemcpyHostToDevice, b->stream));
+  if (two && !b->side) {
+    BCHK(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
+    BCHK(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+    BCHK(b, hipEventCreateWithFlags(&b->join, hipEventDisableTiming));
+  }
+  BCHK(b, zero_async(b->route, sizeof(RouteCtl), b->stream));
   BCHK(b, hipMemcpyAsync(b->plans, pl.data(), pl.size() * sizeof(SweepPlan),
                          hipMemcpyHostToDevice, b->stream));
   BCHK(b, hipMemcpyAsync(b->query, qu.data(), qu.size() * sizeof(BatchQuery),
@@ -255,9 +325,14 @@ int build_schedule(lbm_stefan_batch_t *b) {
   return LBM_STEFAN_OK;
 }
 
+bool routed(const lbm_stefan_batch_t *b) {
+  int nv;
+  return routed(variants(b->q, &nv)[b->variant], b->ps[0]);
+}
+
 // one launch of k steps (at most steps_per_launch) from buffer `parity`
 hipError_t launch_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
-                        int parity, int k) {
+                        int parity, int k, RouteCtl *ctl = nullptr) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
   const Variant &v = vt[b->variant];
@@ -268,10 +343,27 @@ hipError_t launch_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
   L.cus = b->cus;
   L.blocks_per_cu = b->blocks_per_cu;
   L.parity = parity;
+  L.ctl = ctl;
   if (!v.tb) return batch_launch(b->mode, b->q, b->storage, L, v, stream);
   L.plans = b->plans;
   L.ntiles = b->ntiles;
   return batch_sweep(b->mode, b->q, b->storage, L, k, stream);
+}
+
+// a single step beside the sweeps
+hipError_t launch_single(const lbm_stefan_batch_t *b, hipStream_t stream,
+                         int parity, RouteCtl *ctl) {
+  int nv;
+  BatchLaunch L;
+  L.descs = b->descs;
+  L.items = b->singles;
+  L.nitems = b->nsingles;
+  L.cus = b->cus;
+  L.blocks_per_cu = 0;
+  L.parity = parity;
+  L.ctl = ctl;
+  return batch_launch(b->mode, b->q, b->storage, L,
+                      variants(b->q, &nv)[kDefaultVariant2D], stream);
 }
 
 // time steps one launch advances at most under the current variant
@@ -280,15 +372,73 @@ int steps_per_launch(const lbm_stefan_batch_t *b) {
   return variants(b->q, &nv)[b->variant].tb ? 4 : 1;
 }
 
-// launches of nsteps, and the steps of the first of them (as even as they
-// come)
-int64_t launches_of(const lbm_stefan_batch_t *b, int64_t nsteps) {
-  const int64_t k = steps_per_launch(b);
-  return (nsteps + k - 1) / k;
+// nsteps steps from buffer `parity`, which follows them; sweeps that are
+// routed go by groups, as in advance_routed
+hipError_t advance_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
+                         int *parity, int64_t nsteps) {
+  const int64_t K = steps_per_launch(b);
+  hipError_t e = hipSuccess;
+  if (!routed(b)) {
+    while (nsteps > 0 && e == hipSuccess) {
+      const int64_t m = (nsteps + K - 1) / K;
+      const int64_t k = (nsteps + m - 1) / m;
+      e = launch_batch(b, stream, *parity, (int)k);
+      *parity ^= 1;
+      nsteps -= k;
+    }
+    return e;
+  }
+  while (nsteps > 0 && e == hipSuccess) {
+    const int64_t n = nsteps >= 32 * K ? 16 * K : nsteps;
+    int64_t m = (n + K - 1) / K;
+    m += (m ^ n) & 1;
+    if (n / m < 2) {
+      e = launch_single(b, stream, *parity, nullptr);
+      *parity ^= 1;
+      nsteps--;
+      continue;
+    }
+    e = hipEventRecord(b->fork, stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->fork, 0);
+    int p = *parity, c = *parity;
+    for (int64_t i = 0, left = n; i < m && e == hipSuccess; ++i, p ^= 1) {
+      const int64_t k = (left + m - i - 1) / (m - i);
+      e = launch_batch(b, stream, p, (int)k, b->route);
+      for (int64_t j = 0; j < k && e == hipSuccess; ++j, c ^= 1)
+        e = launch_single(b, b->side, c, b->route);
+      left -= k;
+    }
+    if (e == hipSuccess) e = hipEventRecord(b->join, b->side);
+    if (e == hipSuccess) e = hipStreamWaitEvent(stream, b->join, 0);
+    if (e != hipSuccess) break;
+    // (units add up over the group's launches)
+    route_decide_kernel<<<1, 1, 0, stream>>>(b->route, 0, b->chain_max,
+                                             b->units_max * m);
+    e = hipGetLastError();
+    *parity ^= n & 1;
+    nsteps -= n;
+  }
+  return e;
 }
-int first_launch(const lbm_stefan_batch_t *b, int64_t nsteps) {
-  const int64_t n = launches_of(b, nsteps);
-  return (int)((nsteps + n - 1) / n);
+
+// the route of the batch's current states
+hipError_t scan_route(lbm_stefan_batch_t *b) {
+  if (!routed(b)) return hipSuccess;
+  const int64_t nw = b->nitems - b->ntiles;
+  hipError_t e = hipSuccess;
+  if (nw > 0)
+    e = dispatch_qs(b->q, b->storage, [&](auto qt, auto tt) {
+      QS_TYPES(qt, tt);
+      batch_route_scan_kernel<Q, S><<<(unsigned)((nw + 3) / 4), 256, 0,
+                                      b->stream>>>(
+          b->descs, b->plans, b->items + b->ntiles, (int32_t)nw, b->cur,
+          b->route);
+      return hipGetLastError();
+    });
+  if (e != hipSuccess) return e;
+  route_decide_kernel<<<1, 1, 0, b->stream>>>(b->route, 1, b->chain_max,
+                                              b->units_max);
+  return hipGetLastError();
 }
 
 // graph of the launches of graph_steps steps starting at parity `par`
@@ -297,13 +447,9 @@ int ensure_graph(lbm_stefan_batch_t *b, int par) {
   if (!b->cap_stream)
     BCHK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   BCHK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t le = hipSuccess;
   int p = par;
-  for (int64_t left = b->graph_steps; left > 0 && le == hipSuccess; p ^= 1) {
-    const int k = first_launch(b, left);
-    le = launch_batch(b, b->cap_stream, p, k);
-    left -= k;
-  }
+  const hipError_t le = advance_batch(b, b->cap_stream, &p, b->graph_steps);
+  b->graph_flip = p ^ par;
   hipGraph_t g = nullptr;
   const hipError_t ee = hipStreamEndCapture(b->cap_stream, &g);
   if (le != hipSuccess || ee != hipSuccess) {
@@ -358,6 +504,7 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
   auto bail = [&](int code) {
     set_global_error(b->err);
     drop_graphs(b);
+    drop_side(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     delete b;
     return code;
@@ -379,6 +526,8 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
   b->items = (int2 *)(ws + L.items);
   b->slots = (StatSlot *)(ws + L.slots);
   b->nslots = L.max_items;
+  b->singles = (int2 *)(ws + L.singles);
+  b->route = (RouteCtl *)(ws + L.route);
   b->plans = (SweepPlan *)(ws + L.plans);
   b->query = (BatchQuery *)(ws + L.query);
   b->profs = (double *)(ws + L.profs);
@@ -428,7 +577,8 @@ int lbm_stefan_batch_init(const lbm_stefan_params *ps, int32_t count,
         hipSuccess)
       return bail(bfail(b, LBM_STEFAN_EDEVICE, "init kernel failed"));
   }
-  if (hipStreamSynchronize(b->stream) != hipSuccess)
+  if (scan_route(b) != hipSuccess ||
+      hipStreamSynchronize(b->stream) != hipSuccess)
     return bail(bfail(b, LBM_STEFAN_EDEVICE, "init failed"));
   *out = b;
   return LBM_STEFAN_OK;
@@ -457,7 +607,9 @@ int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,
   drop_graphs(b);
   if (nvar != b->variant) {
     b->variant = nvar;
-    return build_schedule(b);
+    const int rc = build_schedule(b);
+    if (rc != LBM_STEFAN_OK) return rc;
+    BCHK(b, scan_route(b));
   }
   return LBM_STEFAN_OK;
 }
@@ -474,16 +626,11 @@ int lbm_stefan_batch_step(lbm_stefan_batch_t *b, int64_t nsteps) {
       BCHK(b, hipGraphLaunch(b->graph[b->cur], b->stream));
       left -= b->graph_steps;
       b->steps += b->graph_steps;
-      b->cur ^= (int)(launches_of(b, b->graph_steps) & 1);
+      b->cur ^= b->graph_flip;
     }
   }
-  while (left > 0) {
-    const int k = first_launch(b, left);
-    BCHK(b, launch_batch(b, b->stream, b->cur, k));
-    b->cur ^= 1;
-    b->steps += k;
-    left -= k;
-  }
+  BCHK(b, advance_batch(b, b->stream, &b->cur, left));
+  b->steps += left;
   return LBM_STEFAN_OK;
 }
 
@@ -629,6 +776,7 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
       b->variant = v;
       rc = build_schedule(b);
     }
+    if (rc == LBM_STEFAN_OK) err = scan_route(b);
     // a sweeping launch covers four steps; the persistent grid is for
     // one-step variants only
     const int spl = steps_per_launch(b);
@@ -637,11 +785,10 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
       if (rc != LBM_STEFAN_OK || err != hipSuccess) break;
       if (vt[v].tb && bpc > 0) break;
       b->blocks_per_cu = bpc;
-      for (int s = 0; s < launches + 2 && err == hipSuccess; ++s) {
-        if (s == 2) err = hipEventRecord(e0, b->stream);
-        if (err == hipSuccess) err = launch_batch(b, b->stream, b->cur, spl);
-        b->cur ^= 1;
-      }
+      err = advance_batch(b, b->stream, &b->cur, 2 * spl);
+      if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
+      if (err == hipSuccess)
+        err = advance_batch(b, b->stream, &b->cur, (int64_t)launches * spl);
       if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
       if (err == hipSuccess) err = hipEventSynchronize(e1);
       float ms = 0.0f;
@@ -670,6 +817,7 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
     b->variant = best_v;
     rc = build_schedule(b);
     if (rc) return rc;
+    BCHK(b, scan_route(b));
   } else {
     BCHK(b, zero_async(b->slots, b->nslots * sizeof(StatSlot), b->stream));
   }
@@ -685,7 +833,9 @@ int lbm_stefan_batch_destroy(lbm_stefan_batch_t *b) {
   if (!b) return LBM_STEFAN_OK;
   DeviceGuard g(b->device);
   hipError_t e = hipStreamSynchronize(b->stream);
+  if (e == hipSuccess && b->side) e = hipStreamSynchronize(b->side);
   drop_graphs(b);
+  drop_side(b);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   delete b;
   if (e != hipSuccess) return bfail(nullptr, LBM_STEFAN_EDEVICE, hipGetErrorString(e));

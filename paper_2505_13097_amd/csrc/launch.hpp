@@ -41,7 +41,8 @@ __device__ __forceinline__ void batch_item(const StepArgs *__restrict__ descs,
 template <int Q, typename S, int NPT, int MODE, bool NT>
 __global__ __launch_bounds__(256) void batch_step_kernel(
     const StepArgs *__restrict__ descs, const int2 *__restrict__ items,
-    int32_t nitems, int32_t parity, int32_t reverse) {
+    int32_t nitems, int32_t parity, int32_t reverse, RouteCtl *ctl) {
+  if (!on_route(ctl, 1)) return;
   const int chunk = (nitems + 7) >> 3;
   const int b = (int)blockIdx.x;
   if ((b & 7) * chunk + (b >> 3) >= nitems) return;
@@ -157,7 +158,8 @@ hipError_t launch_batch_t(const BatchLaunch &b, const Variant &v,
           <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev); \
     else                                                                   \
       batch_step_kernel<Q, S, NPT, MODE, NTS>                              \
-          <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev); \
+          <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev,  \
+                                       b.ctl);                               \
   } while (0)
 #define BLAUNCH_NPT(NTS)                  \
   do {                                    \

@@ -61,7 +61,7 @@ hipError_t launch_batch_sweep_t(const BatchLaunch &b, int k,
 #define BSWEEP(K)                                                         \
   batch_sweep_kernel<Q, S, MODE, K><<<grid, 256, 0, stream>>>(            \
       b.descs, b.plans, b.items, (int32_t)b.ntiles, b.items + b.ntiles,   \
-      (int32_t)(b.nitems - b.ntiles), b.parity, nullptr)
+      (int32_t)(b.nitems - b.ntiles), b.parity, b.ctl)
     if (k == 4) BSWEEP(4);
     else if (k == 3) BSWEEP(3);
     else if (k == 2) BSWEEP(2);

@@ -150,6 +150,9 @@ struct BatchLaunch {
   // first (ntiles of them), then the waves
   const SweepPlan *plans = nullptr;
   int64_t ntiles = 0;
+  // the launch runs on one route only (sweeps, or single steps one block per
+  // item); null: always
+  RouteCtl *ctl = nullptr;
 };
 
 template <int MODE>

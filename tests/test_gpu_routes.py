@@ -164,3 +164,74 @@ def test_captured_steps_replay(nx, ny, at):
     assert np.array_equal(a.state(), ref.state())
     a.close()
     ref.close()
+
+
+# ------------------------------------------------------------- the batched form
+
+def _batch(sizes, q, storage, at):
+    return [_prob(nx, ny, q, storage, _field(nx, ny, at if at > 1 else at * nx),
+                  P if q == 5 else B) for nx, ny in sizes]
+
+
+def _batch_us(probs, variant, steps=40):
+    from paper_2505_13097_amd import StefanBatch
+    b = StefanBatch(probs)
+    b.set_schedule(variant)
+    b.step(steps)
+    best = 1e9
+    for _ in range(3):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        b.step(steps)
+        e[1].record()
+        torch.cuda.synchronize()
+        best = min(best, e[0].elapsed_time(e[1]) / steps * 1e3)
+    b.close()
+    return best
+
+
+@pytest.mark.parametrize("sizes,q", [
+    ([(160, 160), (96, 224), (256, 128), (200, 210)] * 80, 5),
+    ([(512, 700), (1024, 600), (800, 900)] * 4, 9)], ids=["small", "large"])
+def test_no_front_position_slows_a_batch(sizes, q):
+    """The bar of test_no_front_position_is_slower_than_single_steps"""
+    names = variant_names(q, "f32")
+    slow = []
+    for at in (8, 30, 100, 0.5, 3.0):
+        probs = _batch(sizes, q, "f32", at)
+        t = [_batch_us(probs, v) for v in (-1, names.index("128x4/npt2"))]
+        print(f"{len(sizes)} lattices q{q}, front at {at}: default {t[0]:.1f} "
+              f"us per step, single steps {t[1]:.1f}", flush=True)
+        if t[0] > 1.25 * t[1]:
+            slow.append((at, t))
+    assert not slow, slow
+
+
+@pytest.mark.parametrize("at", [8, 30, 0.5])
+@pytest.mark.parametrize("graph", [0, 14, 40])
+def test_batch_routes_equal_single_steps(graph, at):
+    """both routes, eager and in graphs replayed with eager steps between"""
+    from paper_2505_13097_amd import StefanBatch
+    for q, storage in ((5, "f32"), (9, "f64")):
+        names = variant_names(q, storage)
+        probs = _batch([(64, 64), (300, 300), (3, 9), (650, 511), (900, 120)],
+                       q, storage, at)
+        a, ref = StefanBatch(probs), StefanBatch(probs)
+        a.set_schedule(names.index("128x2/t2s/r96/nt"), 0, graph)
+        ref.set_schedule(names.index("64x1/npt1"))
+        done = 0
+        for n in (1, 2, 3, 5, 7, 130, 64, 45):
+            a.step(n)
+            ref.step(n)
+            done += n
+            for k in range(len(probs)):
+                assert np.array_equal(a.temperature(k), ref.temperature(k)), \
+                    (q, storage, n, k)
+        for k, (sa, sb) in enumerate(zip(a.stats(), ref.stats())):
+            for f in ("max_newton_it", "nonconverged", "max_residual"):
+                assert sa[f] == sb[f], (q, storage, k, f)
+            bar = 1e-12 * (abs(sb["energy"]) + done * 9 * probs[k].nodes)
+            for f in ("energy", "flux_in", "flux_out"):
+                assert abs(sa[f] - sb[f]) <= bar, (q, storage, k, f)
+        a.close()
+        ref.close()
