@@ -12,7 +12,7 @@
 // l^(k) = clamp(Ste (H^(k) - T_m), 0, 1).  The source term reaches across
 // nodes; but Omega0 and l do not change during the inner loop, so a block
 // holds the pulled Omega0 of a tile and its halo in registers and takes
-// kTileIt iterations per launch on it, l - l^(k-1) in LDS
+// several iterations per launch on it (at most kTileIt), l - l^(k-1) in LDS
 // (ilfbm_tile_kernel).  Every iteration with a change above tol sets a flag
 // of its own; a launch whose predecessor has an unset one returns.  The host
 // reads the flags after every few launches, and the launch that holds the
@@ -49,12 +49,13 @@ struct IlfCtrl {
   int32_t open[kSets][kTileIt];
 };
 
-// tiles of the lattice: own nodes per tile along x and y at most
-constexpr int tile_x(int q) {
-  return q == 3 ? kTileThreads - 2 * kTileIt : kTileRow - 2 * kTileIt;
+// tiles of a launch of kk iterations: own nodes per tile along x and y at
+// most (the rest of a block's threads hold the halo)
+constexpr int tile_x(int q, int kk) {
+  return q == 3 ? kTileThreads - 2 * kk : kTileRow - 2 * kk;
 }
-constexpr int tile_y(int q) {
-  return q == 3 ? 1 : kTileThreads / kTileRow - 2 * kTileIt;
+constexpr int tile_y(int q, int kk) {
+  return q == 3 ? 1 : kTileThreads / kTileRow - 2 * kk;
 }
 
 struct IlfArgs {
@@ -141,7 +142,8 @@ __device__ __forceinline__ void ilfbm_node(const IlfArgs &G, int64_t k,
 // -> G.lout.  The region a block holds shrinks by one node a side and
 // iteration, as in tile_body; nodes of a halo are computed by their
 // neighbours as well, by the same code from the same values.  open: this
-// launch's flags; prev: those of the launch before (null for the first);
+// launch's flags; prev: those of the launch before (nprev of them, 0 for the
+// first launch);
 // clear: a set that a later launch will use.  FINAL: the last iteration also
 // writes the next state to G.A.dst and per tile (pend) the largest change
 // and the boundary fluxes.
@@ -154,19 +156,19 @@ __device__ __forceinline__ void ilfbm_node(const IlfArgs &G, int64_t k,
 template <int Q, typename S, bool FINAL>
 __global__ __launch_bounds__(kTileThreads) void ilfbm_tile_kernel(
     IlfArgs G, int32_t ntx, int32_t nty, int32_t kk, const int32_t *prev,
-    int32_t *open, int32_t *clear, double tol, double *pend) {
+    int32_t nprev, int32_t *open, int32_t *clear, double tol, double *pend) {
   constexpr int RX = Q == 3 ? kTileThreads : kTileRow;
   __shared__ double lds[2][kTileThreads];
   __shared__ int32_t s_open[kTileIt];
   const int t = (int)threadIdx.x;
-  if (!FINAL && prev) {
+  if (!FINAL) {
     int all = 1;
-    for (int m = 0; m < kTileIt; ++m) all &= prev[m];
+    for (int m = 0; m < nprev; ++m) all &= prev[m];
     if (!all) return;                // an earlier iteration converged
   }
   const int tiles = ntx * nty, per_xcd = (tiles + 7) >> 3;
   const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (!FINAL && blockIdx.x == 0 && t < kTileIt) clear[t] = 0;
+  if (blockIdx.x == 0 && t < kTileIt) clear[t] = 0;
   if (tile >= tiles) return;
   const StepArgs &A = G.A;
   const int nx = A.nx, ny = A.ny;
@@ -279,12 +281,11 @@ __global__ __launch_bounds__(kTileThreads) void ilfbm_tile_kernel(
         }
       }
     }
-    if (!FINAL && __any(big) && (t & 63) == 0) s_open[m - 1] = 1;
+    if (__any(big) && (t & 63) == 0) s_open[m - 1] = 1;
   }
   __syncthreads();
-  if constexpr (!FINAL) {
-    if (t < kk && s_open[t]) open[t] = 1;
-  } else {
+  if (t < kk && s_open[t]) open[t] = 1;
+  if constexpr (FINAL) {
     // (lds is free: the barrier above)
     double *sh = &lds[0][0];
     dl = wave_max(dl);
@@ -450,8 +451,8 @@ __global__ void ilfbm_reset_kernel(IlfCtrl *ctrl) {
 }
 
 int64_t tiles_of(int64_t n, int side) { return (n + side - 1) / side; }
-int64_t iter_tiles(const lbm_stefan_params *p) {
-  return tiles_of(p->nx, tile_x(p->q)) * tiles_of(p->ny, tile_y(p->q));
+int64_t iter_tiles(const lbm_stefan_params *p, int kk = kTileIt) {
+  return tiles_of(p->nx, tile_x(p->q, kk)) * tiles_of(p->ny, tile_y(p->q, kk));
 }
 
 }  // namespace
@@ -534,10 +535,6 @@ hipError_t irebm::ilfbm_advance(lbm_stefan_t *h, int64_t nsteps) {
   const lbm_stefan_params &p = h->p;
   if (p.q == 3 && p.nx <= kResidentNodes)
     return ilfbm_advance_resident(h, nsteps);
-  const int32_t ntx = (int32_t)tiles_of(p.nx, tile_x(p.q));
-  const int32_t nty = (int32_t)tiles_of(p.ny, tile_y(p.q));
-  const int64_t tiles = (int64_t)ntx * nty;
-  const unsigned grid = (unsigned)(8 * ((tiles + 7) / 8));
   IlfCtrl *ctrl = (IlfCtrl *)h->ctrl;
   IlfArgs G;
   fill_step_args(h, &G.A);
@@ -561,47 +558,65 @@ hipError_t irebm::ilfbm_advance(lbm_stefan_t *h, int64_t nsteps) {
     G.A.src = h->buf[h->cur];
     G.A.dst = h->buf[h->cur ^ 1];
     G.l = h->lf;
-    // launch j: iterations j kTileIt + 1 to (j + 1) kTileIt, at most cap
+    // Launch j: iterations from(j) + 1 to from(j + 1), at most cap; the first
+    // as many as the last step took, if those are few: on wider tiles, and as
+    // the step's end if its guess holds (us per step, 8 always / so: 1601^2
+    // D2Q9 FP64 that converges in 3 907 / 210, at a cap of 2 604 / 182, 501^2
+    // 106 / 56; a launch per iteration 467, 306, 63).
+    const int k0 = h->ilf_last > 0 && h->ilf_last < kTileIt ? h->ilf_last
+                                                            : kTileIt;
+    auto from = [&](int64_t j) -> int64_t {
+      return j == 0 ? 0 : std::min<int64_t>(cap, k0 + (j - 1) * kTileIt);
+    };
     auto launch = [&](int64_t j, int kk, bool final) {
+      const int32_t ntx = (int32_t)tiles_of(p.nx, tile_x(p.q, kk));
+      const int32_t nty = (int32_t)tiles_of(p.ny, tile_y(p.q, kk));
+      const unsigned grid = (unsigned)(8 * (((int64_t)ntx * nty + 7) / 8));
       G.lprev = j == 0 ? h->lf : h->lscr[(j - 1) & 1];
       G.lout = h->lscr[j & 1];
       int32_t *open = ctrl->open[j % kSets];
-      const int32_t *prev = j == 0 ? nullptr : ctrl->open[(j - 1) % kSets];
+      const int32_t *prev = ctrl->open[(j + kSets - 1) % kSets];
+      const int32_t np = (int32_t)(j == 0 ? 0 : from(j) - from(j - 1));
       int32_t *clear = ctrl->open[(j + kBurst) % kSets];
       return dispatch_qs(p.q, p.storage, [&](auto qt, auto tt) {
         QS_TYPES(qt, tt);
         if (final)
           ilfbm_tile_kernel<Q, S, true><<<grid, kTileThreads, 0, h->stream>>>(
-              G, ntx, nty, kk, prev, open, clear, p.newton_tol, h->pend);
+              G, ntx, nty, kk, prev, np, open, clear, p.newton_tol, h->pend);
         else
           ilfbm_tile_kernel<Q, S, false><<<grid, kTileThreads, 0, h->stream>>>(
-              G, ntx, nty, kk, prev, open, clear, p.newton_tol, h->pend);
+              G, ntx, nty, kk, prev, np, open, clear, p.newton_tol, h->pend);
         return hipGetLastError();
       });
     };
     ilfbm_reset_kernel<<<1, kSets * kTileIt, 0, h->stream>>>(ctrl);
     hipError_t e = hipGetLastError();
-    int64_t kf = 0;                  // the last iteration, once known
+    int64_t kf = 0, jf = 0;          // the last iteration and its launch
     bool done = false;
     for (int64_t j = 0; e == hipSuccess && !done && kf < cap;) {
       const int64_t j0 = j;
-      for (; j < j0 + kBurst && j * kTileIt < cap && e == hipSuccess; ++j)
-        e = launch(j, (int)std::min<int64_t>(kTileIt, cap - j * kTileIt),
-                   false);
+      // (one launch where the last step's iterations fit into it)
+      const int64_t burst = j == 0 && k0 < kTileIt ? 1 : kBurst;
+      for (; j < j0 + burst && from(j) < cap && e == hipSuccess; ++j)
+        e = launch(j, (int)(from(j + 1) - from(j)), burst == 1);
       if (e == hipSuccess) e = read();
       if (e != hipSuccess) break;
       take();
-      for (int64_t k = j0 * kTileIt; k < cap && k < j * kTileIt && !done; ++k) {
-        kf = k + 1;
-        done = !hc.open[k / kTileIt % kSets][k % kTileIt];
-      }
+      for (int64_t i = j0; i < j && !done; ++i)
+        for (int64_t k = from(i); k < from(i + 1) && !done; ++k) {
+          kf = k + 1;
+          jf = i;
+          done = !hc.open[i % kSets][k - from(i)];
+        }
     }
     if (e != hipSuccess) return e;
-    // the launch that holds it again, up to it
-    const int64_t jf = (kf - 1) / kTileIt;
-    e = launch(jf, (int)(kf - jf * kTileIt), true);
+    // the launch that holds it again, up to it (unless that was the guess)
+    const int kk = (int)(kf - from(jf));
+    if (k0 == kTileIt || jf > 0 || kk < from(1)) e = launch(jf, kk, true);
     if (e != hipSuccess) return e;
-    ilfbm_sum_kernel<<<1, 256, 0, h->stream>>>(h->pend, tiles, ctrl);
+    h->ilf_last = (int32_t)kf;
+    ilfbm_sum_kernel<<<1, 256, 0, h->stream>>>(h->pend, iter_tiles(&p, kk),
+                                               ctrl);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     std::swap(h->lf, h->lscr[jf & 1]);

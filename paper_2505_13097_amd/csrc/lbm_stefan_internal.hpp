@@ -74,6 +74,7 @@ struct lbm_stefan {
   double *lf = nullptr, *lscr[2] = {nullptr, nullptr}, *pend = nullptr;
   void *ctrl = nullptr;
   int32_t ilf_max_it = 0;
+  int32_t ilf_last = 0;          // iterations of the last step
   int64_t ilf_nonconv = 0;
   double ilf_max_res = 0.0, ilf_fin = 0.0, ilf_fout = 0.0;
   std::string err;
