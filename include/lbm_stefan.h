@@ -290,7 +290,9 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    fewer, and up to four steps per launch by waves sweeping m rows (at most
    32 in the batched form) on wider ones and in the batched form; a single
    trailing step then uses the default variant, and a lattice with a Neumann
-   wall runs the default variant; q = 3 also "resident2048": D1Q3 lattices of
+   wall runs the default variant; q = 5 and 9 also "0x0/npt1", the library's
+   own choice for the lattice (what params.variant = -1 takes); q = 3 also
+   "resident2048": D1Q3 lattices of
    at most 2048 nodes with no Neumann wall run many steps per launch in one workgroup, both
    states in LDS (others run the default variant; the batched form rejects
    it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z

@@ -599,8 +599,9 @@ int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,
   if (graph_steps < 0 || graph_steps % 2 || graph_steps > 100000)
     return bfail(b, LBM_STEFAN_EINVAL,
                  "graph_steps must be even and in 0..100000");
-  const int nvar =
-      variant < 0 ? default_variant(b->ps.data(), b->count) : variant;
+  const int nvar = variant < 0 || vt[variant].lib
+                       ? default_variant(b->ps.data(), b->count)
+                       : variant;
   DeviceGuard g(b->device);
   b->blocks_per_cu = blocks_per_cu;
   b->graph_steps = graph_steps;
@@ -771,7 +772,8 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
   int rc = LBM_STEFAN_OK;
   hipError_t err = hipSuccess;
   for (int v = 0; v < nv && rc == LBM_STEFAN_OK && err == hipSuccess; ++v) {
-    if (vt[v].res) continue;  // single lattices only
+    // (single lattices only; one of the others)
+    if (vt[v].res || vt[v].lib) continue;
     if (v != b->variant) {
       b->variant = v;
       rc = build_schedule(b);

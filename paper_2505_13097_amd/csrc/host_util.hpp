@@ -25,9 +25,11 @@ namespace irebm {
 // four steps by sweeping waves instead (sweep_kernel, segments of `rows`
 // rows).  res: D1Q3 lattices of at most kResident1D nodes run many steps
 // per launch in one workgroup (resident1d_kernel); others take the default
-// one-step tiling.  tb = 2: as tb = 1, more segment lengths.
+// one-step tiling.  tb = 2: as tb = 1, more segment lengths.  lib: what the
+// library takes by itself (params.variant = -1): several steps per launch or
+// a one-step tiling, by lattice.
 struct Variant {
-  int bx, by, npt, nt, rev, rows, tb, res;
+  int bx, by, npt, nt, rev, rows, tb, res, lib;
 };
 
 inline const Variant *variants(int q, int *n) {
@@ -50,7 +52,8 @@ inline const Variant *variants(int q, int *n) {
       {128, 2, 1, 1, 0, 16, 2},  {128, 2, 1, 1, 0, 24, 2},
       {128, 2, 1, 1, 0, 32, 2},  {128, 2, 1, 1, 0, 64, 2},
       {128, 4, 1, 1, 0, 32, 2},  {128, 2, 1, 1, 0, 96, 2},
-      {128, 2, 1, 1, 0, 128, 2}};
+      {128, 2, 1, 1, 0, 128, 2},
+      {64, 4, 2, 0, 0, 1, 0, 0, 1}};
   if (q == 3) {
     *n = (int)(sizeof(v1) / sizeof(Variant));
     return v1;
@@ -61,6 +64,7 @@ inline const Variant *variants(int q, int *n) {
 constexpr int kDefaultVariant1D = 0;
 constexpr int kResidentVariant1D = 4;
 constexpr int kDefaultVariant2D = 3;
+constexpr int kLibraryVariant2D = 37;
 // 128x2/t2s/r32/nt: the batched form's default (sweeping waves)
 constexpr int kSweepVariant2D = 32;
 

@@ -527,7 +527,8 @@ hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
   // so does a step under the resident variant
   // (beside sweeps the tiling of fewest blocks: they cost as empty launches)
   const Variant &v = vt[ctl                  ? kDefaultVariant2D
-                        : vt[h->variant].tb  ? default_2d(h->p)
+                        : vt[h->variant].tb || vt[h->variant].lib
+                            ? default_2d(h->p)
                         : vt[h->variant].res ? kDefaultVariant1D
                                              : h->variant];
   // a Dirichlet x = 0 wall is where the workloads heat: its tiles first
@@ -540,12 +541,13 @@ void irebm::plan_steps(lbm_stefan_t *h) {
   h->plan = TilePlan();
   h->sweep = SweepPlan();
   if (h->p.dim != 2) return;
-  if (h->by_default) {
+  int nv;
+  const Variant &v = variants(h->p.q, &nv)[h->variant];
+  if (v.lib) {
     h->sweep = sweep_default(h->p);
     if (h->sweep.k == 0) h->plan = plan_for(h->p);
   } else {
-    int nv;
-    h->sweep = sweep_variant(h->p, variants(h->p.q, &nv)[h->variant]);
+    h->sweep = sweep_variant(h->p, v);
   }
 }
 
@@ -686,8 +688,7 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
                                   : (p->q == 3 ? (resident_ok(*p)
                                                       ? kResidentVariant1D
                                                       : kDefaultVariant1D)
-                                               : default_2d(*p)));
-  h->by_default = p->variant < 0;
+                                               : kLibraryVariant2D));
   plan_steps(h);
   h->stream = (hipStream_t)stream;
   if (hipGetDevice(&h->device) != hipSuccess) {
@@ -883,7 +884,9 @@ const char *lbm_stefan_variant_name(int32_t q, int32_t storage,
   const Variant &w = v[variant];
   char rows[16] = "";
   if (w.rows > 1) std::snprintf(rows, sizeof(rows), "/r%d", w.rows);
-  if (w.res)
+  if (w.lib)
+    std::snprintf(buf, sizeof(buf), "0x0/npt1");
+  else if (w.res)
     std::snprintf(buf, sizeof(buf), "resident%d", (int)kResident1D);
   else if (w.tb)
     std::snprintf(buf, sizeof(buf), "%dx%d/t2%s%s%s", w.bx, w.by,
@@ -903,7 +906,6 @@ int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant) {
     return fail(h, LBM_STEFAN_EINVAL, "unknown kernel variant");
   DeviceGuard g(h->device);
   h->variant = variant;
-  h->by_default = false;
   plan_steps(h);
   HIPCHK(h, scan_route(h));
   // the tile -> slot mapping changes with the tile shape
@@ -943,15 +945,9 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     return fail(h, LBM_STEFAN_EDEVICE, "hipEventCreate failed");
   }
   int best = h->variant;
-  bool best_default = false;
   float best_ms = 0.0f;
   hipError_t err = hipSuccess;
-  // the library default's launches of several steps are one more trial,
-  // after the variants, under its one-step variant's index
-  const int trials = nv + (p.dim == 2 ? 1 : 0);
-  for (int trial = 0; trial < trials && err == hipSuccess; ++trial) {
-    const int v = trial < nv ? trial : default_2d(p);
-    h->by_default = trial == nv;
+  for (int v = 0; v < nv && err == hipSuccess; ++v) {
     // a Neumann lattice runs two-step variants as the default one, and a
     // lattice the resident kernel does not take runs that variant so too
     if (vt && vt[v].tb && has_neumann(p)) continue;
@@ -959,8 +955,8 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     if (vt && vt[v].tb == 2) continue;  // single lattices: same as tb = 1
     h->variant = v;
     plan_steps(h);
-    // a default that launches single steps is its variant's trial
-    if (trial == nv && steps_per_launch(h) == 1) continue;
+    // (the library's, where it takes single steps, is a tiling tried before)
+    if (vt && vt[v].lib && h->plan.k == 0 && h->sweep.k == 0) continue;
     // two untimed steps, then the timed trial (an even count, so that a
     // two-step variant runs its own kernel only)
     const int64_t n = steps + (steps & 1);
@@ -975,10 +971,9 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
     float ms = 0.0f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
     ms /= (float)n;
-    if (err == hipSuccess && (trial == 0 || ms < best_ms)) {
+    if (err == hipSuccess && (v == 0 || ms < best_ms)) {
       best_ms = ms;
       best = v;
-      best_default = h->by_default;
     }
     // restore the saved state for the next trial
     h->cur = cur0;
@@ -990,7 +985,6 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   (void)hipEventDestroy(e1);
   h->cur = cur0;
   h->variant = best;
-  h->by_default = best_default;
   plan_steps(h);
   if (err != hipSuccess)
     return fail(h, LBM_STEFAN_EDEVICE,

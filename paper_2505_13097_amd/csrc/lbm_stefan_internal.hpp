@@ -57,11 +57,10 @@ struct lbm_stefan {
   double *small = nullptr;
   char *adj = nullptr;
   int variant = 0;
-  // several steps per launch: the library default (params.variant = -1)
-  // takes tiles in LDS on small 2D lattices (plan.k > 0) and sweeps on large
-  // ones, the two-step variants sweep where the lattice is large enough
-  // (sweep.k > 0, set with the variant)
-  bool by_default = false;
+  // several steps per launch: the library's variant takes tiles in LDS on
+  // small 2D lattices (plan.k > 0) and sweeps on large ones, the two-step
+  // variants sweep where the lattice is large enough (sweep.k > 0, set with
+  // the variant)
   irebm::TilePlan plan;
   irebm::SweepPlan sweep;
   irebm::RouteCtl *route = nullptr;

@@ -1,0 +1,80 @@
+"""The variant that the autotuner names is the one that it timed."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2505_13097_amd import Stefan, variant_names
+
+pytestmark = pytest.mark.gpu
+
+D, P = "dirichlet", "periodic"
+
+
+def _us(g, steps=200):
+    best = 1e9
+    for _ in range(4):
+        g.step(steps)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        g.step(steps)
+        e[1].record()
+        torch.cuda.synchronize()
+        best = min(best, e[0].elapsed_time(e[1]) / steps * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("nx,ny", [(101, 101), (301, 257), (700, 531)])
+def test_the_variant_named_takes_the_time_named(nx, ny):
+    """EEBM lattices on which several steps per launch take half the time of
+    the best single steps.  The variant that the autotuner names, given to a
+    new handle or to set_variant, is within 1.4 times the tuned handle (under
+    the index of a one-step tiling it was 1.6 to 2 times)."""
+    T0 = np.random.default_rng(3).uniform(-0.6, 0.6, (ny, nx))
+    prob = synth.Problem(dim=2, q=5, nx=nx, ny=ny, tau=0.8, ste=0.2,
+                         delta=0.05, bc=(D, D, P, P),
+                         wall_T=(1.0, -0.5, 0.0, 0.0), tol=1e-12, max_it=40,
+                         storage="f64", scheme="eebm", T0=T0)
+    g = Stefan(prob)
+    v, ms = g.autotune(steps=96)
+    tuned = _us(g)
+    g.close()
+    a = Stefan(prob, variant=v)
+    new = _us(a)
+    a.close()
+    b = Stefan(prob, variant=0)
+    b.set_variant(v)
+    given = _us(b)
+    b.close()
+    print(f"{nx}x{ny}: {variant_names(5, 'f64')[v]}, {ms * 1e3:.2f} us per "
+          f"step; tuned handle {tuned:.2f}, new one {new:.2f}, given "
+          f"{given:.2f}", flush=True)
+    assert new <= 1.4 * tuned and given <= 1.4 * tuned
+
+
+def test_the_library_choice_is_a_variant():
+    """by its index on a handle, in the batch and in one step with no handle"""
+    from paper_2505_13097_amd import StefanBatch, step_noalloc
+    prob = synth.planar_2d(n=70, ny=45, storage="f64").with_(ste=0.2)
+    names = variant_names(5, "f64")
+    v = names.index("0x0/npt1")
+    one = names.index("64x1/npt1")
+    out = []
+    for k in (-1, v, one):
+        g = Stefan(prob, variant=k)
+        g.step(13)
+        out.append(g.state())
+        src = torch.from_numpy(out[-1]).cuda()
+        dst = torch.empty_like(src)
+        step_noalloc(prob, src, dst, variant=k)
+        g.step(1)
+        assert np.array_equal(dst.cpu().numpy(), g.state())
+        g.close()
+        b = StefanBatch([prob, prob.with_(nx=33, T0=None)])
+        b.set_schedule(k)
+        b.step(13)
+        out.append(b.temperature(0))
+        b.close()
+    for k in range(2):
+        assert np.array_equal(out[k], out[k + 2])
+        assert np.array_equal(out[k], out[k + 4])
