@@ -296,7 +296,9 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    at most 2048 nodes with no Neumann wall run many steps per launch in one workgroup, both
    states in LDS (others run the default variant; the batched form rejects
    it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z
-   slices swept by one block); used by autotuners. */
+   slices swept by one block; those of one wave, "64x1/npt1/z1" and z2, run
+   the default variant on lattices larger than those that take them by
+   default); used by autotuners. */
 int lbm_stefan_variant_count(int32_t q, int32_t storage, int32_t *count);
 const char *lbm_stefan_variant_name(int32_t q, int32_t storage,
                                     int32_t variant);

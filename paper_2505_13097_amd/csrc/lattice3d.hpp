@@ -721,6 +721,17 @@ inline const Variant3 *variants3(int *n) {
   *n = (int)(sizeof(v) / sizeof(Variant3));
   return v;
 }
+// Variants of one wave per block run on lattices up to the size where the
+// library takes them itself; a larger one runs them as its default, so that
+// no lattice holds statistics slots for more blocks than it launches (512^3:
+// 2.1M slots of one wave and slice, 64 MiB, against 16).
+constexpr int64_t kSmall3Nodes = 400000, kSmall3Bytes = 130000000;
+constexpr bool variant3_runs(int v, int q, size_t s, int64_t nodes) {
+  return v == 21 ? nodes <= kSmall3Nodes
+         : v == 22 ? nodes <= kSmall3Nodes ||
+                         nodes * q * (int64_t)s <= kSmall3Bytes
+                   : true;
+}
 // The library default.  Up to 400k nodes one wave per block and one slice
 // (index 21): the chip is short of waves, and a wave that sweeps 8 slices
 // takes 8 solves one after the other (us per step, 64x4/npt1/z8/nt -> here:
@@ -736,10 +747,15 @@ inline const Variant3 *variants3(int *n) {
 // the caches).
 constexpr int kLargeVariant3D = 0;
 inline int default_3d(int q, size_t s, bool eebm, int64_t nodes) {
-  if (nodes <= 400000) return 21;
-  if (nodes * q * (int64_t)s <= 130000000) return 22;
+  if (nodes <= kSmall3Nodes) return 21;
+  if (nodes * q * (int64_t)s <= kSmall3Bytes) return 22;
   return q == 19 && nodes <= 8000000 && !(eebm && s == 4) ? 3
                                                           : kLargeVariant3D;
+}
+// what variant v (-1: the default) runs as
+inline int run_variant3(int v, int q, size_t s, bool eebm, int64_t nodes) {
+  return v >= 0 && variant3_runs(v, q, s, nodes) ? v
+                                                 : default_3d(q, s, eebm, nodes);
 }
 // split step: the front strip is the first kFront3Columns columns, run
 // with the tiling of variant kFront3Variant (64 x 4, 32 slices per item:

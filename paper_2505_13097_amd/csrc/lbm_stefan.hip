@@ -118,6 +118,12 @@ TilePlan plan_for(const lbm_stefan_params &p) {
                    p.scheme == LBM_SCHEME_EEBM, p.nx, p.ny);
 }
 
+// the 3D variant that variant v of a lattice runs as (-1: the default)
+int variant_3d(const lbm_stefan_params &p, int v) {
+  return run_variant3(v, p.q, p.storage == LBM_STORE_F64 ? 8 : 4,
+                      p.scheme == LBM_SCHEME_EEBM, nodes_of(p));
+}
+
 int default_2d(const lbm_stefan_params &p) {
   return one_step_default(p.storage == LBM_STORE_F64 ? 8 : 4, nodes_of(p));
 }
@@ -135,6 +141,7 @@ irebm::Layout irebm::layout_for(const lbm_stefan_params *p) {
   if (p->dim == 3) {
     const Variant3 *v3 = variants3(&nv);
     for (int i = 0; i < nv; ++i) {
+      if (variant_3d(*p, i) != i) continue;
       mt = std::max(mt, items3_for(v3[i], p->nx, p->ny, p->nz));
       if (v3[i].split && p->nx > 2 * kFront3Columns) {
         // quiet-pass items, then the front strip's
@@ -435,7 +442,7 @@ hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
     fill_args3(h->p, &A);
     A.slots = h->slots;
     int nv;
-    const Variant3 &v = variants3(&nv)[h->variant];
+    const Variant3 &v = variants3(&nv)[variant_3d(h->p, h->variant)];
     const int mode = mode_of(h->p);
     if (split3_applies(h, v)) {
       for (int64_t s = 0; s < nsteps; ++s) {
@@ -682,9 +689,7 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
   // default: the resident kernel for the small 1D lattices it takes
   h->variant = p->variant >= 0
                    ? p->variant
-                   : (p->dim == 3 ? default_3d(p->q, p->storage == LBM_STORE_F64 ? 8 : 4,
-                                              p->scheme == LBM_SCHEME_EEBM,
-                                              nodes_of(*p))
+                   : (p->dim == 3 ? variant_3d(*p, -1)
                                   : (p->q == 3 ? (resident_ok(*p)
                                                       ? kResidentVariant1D
                                                       : kDefaultVariant1D)
@@ -949,7 +954,9 @@ int lbm_stefan_autotune(lbm_stefan_t *h, void *scratch, size_t scratch_bytes,
   hipError_t err = hipSuccess;
   for (int v = 0; v < nv && err == hipSuccess; ++v) {
     // a Neumann lattice runs two-step variants as the default one, and a
-    // lattice the resident kernel does not take runs that variant so too
+    // lattice the resident kernel does not take runs that variant so too, and
+    // a large 3D one those of small ones
+    if (p.dim == 3 && variant_3d(p, v) != v) continue;
     if (vt && vt[v].tb && has_neumann(p)) continue;
     if (vt && vt[v].res && !resident_ok(p)) continue;
     if (vt && vt[v].tb == 2) continue;  // single lattices: same as tb = 1

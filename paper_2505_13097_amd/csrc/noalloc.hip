@@ -97,9 +97,9 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
   const Variant *v2 = nullptr;
   ScratchPlan s;
   if (q.dim == 3) {
-    const int dflt = default_3d(q.q, q.storage == LBM_STORE_F64 ? 8 : 4,
-                                q.scheme == LBM_SCHEME_EEBM, nodes);
-    v3 = &variants3(&nv)[q.variant >= 0 ? q.variant : dflt];
+    v3 = &variants3(&nv)[run_variant3(q.variant, q.q,
+                                      q.storage == LBM_STORE_F64 ? 8 : 4,
+                                      q.scheme == LBM_SCHEME_EEBM, nodes)];
     s = plan_for(items3_for(*v3, q.nx, q.ny, q.nz), nodes);
     if (q.variant < 0 && s.total > LBM_STEFAN_NOALLOC_SCRATCH_BYTES) {
       // (thin rows: too many blocks for the slots, take larger ones)
