@@ -97,8 +97,9 @@ inline void set_tiling(StepArgs *A, const Variant &v) {
   A->per_xcd = (A->nitems + 7) / 8;
 }
 
-// LDS a block of tile_kernel may take (of 160 KB a CU)
-constexpr size_t kTileLds = 156 * 1024;
+// LDS a block of tile_kernel may take: what a launch gets unasked (the
+// largest tile, 22 x 22 nodes of D2Q9 FP64, takes 35 KB)
+constexpr size_t kTileLds = 64 * 1024;
 
 // The library's choice for tile_kernel on an nx x ny lattice (q populations
 // of s bytes), where sweep_kernel is not taken: steps per launch k and the

@@ -324,7 +324,7 @@ struct NodeStats {
   double max_res = 0.0;
   double flux_in = 0.0;
   double flux_out = 0.0;
-  int solves = 0;  // node updates that took the Newton path (not quiet)
+  int solves = 0;  // 3D split step: nodes that were not quiet
 };
 
 // Raw loads of one node: own populations (for T) and pulled ones.
@@ -499,19 +499,12 @@ struct CloseInfo {
   double TD = 0.0, wu = 0.0;
 };
 
-// PLATEAU (quiet-only kernels): phi is taken only where it is exactly 0
-// or 1 (|T - T_m| > 20 delta), with no exp in the code; a Dirichlet node
-// whose wall or own temperature lies nearer the band sets *near instead
-// (its update is then left to a full kernel).
-// om: the node's own post-collision populations, om[i] (an array, or a
-// type that looks them up).
-template <int Q, int SCH = SCHEME_IREBM, bool NEU = true,
-          bool PLATEAU = false, class OM>
+// om: the node's own post-collision populations.
+template <int Q, int SCH = SCHEME_IREBM, bool NEU = true>
 __device__ __forceinline__ double close_node(const StepArgs &A, int x, int y,
-                                    double th, const OM &om, double *q,
+                                    double th, const double *om, double *q,
                                     uint32_t known, double mirror,
-                                    CloseInfo *ci = nullptr,
-                                    int *near = nullptr) {
+                                    CloseInfo *ci = nullptr) {
   uint32_t set = known;
   double fill = 0.0;
 #pragma unroll
@@ -529,20 +522,11 @@ __device__ __forceinline__ double close_node(const StepArgs &A, int x, int y,
   if (ci) ci->wall = wall;
   if (wall >= 0) {
     const double TD = wall_value(A, wall, x, y);
-    double D;
-    if constexpr (PLATEAU && SCH == SCHEME_IREBM) {
-      const double ud = (TD - A.tm) * A.inv_delta;
-      const double ut = (th - A.tm) * A.inv_delta;
-      if (!(fabs(ud) > 20.0 && fabs(ut) > 20.0)) *near = 1;
-      D = TD + ((ud > 20.0 ? 1.0 : 0.0) - (ut > 20.0 ? 1.0 : 0.0)) *
-                   A.inv_ste;
-    } else {
-      D = SCH == SCHEME_EEBM    ? TD + (TD > A.tm ? A.inv_ste : 0.0)
-          : SCH == SCHEME_ILFBM ? TD
-                                : TD + (phi_only(TD, A.tm, A.inv_delta) -
-                                        phi_only(th, A.tm, A.inv_delta)) *
-                                           A.inv_ste;
-    }
+    double D = SCH == SCHEME_EEBM    ? TD + (TD > A.tm ? A.inv_ste : 0.0)
+               : SCH == SCHEME_ILFBM ? TD
+                                     : TD + (phi_only(TD, A.tm, A.inv_delta) -
+                                             phi_only(th, A.tm, A.inv_delta)) *
+                                                A.inv_ste;
     double wu = 0.0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -615,13 +599,10 @@ __device__ __forceinline__ void node_masks(const StepArgs &A, int x, int y,
 
 // The update of one node from its temperature th and its pulled and closed
 // populations q: the next state's populations into v (rounded to the
-// storage type).  QUIET: a kernel built for quiet nodes only (no Newton
-// code, so fewer registers); a node that is not quiet (or near, a wall node
-// close_node marked) is counted in st.solves, v is left meaningless, and
-// the caller hands its work item to a full kernel.
-template <int Q, typename S, int MODE, bool QUIET = false>
+// storage type).
+template <int Q, typename S, int MODE>
 __device__ __forceinline__ void update_pulled(const StepArgs &A, double th,
-                                              const double q[Q], int near,
+                                              const double q[Q],
                                               NodeStats &st, S v[Q]) {
   constexpr bool PLAIN = base_mode(MODE) == kPlain;
   constexpr bool EEBM = base_mode(MODE) == kEebm;
@@ -647,7 +628,7 @@ __device__ __forceinline__ void update_pulled(const StepArgs &A, double th,
     const double um = (m0 - A.tm) * A.inv_delta;
     const double d = th - m0;
     const double dx0 = m0 - (m0 - A.inv_ste);
-    if (u < -20.0 && um < -20.0 && th - d == m0 && !near &&
+    if (u < -20.0 && um < -20.0 && th - d == m0 &&
         (PLAIN || 2.0 * fabs(d) <= fabs(dx0))) {
       const bool one = fabs(d) <= A.tol;
       const int it = (one || A.max_it < 2) ? 1 : 2;
@@ -658,12 +639,6 @@ __device__ __forceinline__ void update_pulled(const StepArgs &A, double th,
         v[i] = (S)(A.a * q[i] + A.wtau[wclass<Q>(i)] * m0);
       return;
     }
-  }
-  ++st.solves;
-  if constexpr (QUIET) {
-#pragma unroll
-    for (int i = 0; i < Q; ++i) v[i] = (S)q[i];
-    return;
   }
   double pth, dpth;
   phi_dphi(th, A.tm, A.inv_delta, pth, dpth);
@@ -690,7 +665,7 @@ __device__ __forceinline__ void update_pulled(const StepArgs &A, double th,
 }
 
 // The update of one node from its loads (update_pulled after the closures).
-template <int Q, typename S, int MODE, bool FAST, bool QUIET = false>
+template <int Q, typename S, int MODE, bool FAST>
 __device__ __forceinline__ void update_values(const StepArgs &A, int x, int y,
                                               const NodeLoad<Q, S> &L,
                                               NodeStats &st, S v[Q]) {
@@ -705,19 +680,18 @@ __device__ __forceinline__ void update_values(const StepArgs &A, int x, int y,
   }
 #pragma unroll
   for (int i = 0; i < Q; ++i) q[i] = (double)L.pull[i];
-  int near = 0;
   if (!FAST) {
     if (L.known != (1u << Q) - 1u)
       st.flux_in +=
-          close_node<Q, EEBM ? SCHEME_EEBM : SCHEME_IREBM, NEU, QUIET>(
-              A, x, y, th, om, q, L.known, L.mirror, nullptr, &near);
+          close_node<Q, EEBM ? SCHEME_EEBM : SCHEME_IREBM, NEU>(
+              A, x, y, th, om, q, L.known, L.mirror);
     if (L.out) {
 #pragma unroll
       for (int i = 1; i < Q; ++i)
         if (L.out >> i & 1u) st.flux_out += om[i];
     }
   }
-  update_pulled<Q, S, MODE, QUIET>(A, th, q, near, st, v);
+  update_pulled<Q, S, MODE>(A, th, q, st, v);
 }
 
 // The update of one node from its loads; writes the next state.

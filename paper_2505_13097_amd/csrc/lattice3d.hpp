@@ -289,8 +289,9 @@ __device__ __forceinline__ int dirichlet_face3(const StepArgs3 &A, int x,
 // The zeroth moment a Dirichlet closure gives a node at wall temperature
 // TD: IREBM eq. Dir_on_q (TD plus the latent term's jump between the wall
 // and the node's temperature th), EEBM the wall enthalpy.  PLATEAU (the
-// quiet pass): phi only where it is exactly 0 or 1, *near set when the
-// wall or the node lies nearer the band (see close_node)
+// quiet pass): phi is taken only where it is exactly 0 or 1 (|T - T_m| >
+// 20 delta), with no exp in the code; a node whose wall or own temperature
+// lies nearer the band sets *near (its update is then left to the full pass)
 template <bool EEBM, bool PLATEAU>
 __device__ __forceinline__ double dirichlet_deficit3(const StepArgs3 &A,
                                                      double TD, double th,
@@ -313,8 +314,7 @@ __device__ __forceinline__ double dirichlet_deficit3(const StepArgs3 &A,
 // Dir_on_q, EEBM the wall enthalpy) shared by weight; Neumann deficit to
 // M0 of the mirror's pulls (eq. Neu_on_q) shared by weight; own
 // Omega_opp for anything left.  Returns the sum of the closed values.
-// PLATEAU (the quiet pass): phi only where it is exactly 0 or 1, *near set
-// when the wall or the node lies nearer the band (see close_node)
+// PLATEAU, near: as in dirichlet_deficit3.
 template <int Q, bool EEBM, bool NEU, bool PLATEAU = false, typename S>
 __device__ __forceinline__ double close3(const StepArgs3 &A, int x, int y,
                                          int z, double th, const S *om,

@@ -125,13 +125,6 @@ hipError_t launch_tile_t(const StepArgs &A, const TilePlan &P, int k,
     const size_t lds = (size_t)P.rx * P.ry * Q * sizeof(S);
     if (k < 1 || k > P.k || threads > 1024 || lds > kTileLds || tiles < 1)
       return hipErrorInvalidValue;
-    if (lds > 65536) {
-      // above the default limit of dynamic LDS (cheap, and per device)
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void *>(tile_kernel<Q, S, MODE>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds);
-      if (e != hipSuccess) return e;
-    }
     dim3 grid((unsigned)(8 * ((tiles + 7) / 8))), block((unsigned)threads);
     tile_kernel<Q, S, MODE><<<grid, block, lds, stream>>>(A, P, k, mid,
                                                           mid_stride);

@@ -185,7 +185,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
 #pragma unroll
       for (int i = 0; i < Q; ++i) m0 += q[i];
       if constexpr (EEBM) {
-        update_pulled<Q, S, MODE>(A, 0.0, q, 0, st, v);
+        update_pulled<Q, S, MODE>(A, 0.0, q, st, v);
       } else {
         // the quiet test and update of update_pulled, for the whole row
         const bool valid = lane >= l && lane < w - l;
@@ -253,7 +253,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
               q[i] = (double)p[i];
             }
             NodeStats one;
-            update_pulled<Q, S, MODE>(B, th, q, 0, one, v);
+            update_pulled<Q, S, MODE>(B, th, q, one, v);
             // (a halo node's solve is counted by its own wave as well)
             st.max_it = max(st.max_it, one.max_it);
             st.max_res = fmax(st.max_res, one.max_res);
