@@ -285,12 +285,13 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    name of one ("<tile_x>x<tile_y>/npt<k>[/r<m>][/nt][/rev]": tile size,
    nodes per thread, m tiles stacked along y per thread block,
    non-temporal stores, block order reversed every other step; or
-   "<w>x<b>/t2/r<m>[/nt]": two time steps per launch, a w-column window
-   sweeping m rows, b rows per pass, on lattices of about 100 columns or
-   fewer, and up to four steps per launch by waves sweeping m rows (at most
-   32 in the batched form) on wider ones and in the batched form; a single
-   trailing step then uses the default variant, and a lattice with a Neumann
-   wall runs the default variant; q = 5 and 9 also "0x0/npt1", the library's
+   "<w>x<b>/t2/r<m>[/nt]" and "/t2s/": two time steps per launch, a w-column
+   window sweeping m rows, b rows per pass; on wide lattices (88 columns and
+   32 rows, 64 and 16 where periodic, and with IREBM more than 600k nodes in
+   FP64 and 1.5M in FP32) up to four steps per launch instead, by waves
+   sweeping at most m rows, and in the batched form always so (there w and b
+   do not matter, nor m above 32); a single trailing step then uses the default
+   variant, and a lattice with a Neumann wall runs the default variant; q = 5 and 9 also "0x0/npt1", the library's
    own choice for the lattice (what params.variant = -1 takes); q = 3 also
    "resident2048": D1Q3 lattices of
    at most 2048 nodes with no Neumann wall run many steps per launch in one workgroup, both

@@ -774,6 +774,12 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
   for (int v = 0; v < nv && rc == LBM_STEFAN_OK && err == hipSuccess; ++v) {
     // (single lattices only; one of the others)
     if (vt[v].res || vt[v].lib) continue;
+    // two-step variants differ by their segments' rows alone
+    bool tried = false;
+    for (int u = 0; u < v && vt[v].tb; ++u)
+      tried |= vt[u].tb && batch_rows(vt[u]) == batch_rows(vt[v]) &&
+               vt[u].nt == vt[v].nt;
+    if (tried) continue;
     if (v != b->variant) {
       b->variant = v;
       rc = build_schedule(b);

@@ -283,8 +283,9 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
 // 64^2 to 1024^2 take 505 us per four steps with 32 and 64 rows, 560 with 16
 // and 128 (two-step launches of step2_kernel, split by quiet and solving
 // items, took 1040).
+inline int batch_rows(const Variant &v) { return v.rows < 32 ? v.rows : 32; }
 inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v) {
-  SweepPlan P = sweep_plan(p, 4, v.rows < 32 ? v.rows : 32, 8, v.nt != 0);
+  SweepPlan P = sweep_plan(p, 4, batch_rows(v), 8, v.nt != 0);
   if (P.k > 0) return P;
   P.k = 4;
   P.tile = frame_tile(4);

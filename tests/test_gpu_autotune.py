@@ -78,3 +78,27 @@ def test_the_library_choice_is_a_variant():
     for k in range(2):
         assert np.array_equal(out[k], out[k + 2])
         assert np.array_equal(out[k], out[k + 4])
+
+
+@pytest.mark.parametrize("q", [5, 9])
+def test_the_batch_tuner_tries_each_schedule_once(q):
+    """In a batch two-step variants differ by the rows of their segments (at
+    most 32) alone: of each length the first one is tried.  Lattices on which
+    sweeps take half the time of single steps, so that one of them is named."""
+    from paper_2505_13097_amd import StefanBatch
+    probs = [synth.Problem(
+        dim=2, q=q, nx=700, ny=600 + k, tau=0.8, ste=0.2, delta=0.05,
+        bc=(D, D, P, P), wall_T=(1.0, -0.5, 0.0, 0.0), tol=1e-12, max_it=40,
+        storage="f32", scheme="eebm", T0=np.full((600 + k, 700), -0.5))
+        for k in range(4)]
+    names = variant_names(q, "f32")
+    first = {}
+    for n in names:
+        if "/t2" in n:
+            first.setdefault(min(int(n.split("/r")[1].split("/")[0]), 32), n)
+    for _ in range(3):
+        b = StefanBatch(probs)
+        v, bpc, ms = b.autotune(steps=8)
+        b.close()
+        print(f"q{q}: {names[v]}, {ms * 1e3:.1f} us per step", flush=True)
+        assert names[v] in first.values()
