@@ -307,6 +307,14 @@ const char *lbm_stefan_variant_name(int32_t q, int32_t storage,
 /* Select the kernel variant of an existing handle (resets statistics). */
 int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant);
 
+/* The kernel that lbm_stefan_step launches under the handle's variant (a
+   static name) and the most steps that one launch of it takes; either output
+   may be NULL.  IREBM lattices under "sweep_kernel" that it does not suit in
+   every state go by single steps ("step_kernel") where the front stands off
+   the walls; *routed (nullable) is 1 for those, else 0. */
+int lbm_stefan_launches(const lbm_stefan_t *h, const char **kernel,
+                        int32_t *steps, int32_t *routed);
+
 /*
  * Autotuner: time every compiled variant for `steps` steps (1..10000) with
  * HIP events on the handle's stream, keep the fastest.  The state is saved
@@ -486,6 +494,11 @@ int lbm_stefan_batch_init(const lbm_stefan_params *params, int32_t count,
  */
 int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,
                                   int32_t blocks_per_cu, int32_t graph_steps);
+
+/* As lbm_stefan_launches, of the batch's current variant. */
+int lbm_stefan_batch_launches(const lbm_stefan_batch_t *b,
+                              const char **kernel, int32_t *steps,
+                              int32_t *routed);
 
 /* Advance every instance nsteps (asynchronous on the batch's stream). */
 int lbm_stefan_batch_step(lbm_stefan_batch_t *b, int64_t nsteps);

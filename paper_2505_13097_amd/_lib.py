@@ -76,6 +76,10 @@ SIGNATURES = {
     "lbm_stefan_variant_name": (ctypes.c_char_p, [ctypes.c_int32, ctypes.c_int32,
                                                   ctypes.c_int32]),
     "lbm_stefan_set_variant": (ctypes.c_int, [_vp, ctypes.c_int32]),
+    "lbm_stefan_launches": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_char_p),
+                                           ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
+    "lbm_stefan_batch_launches": (ctypes.c_int, [
+        _vp, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
     "lbm_stefan_autotune": (ctypes.c_int, [_vp, _vp, ctypes.c_size_t, ctypes.c_int32,
                                            ctypes.POINTER(ctypes.c_int32),
                                            _c_double_p]),

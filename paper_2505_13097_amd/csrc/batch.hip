@@ -615,6 +615,20 @@ int lbm_stefan_batch_set_schedule(lbm_stefan_batch_t *b, int32_t variant,
   return LBM_STEFAN_OK;
 }
 
+int lbm_stefan_batch_launches(const lbm_stefan_batch_t *b,
+                              const char **kernel, int32_t *steps,
+                              int32_t *routed_out) {
+  if (!b) return bfail(nullptr, LBM_STEFAN_EINVAL, "batch is NULL");
+  const int k = steps_per_launch(b);
+  if (kernel)
+    *kernel = k > 1                  ? "batch_sweep_kernel"
+              : b->blocks_per_cu > 0 ? "batch_persistent_kernel"
+                                     : "batch_step_kernel";
+  if (steps) *steps = k;
+  if (routed_out) *routed_out = routed(b);
+  return LBM_STEFAN_OK;
+}
+
 int lbm_stefan_batch_step(lbm_stefan_batch_t *b, int64_t nsteps) {
   if (!b) return bfail(nullptr, LBM_STEFAN_EINVAL, "batch is NULL");
   if (nsteps < 0) return bfail(b, LBM_STEFAN_EINVAL, "nsteps < 0");

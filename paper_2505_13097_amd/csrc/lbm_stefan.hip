@@ -112,6 +112,8 @@ std::string irebm::validate_params(const lbm_stefan_params *p) {
 
 namespace {
 
+constexpr int kResidentSteps = 4096;  // of one launch of resident1d_kernel
+
 TilePlan plan_for(const lbm_stefan_params &p) {
   if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM) return TilePlan();
   return tile_plan(p.q, p.storage == LBM_STORE_F64 ? 8 : 4,
@@ -476,7 +478,7 @@ hipError_t irebm::advance(lbm_stefan_t *h, int64_t nsteps) {
       const int mode = mode_of(h->p);
       while (nsteps > 0) {
         // bounded launches (a few ms each)
-        const int32_t k = (int32_t)std::min<int64_t>(nsteps, 4096);
+        const int32_t k = (int32_t)std::min<int64_t>(nsteps, kResidentSteps);
         A.src = h->buf[h->cur];
         A.dst = h->buf[h->cur ^ 1];
         const hipError_t e =
@@ -915,6 +917,36 @@ int lbm_stefan_set_variant(lbm_stefan_t *h, int32_t variant) {
   HIPCHK(h, scan_route(h));
   // the tile -> slot mapping changes with the tile shape
   HIPCHK(h, zero_stats_async(h));
+  return LBM_STEFAN_OK;
+}
+
+int lbm_stefan_launches(const lbm_stefan_t *h, const char **kernel,
+                        int32_t *steps, int32_t *routed) {
+  if (!h) return fail(nullptr, LBM_STEFAN_EINVAL, "handle is NULL");
+  const lbm_stefan_params &p = h->p;
+  const char *name = "step_kernel";
+  int k = 1;
+  int nv;
+  if (p.dim == 3) {
+    name = "step3_kernel";
+  } else if (p.scheme == LBM_SCHEME_ILFBM) {
+    name = "ilfbm_tile_kernel";
+  } else if (variants(p.q, &nv)[h->variant].res && resident_ok(p)) {
+    name = "resident1d_kernel";
+    k = kResidentSteps;
+  } else if (h->plan.k > 0) {
+    name = "tile_kernel";
+    k = h->plan.k;
+  } else if (h->sweep.k > 0) {
+    name = "sweep_kernel";
+    k = h->sweep.k;
+  } else if (two_step_variant(h)) {
+    name = "step2_kernel";
+    k = 2;
+  }
+  if (kernel) *kernel = name;
+  if (steps) *steps = k;
+  if (routed) *routed = h->sweep.gated;
   return LBM_STEFAN_OK;
 }
 

@@ -99,6 +99,13 @@ def step_noalloc(prob, src, dst, stats=False, variant=-1, strict=False,
     return st.as_dict() if st is not None else None
 
 
+def _launches(query, h):
+    name, steps, routed = ctypes.c_char_p(), ctypes.c_int32(), ctypes.c_int32()
+    C.check(query(h, ctypes.byref(name), ctypes.byref(steps),
+                  ctypes.byref(routed)))
+    return name.value.decode(), steps.value, bool(routed.value)
+
+
 class Stefan:
     """One lattice on the current CUDA (HIP) device: D1Q3, D2Q5, D2Q9,
     D3Q7 or D3Q19, stepped by IREBM (Algorithm 3), EEBM (Algorithm 2) or
@@ -214,6 +221,11 @@ class Stefan:
 
     def set_variant(self, v):
         C.check(self._lib.lbm_stefan_set_variant(self.h, int(v)), self.h)
+
+    def launches(self):
+        """(kernel, most steps per launch, whether single steps take over
+        where a front stands off the walls) under the handle's variant."""
+        return _launches(self._lib.lbm_stefan_launches, self.h)
 
     def autotune(self, steps=10):
         """Time every kernel variant on this lattice and keep the fastest;
@@ -355,6 +367,10 @@ class StefanBatch:
     def set_schedule(self, variant=-1, blocks_per_cu=0, graph_steps=0):
         C.check_batch(self._lib.lbm_stefan_batch_set_schedule(
             self.h, int(variant), int(blocks_per_cu), int(graph_steps)), self.h)
+
+    def launches(self):
+        """As Stefan.launches, of the current schedule."""
+        return _launches(self._lib.lbm_stefan_batch_launches, self.h)
 
     def step(self, nsteps):
         C.check_batch(self._lib.lbm_stefan_batch_step(self.h, int(nsteps)), self.h)
