@@ -88,10 +88,13 @@ def waves(P, w):
         yield x0, min(x0 + w, P["xb"]), y0, min(y0 + rows, P["yb"])
 
 
-def check_wave(x0, x1, y0, y1, K, nx, ny):
-    """lanes and rows that sweep_body loads; wraps at most once"""
+def check_wave(x0, x1, y0, y1, K, nx, ny, px, py):
+    """lanes and rows that sweep_body loads: they wrap at most once, and on a
+    periodic axis only"""
     w = x1 - x0 + 2 * K
     assert x0 < x1 and y0 < y1 and w <= 64
+    assert px or (x0 >= K and x1 + K <= nx)
+    assert py or (y0 >= K and y1 + K <= ny)
     x = x0 - K + np.minimum(np.arange(64), w - 1)
     x = np.where(x < 0, x + nx, x)
     x = np.where(x >= nx, x - nx, x)
@@ -188,7 +191,7 @@ def test_sweep_partition(nx, ny, px, py, front):
                 ws = list(waves(P, w))
                 covered(tiles + ws, nx, ny)
                 for b in ws:
-                    check_wave(*b, K, nx, ny)
+                    check_wave(*b, K, nx, ny, px, py)
         ns = (P["nleft"] + P["nright"]) * P["nside"]
         for i in {0, ns - 1, ns, len(tiles) - 1} & set(range(len(tiles))):
             for K in range(1, plan_k + 1):
@@ -280,6 +283,6 @@ def test_planted_mistakes_are_seen():
     with pytest.raises(AssertionError):   # a segment left out
         covered(list(frame_tiles(P, 300, 200)) + list(waves(P, 56)), 300, 200)
     with pytest.raises(AssertionError):   # a strip too wide for a wave
-        check_wave(20, 80, 20, 36, 4, 300, 200)
+        check_wave(20, 80, 20, 36, 4, 300, 200, 0, 0)
     with pytest.raises(AssertionError):   # a segment at a wall with no frame
-        check_wave(20, 76, 190, 206, 4, 300, 200)
+        check_wave(20, 76, 182, 198, 4, 300, 200, 1, 0)
