@@ -290,7 +290,8 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    32 rows, 64 and 16 where periodic, and with IREBM more than 600k nodes in
    FP64 and 1.5M in FP32) up to four steps per launch instead, by waves
    sweeping at most m rows, and in the batched form always so (there w and b
-   do not matter, nor m above 32); a single trailing step then uses the default
+   do not matter, nor m above 32), or, in a batch of small lattices, the
+   default's single steps; a single trailing step then uses the default
    variant, and a lattice with a Neumann wall runs the default variant; q = 5 and 9 also "0x0/npt1", the library's
    own choice for the lattice (what params.variant = -1 takes); q = 3 also
    "resident2048": D1Q3 lattices of

@@ -67,6 +67,7 @@ struct lbm_stefan_batch {
   int64_t max_items = 0, nitems = 0;
   int cur = 0;
   int variant = kDefaultVariant2D, blocks_per_cu = 0, graph_steps = 0;
+  int run = kDefaultVariant2D; // what the variant runs as (run_variant)
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   int64_t steps = 0;
   std::string err;
@@ -100,8 +101,36 @@ int64_t batch_slots(const Variant &v, const lbm_stefan_params &p) {
                                p.ny));
 }
 
+// Do two-step variants of a batch sweep?  The frame's tiles compute each node
+// up to four times over, and lattices too small for a strip are all tiles, so
+// the batch takes single steps (the default tiling) where more than 0.3 of its
+// nodes lie in frames, EEBM 0.45 (us per step, single steps / sweeps: 1000
+// FP32 D2Q5 lattices of 64^2 80 / 205, EEBM 46 / 66; 600 FP64 D2Q9 ones 131 /
+// 269; 500 FP32 D2Q9 ones of 87^2 119 / 204; 100 FP64 D2Q5 ones of 150^2, 0.26
+// in frames, 58 / 49; 60 FP64 D2Q9 ones of 200^2 107 / 73; EEBM 110^2, 0.27,
+// 40 / 22).
+bool batch_sweeps(const lbm_stefan_params *ps, int count) {
+  int nv;
+  const Variant &v = variants(ps[0].q, &nv)[kSweepVariant2D];
+  double all = 0.0, strips = 0.0;
+  for (int k = 0; k < count; ++k) {
+    const SweepPlan P = batch_plan(ps[k], v);
+    all += (double)ps[k].nx * ps[k].ny;
+    strips += (double)(P.xb - P.xa) * (P.yb - P.ya);
+  }
+  return all - strips <= (ps[0].scheme == LBM_SCHEME_EEBM ? 0.45 : 0.3) * all;
+}
+
+// what variant v of a batch runs as
+int run_variant(const lbm_stefan_params *ps, int count, int v) {
+  int nv;
+  return variants(ps[0].q, &nv)[v].tb && !batch_sweeps(ps, count)
+             ? kDefaultVariant2D
+             : v;
+}
+
 // the variant a batch starts with (and -1 selects): sweeping waves, unless
-// the batch is small or a member is an IREBM melt that freezes (see
+// the batch is small or of small lattices, or a member is an IREBM melt that freezes (see
 // sweep_nodes, sweep_default)
 int default_variant(const lbm_stefan_params *ps, int count) {
   if (ps[0].q == 3) return kDefaultVariant1D;
@@ -114,7 +143,7 @@ int default_variant(const lbm_stefan_params *ps, int count) {
     front_walls(ps[k], &hot);
     if (ps[k].scheme == LBM_SCHEME_IREBM && !hot) return kDefaultVariant2D;
   }
-  return kSweepVariant2D;
+  return run_variant(ps, count, kSweepVariant2D);
 }
 
 int bfail(lbm_stefan_batch_t *b, int code, const std::string &msg) {
@@ -251,7 +280,8 @@ void set_batch_route(lbm_stefan_batch_t *b, int K, double bytes) {
 int build_schedule(lbm_stefan_batch_t *b) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
-  const Variant &v = vt[b->variant];
+  b->run = run_variant(b->ps.data(), b->count, b->variant);
+  const Variant &v = vt[b->run];
   const bool two = routed(v, b->ps[0]);   // (also laid out for single steps)
   std::vector<StepArgs> d(b->count);
   std::vector<SweepPlan> pl(b->count);
@@ -327,7 +357,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
 
 bool routed(const lbm_stefan_batch_t *b) {
   int nv;
-  return routed(variants(b->q, &nv)[b->variant], b->ps[0]);
+  return routed(variants(b->q, &nv)[b->run], b->ps[0]);
 }
 
 // one launch of k steps (at most steps_per_launch) from buffer `parity`
@@ -335,13 +365,13 @@ hipError_t launch_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
                         int parity, int k, RouteCtl *ctl = nullptr) {
   int nv;
   const Variant *vt = variants(b->q, &nv);
-  const Variant &v = vt[b->variant];
+  const Variant &v = vt[b->run];
   BatchLaunch L;
   L.descs = b->descs;
   L.items = b->items;
   L.nitems = b->nitems;
   L.cus = b->cus;
-  L.blocks_per_cu = b->blocks_per_cu;
+  L.blocks_per_cu = b->run == b->variant ? b->blocks_per_cu : 0;
   L.parity = parity;
   L.ctl = ctl;
   if (!v.tb) return batch_launch(b->mode, b->q, b->storage, L, v, stream);
@@ -369,7 +399,7 @@ hipError_t launch_single(const lbm_stefan_batch_t *b, hipStream_t stream,
 // time steps one launch advances at most under the current variant
 int steps_per_launch(const lbm_stefan_batch_t *b) {
   int nv;
-  return variants(b->q, &nv)[b->variant].tb ? 4 : 1;
+  return variants(b->q, &nv)[b->run].tb ? 4 : 1;
 }
 
 // nsteps steps from buffer `parity`, which follows them; sweeps that are
@@ -621,9 +651,10 @@ int lbm_stefan_batch_launches(const lbm_stefan_batch_t *b,
   if (!b) return bfail(nullptr, LBM_STEFAN_EINVAL, "batch is NULL");
   const int k = steps_per_launch(b);
   if (kernel)
-    *kernel = k > 1                  ? "batch_sweep_kernel"
-              : b->blocks_per_cu > 0 ? "batch_persistent_kernel"
-                                     : "batch_step_kernel";
+    *kernel = k > 1 ? "batch_sweep_kernel"
+              : b->blocks_per_cu > 0 && b->run == b->variant
+                  ? "batch_persistent_kernel"
+                  : "batch_step_kernel";
   if (steps) *steps = k;
   if (routed_out) *routed_out = routed(b);
   return LBM_STEFAN_OK;
@@ -788,6 +819,7 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
   for (int v = 0; v < nv && rc == LBM_STEFAN_OK && err == hipSuccess; ++v) {
     // (single lattices only; one of the others)
     if (vt[v].res || vt[v].lib) continue;
+    if (run_variant(b->ps.data(), b->count, v) != v) continue;
     // two-step variants differ by their segments' rows alone
     bool tried = false;
     for (int u = 0; u < v && vt[v].tb; ++u)

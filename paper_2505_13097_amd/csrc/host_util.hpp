@@ -159,8 +159,9 @@ inline int front_walls(const lbm_stefan_params &p, bool *hot) {
 // launch, segments of `rows` rows; an empty plan when the lattice is too
 // small for the frame and a strip.  The frame is two tiles deep where a
 // front starts (a strip that reaches the front solves in every row: the
-// 8192^2 cavity takes 380 us per step with one tile, 324 with two, 347 and
-// 330 with three and four), one at the other walls.  The strip next to it
+// 8192^2 cavity took 380 us per step with one tile, 324 with two, 347 and 330
+// with three and four, segments of 32 rows everywhere), one at the other
+// walls.  The strip next to it
 // goes in segments of `frows` rows, for a front that has left the frame:
 // 8 in a batch (the one named at batch_plan takes 622 us with segments as
 // everywhere, 505 with 8, 520 with 4), 2 in a single lattice that sweeps
@@ -255,10 +256,10 @@ inline int sweep_rows(int64_t ny) {
 
 // sweep_kernel under the library default (an empty plan: tile_kernel or
 // single steps).  Measured (us per step, the best one-step tiling -> here):
-// IREBM heated at a wall 1001
-// x 777 D2Q9 FP64 21.4 -> 11.6, 2048^2 D2Q5 FP32 32.6 -> 16.0, D2Q9 FP64
-// 134 -> 46, 8192^2 D2Q9 FP32 921 -> 324; EEBM 201^2 D2Q9 FP64 6.0 -> 3.8
-// (tile_kernel 4.2), 801^2 19.1 -> 7.2, 2048^2 D2Q5 FP32 27.9 -> 9.6.  A
+// IREBM heated at a wall, the front in the frame (beyond it: route_lattice),
+// 1001 x 777 D2Q9 FP64 21.3 -> 12.9, 2048^2 D2Q5 FP32 31.6 -> 20.3, D2Q9 FP64
+// 134 -> 50, 8192^2 D2Q9 FP32 921 -> 345; EEBM 201^2 D2Q9 FP64 5.8 -> 3.4
+// (tile_kernel 4.2), 801^2 18.2 -> 7.9, 2048^2 D2Q5 FP32 28.0 -> 11.4.  A
 // freezing IREBM lattice (no hot wall) keeps single steps: its bulk is
 // liquid, so the solves of a wave, one after the other, cost more than the
 // traffic saved (801^2 D2Q5 21.2 -> 22.4).

@@ -207,6 +207,24 @@ def test_no_front_position_slows_a_batch(sizes, q):
     assert not slow, slow
 
 
+@pytest.mark.parametrize("count,n,q,storage", [
+    (800, 64, 5, "f32"), (500, 64, 9, "f64"), (400, 87, 9, "f32"),
+    (250, 110, 5, "f32"), (60, 200, 9, "f64")])
+@pytest.mark.parametrize("scheme", ["irebm", "eebm"])
+def test_batches_of_small_lattices(count, n, q, storage, scheme):
+    """lattices that are all frame, nearly so, and mostly strips: the default
+    and a two-step variant against single steps, the same bar"""
+    names = variant_names(q, storage)
+    probs = [p.with_(scheme=scheme)
+             for p in _batch([(n, n)], q, storage, 8)] * count
+    t = [_batch_us(probs, v) for v in (-1, names.index("128x2/t2s/r96/nt"),
+                                       names.index("128x4/npt2"))]
+    print(f"{count} of {n}^2 q{q} {storage} {scheme}: default {t[0]:.1f} us "
+          f"per step, two-step variant {t[1]:.1f}, single steps {t[2]:.1f}",
+          flush=True)
+    assert max(t[:2]) <= 1.25 * t[2]
+
+
 @pytest.mark.parametrize("at", [8, 30, 0.5])
 @pytest.mark.parametrize("graph", [0, 14, 40])
 def test_batch_routes_equal_single_steps(graph, at):
