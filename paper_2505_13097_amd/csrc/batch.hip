@@ -304,7 +304,6 @@ int build_schedule(lbm_stefan_batch_t *b) {
     d[k].src = b->state[0] + b->off[k];
     d[k].dst = b->state[1] + b->off[k];
     set_tiling(&d[k], two ? vt[kDefaultVariant2D] : v);
-    d[k].ctl = two ? b->route : nullptr;
     bytes += 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) * p.nx * p.ny;
     for (int i = 0; two && i < d[k].nitems; ++i) sg.push_back(make_int2(k, i));
     const int64_t n = batch_slots(v, p);
@@ -312,6 +311,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
     b->first_item[k] = sbase;
     if (v.tb) {
       pl[k] = batch_plan(p, v);
+      pl[k].ctl = two ? b->route : nullptr;
       for (int64_t i = 0; i < pl[k].tiles(); ++i)
         t.push_back(make_int2(k, (int)i));
       for (int64_t i = 0; i < pl[k].waves(); ++i)

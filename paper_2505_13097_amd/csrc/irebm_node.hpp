@@ -133,12 +133,11 @@ struct StepArgs {
   double wall_T[4];
   const double *prof[4];
   StatSlot *slots;
-  RouteCtl *ctl;        // null: the launch always runs
 };
 
 // may this launch (of sweeps, route 0, or single steps, 1) run?
 __device__ __forceinline__ bool on_route(const RouteCtl *ctl, int route) {
-  return !ctl || *to_global(&ctl->route) == route;
+  return *to_global(&ctl->route) == route;
 }
 
 // ---- regularized liquid fraction (Section 4.1)

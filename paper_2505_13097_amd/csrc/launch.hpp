@@ -41,13 +41,25 @@ __device__ __forceinline__ void batch_item(const StepArgs *__restrict__ descs,
 template <int Q, typename S, int NPT, int MODE, bool NT>
 __global__ __launch_bounds__(256) void batch_step_kernel(
     const StepArgs *__restrict__ descs, const int2 *__restrict__ items,
-    int32_t nitems, int32_t parity, int32_t reverse, RouteCtl *ctl) {
-  if (!on_route(ctl, 1)) return;
+    int32_t nitems, int32_t parity, int32_t reverse) {
   const int chunk = (nitems + 7) >> 3;
   const int b = (int)blockIdx.x;
   if ((b & 7) * chunk + (b >> 3) >= nitems) return;
   batch_item<Q, S, NPT, MODE, NT, false>(
       descs, items, xcd_item(b, chunk, nitems, reverse), parity);
+}
+
+// the same beside the sweeps of a group (step_routed_kernel)
+template <int Q, typename S, int MODE>
+__global__ __launch_bounds__(256) void batch_step_routed_kernel(
+    const StepArgs *__restrict__ descs, const int2 *__restrict__ items,
+    int32_t nitems, int32_t parity, const RouteCtl *ctl) {
+  if (!on_route(ctl, 1)) return;
+  const int chunk = (nitems + 7) >> 3;
+  const int b = (int)blockIdx.x;
+  if ((b & 7) * chunk + (b >> 3) >= nitems) return;
+  batch_item<Q, S, 2, MODE, false, false>(
+      descs, items, xcd_item(b, chunk, nitems, 0), parity);
 }
 
 // persistent grid sized to the machine: each block walks its XCD's chunk
@@ -71,11 +83,20 @@ __global__ __launch_bounds__(256) void batch_persistent_kernel(
 // one step of one lattice with the (one-step) tiling of v
 template <int Q, typename S, int MODE>
 hipError_t launch_step_t(const StepArgs &A, const Variant &v, bool reverse,
-                         hipStream_t stream) {
+                         hipStream_t stream, const RouteCtl *ctl) {
   StepArgs B = A;
   set_tiling(&B, v);
   B.reverse = reverse;
   dim3 grid(8 * B.per_xcd), block(v.bx, v.by);
+  if (ctl) {
+    if constexpr (Q == 3) {
+      return hipErrorInvalidValue;
+    } else {
+      if (v.npt != 2 || v.nt || reverse) return hipErrorInvalidValue;
+      step_routed_kernel<Q, S, MODE><<<grid, block, 0, stream>>>(B, ctl);
+      return hipGetLastError();
+    }
+  }
 #define LAUNCH(NPT, NT) \
   step_kernel<Q, S, NPT, MODE, NT><<<grid, block, 0, stream>>>(B)
 #define LAUNCH_NPT(NT)                 \
@@ -144,6 +165,16 @@ hipError_t launch_batch_t(const BatchLaunch &b, const Variant &v,
   dim3 grid((unsigned)(8 * std::max<int64_t>(g8, 1))), block(v.bx, v.by);
   const int32_t rev = v.rev && b.parity;
   const bool pers = b.blocks_per_cu > 0;
+  if (b.ctl) {
+    if constexpr (Q == 3) {
+      return hipErrorInvalidValue;
+    } else {
+      if (v.npt != 2 || v.nt || rev || pers) return hipErrorInvalidValue;
+      batch_step_routed_kernel<Q, S, MODE>
+          <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, b.ctl);
+      return hipGetLastError();
+    }
+  }
 #define BLAUNCH(NPT, NTS)                                                  \
   do {                                                                     \
     if (pers)                                                              \
@@ -151,8 +182,7 @@ hipError_t launch_batch_t(const BatchLaunch &b, const Variant &v,
           <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev); \
     else                                                                   \
       batch_step_kernel<Q, S, NPT, MODE, NTS>                              \
-          <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev,  \
-                                       b.ctl);                               \
+          <<<grid, block, 0, stream>>>(b.descs, b.items, nt, b.parity, rev); \
   } while (0)
 #define BLAUNCH_NPT(NTS)                  \
   do {                                    \
@@ -175,10 +205,10 @@ hipError_t launch_batch_t(const BatchLaunch &b, const Variant &v,
 template <int MODE>
 hipError_t step_launch_mode(int q, int storage, const StepArgs &A,
                             const Variant &v, bool reverse,
-                            hipStream_t stream) {
+                            hipStream_t stream, const RouteCtl *ctl) {
   return dispatch_qs(q, storage, [&](auto qt, auto tt) {
     QS_TYPES(qt, tt);
-    return launch_step_t<Q, S, MODE>(A, v, reverse, stream);
+    return launch_step_t<Q, S, MODE>(A, v, reverse, stream, ctl);
   });
 }
 
@@ -225,7 +255,7 @@ hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
 #define IREBM_INSTANTIATE_STEP(M)                                          \
   template hipError_t irebm::step_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::Variant &, bool,     \
-      hipStream_t);                                                        \
+      hipStream_t, const irebm::RouteCtl *);                                                        \
   template hipError_t irebm::tile_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::TilePlan &, int,     \
       char *, int64_t, hipStream_t);                                       \
@@ -238,7 +268,7 @@ hipError_t batch_launch_mode(int q, int storage, const BatchLaunch &b,
 #define IREBM_INSTANTIATE_STEP1(M)                                         \
   template hipError_t irebm::step_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::Variant &, bool,     \
-      hipStream_t);                                                        \
+      hipStream_t, const irebm::RouteCtl *);                                                        \
   template hipError_t irebm::tile_launch_mode<M>(                          \
       int, int, const irebm::StepArgs &, const irebm::TilePlan &, int,     \
       char *, int64_t, hipStream_t)

@@ -527,7 +527,6 @@ hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
                               RouteCtl *ctl) {
   StepArgs A;
   fill_step_args(h, &A);
-  A.ctl = ctl;
   A.src = src;
   A.dst = dst;
   int nv;
@@ -543,7 +542,8 @@ hipError_t irebm::launch_step(const lbm_stefan_t *h, const void *src,
   // a Dirichlet x = 0 wall is where the workloads heat: its tiles first
   A.front_first = h->p.bc[0] == LBM_BC_DIRICHLET;
   return step_launch(mode_of(h->p), h->p.q, h->p.storage, A, v,
-                     v.rev && (h->steps & 1), stream ? stream : h->stream);
+                     v.rev && (h->steps & 1), stream ? stream : h->stream,
+                     ctl);
 }
 
 void irebm::plan_steps(lbm_stefan_t *h) {
@@ -577,14 +577,15 @@ hipError_t irebm::launch_steps(const lbm_stefan_t *h, const void *src,
   if (k == 1) return launch_step(h, src, dst, stream, ctl);
   StepArgs A;
   fill_step_args(h, &A);
-  A.ctl = ctl;
   A.src = src;
   A.dst = dst;
   if (h->plan.k > 0)
     return tile_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->plan, k,
                        stream, (char *)mid, mid_stride);
-  return sweep_launch(mode_of(h->p), h->p.q, h->p.storage, A, h->sweep, k,
-                      stream, (char *)mid, mid_stride);
+  SweepPlan P = h->sweep;
+  P.ctl = ctl;
+  return sweep_launch(mode_of(h->p), h->p.q, h->p.storage, A, P, k, stream,
+                      (char *)mid, mid_stride);
 }
 
 namespace {

@@ -91,6 +91,7 @@ void set_global_error(const std::string &msg);
 void fill_args(const lbm_stefan_params &p, double *const prof[4],
                StepArgs *A);
 void fill_step_args(const lbm_stefan_t *h, StepArgs *A);
+// (ctl: the launch runs on the route of single steps only)
 hipError_t launch_step(const lbm_stefan_t *h, const void *src, void *dst,
                        hipStream_t stream = nullptr,
                        RouteCtl *ctl = nullptr);
@@ -158,7 +159,7 @@ struct BatchLaunch {
 template <int MODE>
 hipError_t step_launch_mode(int q, int storage, const StepArgs &A,
                             const Variant &v, bool reverse,
-                            hipStream_t stream);
+                            hipStream_t stream, const RouteCtl *ctl);
 template <int MODE>
 hipError_t step2_launch_mode(int q, int storage, const StepArgs &A,
                              const Variant &v, bool two, hipStream_t stream);
@@ -187,7 +188,8 @@ hipError_t resident_launch_mode(int storage, const StepArgs &A,
 
 #define IREBM_DECLARE_STEP1(M)                                             \
   extern template hipError_t step_launch_mode<M>(                          \
-      int, int, const StepArgs &, const Variant &, bool, hipStream_t);     \
+      int, int, const StepArgs &, const Variant &, bool, hipStream_t,      \
+      const RouteCtl *);                                                   \
   extern template hipError_t sweep_launch_mode<M>(                         \
       int, int, const StepArgs &, const SweepPlan &, int, char *, int64_t, \
       hipStream_t);                                                        \
@@ -267,27 +269,23 @@ inline int mode_of(const lbm_stefan_params &p) {
   return (p.newton_mode == LBM_NEWTON_PLAIN ? kPlain : kSafeguarded) | neu;
 }
 
-// one step of one lattice (one-step variant v)
+// one step of one lattice (one-step variant v; ctl: see launch_step)
 inline hipError_t step_launch(int mode, int q, int storage, const StepArgs &A,
                               const Variant &v, bool reverse,
-                              hipStream_t stream) {
+                              hipStream_t stream,
+                              const RouteCtl *ctl = nullptr) {
   switch (mode) {
-    case kEebm:
-      return step_launch_mode<kEebm>(q, storage, A, v, reverse, stream);
-    case kPlain:
-      return step_launch_mode<kPlain>(q, storage, A, v, reverse, stream);
-    case kEebm | kNeumann:
-      return step_launch_mode<kEebm | kNeumann>(q, storage, A, v, reverse,
-                                                stream);
-    case kPlain | kNeumann:
-      return step_launch_mode<kPlain | kNeumann>(q, storage, A, v, reverse,
-                                                 stream);
-    case kSafeguarded | kNeumann:
-      return step_launch_mode<kSafeguarded | kNeumann>(q, storage, A, v,
-                                                       reverse, stream);
+#define IREBM_STEP_CASE(M) \
+  case M:                  \
+    return step_launch_mode<M>(q, storage, A, v, reverse, stream, ctl)
+    IREBM_STEP_CASE(kEebm);
+    IREBM_STEP_CASE(kPlain);
+    IREBM_STEP_CASE(kEebm | kNeumann);
+    IREBM_STEP_CASE(kPlain | kNeumann);
+    IREBM_STEP_CASE(kSafeguarded | kNeumann);
     default:
-      return step_launch_mode<kSafeguarded>(q, storage, A, v, reverse,
-                                            stream);
+    IREBM_STEP_CASE(kSafeguarded);
+#undef IREBM_STEP_CASE
   }
 }
 

@@ -75,14 +75,56 @@ __host__ __device__ constexpr int route_units(int nband, int nliquid) {
 constexpr int sweep_mid(int i) { return i == 0 ? 0 : (i == 1 ? 1 : 2); }
 constexpr int sweep_up(int i) { return i == 2 ? 0 : (i == 5 ? 1 : 2); }
 
+// Work of one lattice at up to k steps per launch: the frame's tiles, a
+// block of 256 threads each, then the strips of [xa, xb) x [ya, yb) in
+// segments of `rows` rows, a wave each, strip-fastest, so that neighbouring
+// strips share halo lines in an L2.  The strip next to a side band where a
+// front starts (nfl, nfr: the first, the last) is cut into shorter segments
+// and goes first: a front that has left the band puts a solve into every row
+// of it, one after the other.  Each XCD takes one contiguous part of
+// either list, the frame's (which hold the solves and take longest) first.
+struct SweepPlan {
+  int32_t k = 0;                       // 0: the lattice takes another kernel
+  int32_t xa = 0, xb = 0, ya = 0, yb = 0;
+  int32_t tile = 0;                    // side of a frame tile
+  int32_t nleft = 0, nright = 0;       // tile columns of the side bands
+  int32_t nside = 0;                   // tile rows of the side bands (whole
+                                       // height)
+  int32_t nbottom = 0, ntop = 0;       // tile rows of the other bands
+  int32_t nacross = 0;                 // their tile columns, over [xa, xb)
+  int32_t strips = 0, rows = 0, nseg = 0;
+  int32_t fl = 0, fr = 0;              // a front starts at x = 0, at nx - 1
+  int32_t nfl = 0, nfr = 0, frows = 1, fseg = 0;
+  int32_t nt = 0;
+  // 1: the lattice (the batch) goes by single steps where a sweep holds a
+  // wave of more than chain_max rows with solves
+  int32_t gated = 0, chain_max = 0;
+  RouteCtl *ctl = nullptr;             // null: the launch always runs
+  // strips of w columns
+  void cut(int w) {
+    strips = (xb - xa + w - 1) / w;
+    nfl = fl && strips > 0 ? 1 : 0;
+    nfr = fr && strips > nfl ? 1 : 0;
+  }
+  __host__ __device__ int64_t tiles() const {
+    return (int64_t)(nleft + nright) * nside +
+           (int64_t)(nbottom + ntop) * nacross;
+  }
+  __host__ __device__ int64_t waves() const {
+    return (int64_t)(nfl + nfr) * fseg + (int64_t)(strips - nfl - nfr) * nseg;
+  }
+  __host__ __device__ int64_t slots() const { return tiles() + waves(); }
+};
+
 // One wave: columns [x0, x1) (at most 64 - 2 K), rows [y0, y1), K steps
 // from src to dst.  The K columns and rows around them are lattice nodes
 // (the frame, or wrapped on a periodic axis).  nt: stores bypass the
 // caches.  MID: level l < K is also stored at mid + l * mid_stride bytes
-// (the reverse mode's recomputed states).  A.ctl: when given, takes the rows
+// (the reverse mode's recomputed states).  plan.ctl: when given, takes the rows
 // that held a solve.
 template <int Q, typename S, int MODE, int K, bool MID>
 __device__ __forceinline__ void sweep_body(const StepArgs &A,
+                                           const SweepPlan &plan,
                                            gptr<const S> __restrict__ src,
                                            gptr<S> __restrict__ dst, int x0,
                                            int x1, int y0, int y1, bool nt,
@@ -278,7 +320,7 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
       // (read here: held through the sweep it would cost registers)
       int z = 0;
       asm volatile("" : "+s"(z));
-      RouteCtl *ctl = (&A)[z].ctl;
+      RouteCtl *ctl = (&plan)[z].ctl;
       if (ctl && rows_solved > 0) {
         const int nband = rows_solved >> 16, nliquid = rows_solved & 0xffff;
         atomicMax(&ctl->chain, nband + nliquid);
@@ -288,46 +330,6 @@ __device__ __forceinline__ void sweep_body(const StepArgs &A,
     }
   }
 }
-
-// Work of one lattice at up to k steps per launch: the frame's tiles, a
-// block of 256 threads each, then the strips of [xa, xb) x [ya, yb) in
-// segments of `rows` rows, a wave each, strip-fastest, so that neighbouring
-// strips share halo lines in an L2.  The strip next to a side band where a
-// front starts (nfl, nfr: the first, the last) is cut into shorter segments
-// and goes first: a front that has left the band puts a solve into every row
-// of it, one after the other.  Each XCD takes one contiguous part of
-// either list, the frame's (which hold the solves and take longest) first.
-struct SweepPlan {
-  int32_t k = 0;                       // 0: the lattice takes another kernel
-  int32_t xa = 0, xb = 0, ya = 0, yb = 0;
-  int32_t tile = 0;                    // side of a frame tile
-  int32_t nleft = 0, nright = 0;       // tile columns of the side bands
-  int32_t nside = 0;                   // tile rows of the side bands (whole
-                                       // height)
-  int32_t nbottom = 0, ntop = 0;       // tile rows of the other bands
-  int32_t nacross = 0;                 // their tile columns, over [xa, xb)
-  int32_t strips = 0, rows = 0, nseg = 0;
-  int32_t fl = 0, fr = 0;              // a front starts at x = 0, at nx - 1
-  int32_t nfl = 0, nfr = 0, frows = 1, fseg = 0;
-  int32_t nt = 0;
-  // 1: the lattice (the batch) goes by single steps where a sweep holds a
-  // wave of more than chain_max rows with solves
-  int32_t gated = 0, chain_max = 0;
-  // strips of w columns
-  void cut(int w) {
-    strips = (xb - xa + w - 1) / w;
-    nfl = fl && strips > 0 ? 1 : 0;
-    nfr = fr && strips > nfl ? 1 : 0;
-  }
-  __host__ __device__ int64_t tiles() const {
-    return (int64_t)(nleft + nright) * nside +
-           (int64_t)(nbottom + ntop) * nacross;
-  }
-  __host__ __device__ int64_t waves() const {
-    return (int64_t)(nfl + nfr) * fseg + (int64_t)(strips - nfl - nfr) * nseg;
-  }
-  __host__ __device__ int64_t slots() const { return tiles() + waves(); }
-};
 
 // the tile t of the frame
 __device__ __forceinline__ void frame_tile_of(const SweepPlan &P, int nx,
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(sweep_waves(Q, sizeof(S), K))))
 void sweep_kernel(StepArgs A, SweepPlan P, char *mid, int64_t mid_stride) {
   __shared__ S lds[Q * kFrameSide * kFrameSide];
-  if (!on_route(A.ctl, 0)) return;
+  if (P.ctl && !on_route(P.ctl, 0)) return;
   const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
   const int nt = (int)P.tiles(), nw = (int)P.waves();
   const int ct = (nt + 7) >> 3, cw = (((nw + 7) >> 3) + 3) & ~3;
@@ -405,7 +407,7 @@ void sweep_kernel(StepArgs A, SweepPlan P, char *mid, int64_t mid_stride) {
   int x0, x1, y0, y1;
   sweep_wave_of(P, k, 64 - 2 * K, x0, x1, y0, y1);
   sweep_body<Q, S, base_mode(MODE), K, MID>(
-      A, to_global((const S *)A.src), to_global((S *)A.dst), x0, x1, y0, y1,
+      A, P, to_global((const S *)A.src), to_global((S *)A.dst), x0, x1, y0, y1,
       P.nt != 0, mid, mid_stride, A.slots + nt + k);
 }
 
@@ -422,7 +424,7 @@ void batch_sweep_kernel(const StepArgs *__restrict__ descs,
                         const int2 *__restrict__ waves, int32_t nw,
                         int32_t parity, RouteCtl *ctl) {
   __shared__ S lds[Q * kFrameSide * kFrameSide];
-  if (!on_route(ctl, 0)) return;
+  if (ctl && !on_route(ctl, 0)) return;
   const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
   const int ct = (nt + 7) >> 3, cw = (((nw + 7) >> 3) + 3) & ~3;
   if (j < ct) {
@@ -453,7 +455,7 @@ void batch_sweep_kernel(const StepArgs *__restrict__ descs,
   int x0, x1, y0, y1;
   sweep_wave_of(P, k, 64 - 2 * P.k, x0, x1, y0, y1);
   sweep_body<Q, S, MODE, K, false>(
-      A, to_global((const S *)(parity ? A.dst : A.src)),
+      A, P, to_global((const S *)(parity ? A.dst : A.src)),
       to_global((S *)(parity ? A.src : A.dst)), x0, x1, y0, y1, P.nt != 0,
       nullptr, 0, A.slots + (int)P.tiles() + k);
 }
