@@ -206,9 +206,11 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
 }
 
 // Where a front stands off the walls, the waves that hold it solve in every
-// row, one after the other, about 6 us a row at the slowest lane: a chain of
-// k rows + k (k - 1) of them per launch, against k single steps that each
-// pass over the state at 5 TB/s.  us per step, sweeps with the front in the
+// row, one after the other, 2 to 4 us a row at the slowest lane, on top of the
+// sweep's own time: a chain of k rows + k (k - 1) of them per launch, against
+// k single steps that each pass over the state at 5 TB/s.  The sweep itself
+// takes 0.37 of those on lattices of 60 us a step and more, 0.5 to 0.6 below,
+// which leaves 0.16 and 0.105 rows for every us.  us per step, sweeps with the front in the
 // frame / at column 100 / half way / single steps, half way: 900 x 700 D2Q9
 // FP64 10 / 40 / 47 / 21, 2048^2 D2Q5 FP32 18 / 58 / 71 / 38, 4096^2 68 / 142
 // / 199 / 151, 2048^2 D2Q9 FP64 50 / 98 / 129 / 134, 8192^2 D2Q9 FP32 344 /
@@ -221,8 +223,8 @@ inline void route_lattice(SweepPlan *P, const lbm_stefan_params &p, int frows) {
   if (P->k == 0 || p.scheme != LBM_SCHEME_IREBM) return;
   const double step_us = 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) *
                          (double)p.nx * (double)p.ny / 5e6;
-  P->chain_max = (int32_t)(P->k * step_us / 6.0 < 1e6 ? P->k * step_us / 6.0
-                                                      : 1e6);
+  const double rows = P->k * step_us * (step_us >= 60.0 ? 0.16 : 0.105);
+  P->chain_max = (int32_t)(rows < 1e6 ? rows : 1e6);
   P->gated = P->k * P->rows + P->k * (P->k - 1) > P->chain_max;
   if (P->k * frows + P->k * (P->k - 1) > P->chain_max) {
     P->fl = P->fr = 0;

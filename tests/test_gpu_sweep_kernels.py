@@ -62,8 +62,8 @@ def test_newton_modes_and_neumann_walls(q, storage, nx, ny, mode):
 
 # lattices on which a sweep never costs more than single steps (low ones have
 # short segments): their forward tapes and recomputed states are swept
-ALWAYS = [(9, "f64", 4700, 520), (5, "f64", 8300, 500), (9, "f32", 9100, 520),
-          (5, "f32", 16500, 510)]
+ALWAYS = [(9, "f64", 4700, 520), (5, "f64", 9000, 500), (9, "f32", 9100, 520),
+          (5, "f32", 17500, 510)]
 
 
 @pytest.mark.parametrize("q,storage,nx,ny", ALWAYS)
