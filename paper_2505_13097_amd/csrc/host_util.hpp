@@ -318,9 +318,15 @@ inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
 // node's chain per wave: 201^2 D2Q5 FP64 freezing 12.4 -> 9.2 us per step,
 // 512^2 D2Q9 FP64 14.0 -> 11.5, 1001 x 777 23.3 -> 21.5; FP32 512^2 D2Q5
 // 8.3 -> 7.5, 1001 x 777 11.5 against 13.1), 128 x 4 tiles with two nodes
-// per thread (kDefaultVariant2D) above.
-inline int one_step_default(size_t s, int64_t nodes) {
-  return nodes <= (s == 8 ? 1200000 : 400000) ? 20 : kDefaultVariant2D;
+// per thread (kDefaultVariant2D) above, and where there are many rows: those
+// deal the columns at x = 0 out, so that a front there falls into one wave of
+// four rows instead of one a row (64 x 1 against 128 x 4: 215 x 1838 D2Q5 FP32
+// 11.5 / 9.2, 100 x 3000 11.8 / 10.4, 300 x 700 7.9 / 8.0; FP64 11 x 22757
+// D2Q9 56 / 42, 130 x 6000 43.7 / 39.0 freezing, 64 x 4000 17.3 / 18.8).
+inline int one_step_default(size_t s, int64_t nodes, int64_t ny) {
+  const bool small = s == 8 ? nodes <= 1200000 && ny <= 5000
+                            : nodes <= 350000 && ny <= 800;
+  return small ? 20 : kDefaultVariant2D;
 }
 
 // doubles of scratch that stats_async needs for n slots

@@ -127,7 +127,7 @@ int variant_3d(const lbm_stefan_params &p, int v) {
 }
 
 int default_2d(const lbm_stefan_params &p) {
-  return one_step_default(p.storage == LBM_STORE_F64 ? 8 : 4, nodes_of(p));
+  return one_step_default(p.storage == LBM_STORE_F64 ? 8 : 4, nodes_of(p), p.ny);
 }
 
 }  // namespace

@@ -112,7 +112,7 @@ int lbm_stefan_step_noalloc(const lbm_stefan_params *p, const void *src,
     // handle)
     const Variant *vt = variants(q.q, &nv);
     int vi = q.variant;
-    const int dflt = one_step_default(q.storage == LBM_STORE_F64 ? 8 : 4, nodes);
+    const int dflt = one_step_default(q.storage == LBM_STORE_F64 ? 8 : 4, nodes, q.ny);
     if (vi < 0) vi = q.dim == 1 ? kDefaultVariant1D : dflt;
     if (vt[vi].tb || vt[vi].lib) vi = dflt;
     if (vt[vi].res) vi = kDefaultVariant1D;

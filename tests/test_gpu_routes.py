@@ -253,3 +253,28 @@ def test_batch_routes_equal_single_steps(graph, at):
                 assert abs(sa[f] - sb[f]) <= bar, (q, storage, k, f)
         a.close()
         ref.close()
+
+
+# ------------------------------------------------- lattices of unequal sides
+
+def _default_against(prob, name="128x4/npt2"):
+    v = variant_names(prob.q, prob.storage).index(name)
+    t = []
+    for k in (-1, v):
+        g = Stefan(prob, variant=k)
+        t.append(_us(g, torch.from_numpy(g.state()).cuda()))
+        g.close()
+    print(f"{prob.nx}x{prob.ny} q{prob.q} {prob.storage} {prob.scheme}: "
+          f"default {t[0]:.1f} us per step, {name} {t[1]:.1f}", flush=True)
+    return t
+
+
+@pytest.mark.parametrize("nx,ny,q,storage", [
+    (11, 22757, 5, "f32"), (11, 22757, 9, "f64"), (8, 33760, 5, "f32"),
+    (215, 1838, 5, "f32"), (40, 4700, 9, "f32")])
+def test_tall_lattices_take_tiles_of_several_rows(nx, ny, q, storage):
+    """a hot wall along many rows: the default against 128 x 4 tiles, 1.2
+    times those (a wave a row took 1.25 to 1.6 times)"""
+    a, b = _default_against(_prob(nx, ny, q, storage,
+                                  _field(nx, ny, min(8, nx // 2))))
+    assert a <= 1.2 * b
