@@ -98,7 +98,7 @@ inline void set_tiling(StepArgs *A, const Variant &v) {
 }
 
 // LDS a block of tile_kernel may take: what a launch gets unasked (the
-// largest tile, 22 x 22 nodes of D2Q9 FP64, takes 35 KB)
+// largest tile, 20 x 20 nodes of D2Q9 FP64, takes 29 KB)
 constexpr size_t kTileLds = 64 * 1024;
 
 // The library's choice for tile_kernel on an nx x ny lattice (q populations
@@ -112,7 +112,9 @@ constexpr size_t kTileLds = 64 * 1024;
 //   (k 4, side 8), 201^2 9.1 -> 6.2, 301^2 9.7 -> 7.8 (3, 10), 351^2 10.0 ->
 //   8.8 (2, 12), 401^2 10.4 -> 10.8.
 //   EEBM: no solve, so more steps: 101^2 4.5 -> 2.5 (6, 8), 201^2 4.8 -> 2.7
-//   (4, 8), 301^2 5.5 -> 3.3, 512^2 7.0 -> 5.5 (4, 14).
+//   (4, 8).  Above 60000 nodes only lattices too thin for a strip are left,
+//   and their tiles are mostly wall: single steps (22757 x 11 D2Q9 FP32 12.5
+//   in tiles of 14, 7.4 so, 27837 x 4 12.4 against 6.3).
 inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
                           int64_t ny) {
   const int64_t n = nx * ny;
@@ -124,7 +126,6 @@ inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
   } else {
     if (n <= 15000) k = 6, side = 8;
     else if (n <= 60000) k = 4, side = 8;
-    else if (n <= 400000) k = 4, side = 14;
   }
   TilePlan P;
   if (k == 0) return P;

@@ -278,3 +278,14 @@ def test_tall_lattices_take_tiles_of_several_rows(nx, ny, q, storage):
     a, b = _default_against(_prob(nx, ny, q, storage,
                                   _field(nx, ny, min(8, nx // 2))))
     assert a <= 1.2 * b
+
+
+@pytest.mark.parametrize("nx,ny,q,storage", [
+    (22757, 11, 9, "f32"), (27837, 4, 9, "f64"), (64, 4000, 9, "f32"),
+    (5000, 4, 9, "f32"), (3000, 20, 5, "f64")])
+def test_thin_lattices_of_the_explicit_scheme(nx, ny, q, storage):
+    """too thin for a strip, large and small: the default against 128 x 4
+    tiles, 1.2 times those (tiles in LDS took 1.3 to 1.7 times on the large)"""
+    a, b = _default_against(_prob(nx, ny, q, storage, _field(
+        nx, ny, 8)).with_(scheme="eebm"))
+    assert a <= 1.2 * b

@@ -218,7 +218,7 @@ def tile_plan(q, eebm, nx, ny):
     n = nx * ny
     if eebm:
         k, side = ((6, 8) if n <= 15000 else (4, 8) if n <= 60000 else
-                   (4, 14) if n <= 400000 else (0, 0))
+                   (0, 0))
     else:
         k, side = ((4, 8) if n <= 30000 else (3, 10) if n <= 110000 else
                    (2, 12) if n <= 130000 else (0, 0))
@@ -232,6 +232,9 @@ def tile_plan(q, eebm, nx, ny):
                                    (40, 33), (173, 173), (331, 331)])
 @pytest.mark.parametrize("eebm", [False, True])
 def test_tile_kernel(nx, ny, eebm):
+    if eebm and nx * ny > 60000:
+        assert tile_plan(9, eebm, nx, ny) is None
+        return
     k, ntx, nty, rx, ry = tile_plan(9, eebm, nx, ny)
     assert rx * ry <= 1024 and rx * ry * 9 * 8 <= 65536
     boxes = [(c * nx // ntx, (c + 1) * nx // ntx, r * ny // nty,
