@@ -40,8 +40,8 @@ struct lbm_stefan_batch {
   int mode = kSafeguarded;  // node-update mode shared by the instances
   int device = 0, cus = 0;
   hipStream_t stream = nullptr, cap_stream = nullptr;
-  // sweeps of IREBM lattices: the single steps' launches on a stream of
-  // their own, forked from and joined back into the launching stream
+  // sweeps of IREBM lattices: the single steps' launches of a large batch go
+  // on a stream of their own, forked from and joined into the launching one
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
   char *ws = nullptr;
@@ -53,6 +53,7 @@ struct lbm_stefan_batch {
   RouteCtl *route = nullptr;
   int2 *singles = nullptr;     // the single steps' items beside sweeps
   int64_t nsingles = 0;
+  bool beside = false;         // ... on a stream of their own (kRouteBeside)
   int32_t chain_max = 0;       // what sweeps may hold (RouteCtl)
   unsigned long long units_max = 0;
   int64_t nparts = 0;          // energy chunks of all instances
@@ -104,11 +105,11 @@ int64_t batch_slots(const Variant &v, const lbm_stefan_params &p) {
 // Do two-step variants of a batch sweep?  The frame's tiles compute each node
 // up to four times over, and lattices too small for a strip are all tiles, so
 // the batch takes single steps (the default tiling) where more than 0.3 of its
-// nodes lie in frames, EEBM 0.45 (us per step, single steps / sweeps: 1000
+// nodes lie in frames, EEBM 0.35 (us per step, single steps / sweeps: 1000
 // FP32 D2Q5 lattices of 64^2 80 / 205, EEBM 46 / 66; 600 FP64 D2Q9 ones 131 /
 // 269; 500 FP32 D2Q9 ones of 87^2 119 / 204; 100 FP64 D2Q5 ones of 150^2, 0.26
 // in frames, 58 / 49; 60 FP64 D2Q9 ones of 200^2 107 / 73; EEBM 110^2, 0.27,
-// 40 / 22).
+// 40 / 22, 70 FP64 D2Q5 ones of about 1600 x 30, 0.4, 42 / 47).
 bool batch_sweeps(const lbm_stefan_params *ps, int count) {
   int nv;
   const Variant &v = variants(ps[0].q, &nv)[kSweepVariant2D];
@@ -118,7 +119,7 @@ bool batch_sweeps(const lbm_stefan_params *ps, int count) {
     all += (double)ps[k].nx * ps[k].ny;
     strips += (double)(P.xb - P.xa) * (P.yb - P.ya);
   }
-  return all - strips <= (ps[0].scheme == LBM_SCHEME_EEBM ? 0.45 : 0.3) * all;
+  return all - strips <= (ps[0].scheme == LBM_SCHEME_EEBM ? 0.35 : 0.3) * all;
 }
 
 // what variant v of a batch runs as
@@ -259,19 +260,24 @@ void drop_graphs(lbm_stefan_batch_t *b) {
 }
 
 // What the sweeps of up to K steps may hold before the batch goes by single
-// steps, which pass over the states (`bytes` in and out) at 4 TB/s.  A wave
-// takes 6 us a row with solves (route_lattice); all such rows together may
-// come to 0.65 of those steps' time (route_units; at 0.5 the first batch below
-// leaves the sweeps at column 64, at 0.9 it never does).  us per step, single steps / sweeps with the
-// front at column 8, 24, 64, 100, half way: 48 FP32 D2Q5 lattices of 64^2 to
-// 1024^2 272 / 121, 158, 213, 267, 310; 12 D2Q9 ones of 512^2 to 1024^2 150 /
-// 65, 89, 146, 171, 189; 400 D2Q5 ones of 64^2 to 256^2 188 to 231 / 178, 241,
-// 361, 343, 364; 24 FP64 D2Q9 ones of 64^2 to 1024^2 384 / 156, 167, 203, 288,
-// 376.
+// steps, which pass over the states (`bytes` in and out) at 4 TB/s: in one
+// wave 0.105 (FP64) or 0.155 (FP32) rows with solves for every us of those
+// (route_lattice); all such rows together may come to 0.65 of those steps'
+// time (route_units; at 0.5 the first batch below leaves the sweeps at column
+// 64, at 0.9 it never does).  us per step, single steps / sweeps with the front
+// at column 8, 24, 64, 100, half way: 48 FP32 D2Q5 lattices of 64^2 to 1024^2
+// 272 / 121, 158, 213, 267, 310; 12 D2Q9 ones of 512^2 to 1024^2 150 / 65, 89,
+// 146, 171, 189; 400 D2Q5 ones of 64^2 to 256^2 188 to 231 / 178, 241, 361, 343,
+// 364; 24 FP64 D2Q9 ones of 64^2 to 1024^2 384 / 156, 167, 203, 288, 376; 43
+// FP64 D2Q5 ones of up to 753 x 690, half way, 245 / 313; 11 of about 1200 x 900
+// 235 / 280.
 void set_batch_route(lbm_stefan_batch_t *b, int K, double bytes) {
   const double us = K * bytes / 4e6;
-  b->chain_max = (int32_t)std::min(us / 6.0, 1e6);
-  b->units_max = (unsigned long long)(0.65 * us * 1e3 / 0.45);
+  // ns of a unit (route_units)
+  const double ns = b->storage == LBM_STORE_F64 ? 0.65 : 0.45;
+  const double rows = us * (b->storage == LBM_STORE_F64 ? 0.105 : 0.155);
+  b->chain_max = (int32_t)std::min(rows, 1e6);
+  b->units_max = (unsigned long long)(0.65 * us * 1e3 / ns);
 }
 
 // descriptors and item table for the current variant; uploads both and
@@ -293,6 +299,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
   int64_t sbase = 0;
   b->nparts = 0;
   double bytes = 0.0;
+  int64_t nodes = 0;
   for (int k = 0; k < b->count; ++k) {
     const lbm_stefan_params &p = b->ps[k];
     double *prof[4];
@@ -304,6 +311,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
     d[k].src = b->state[0] + b->off[k];
     d[k].dst = b->state[1] + b->off[k];
     set_tiling(&d[k], two ? vt[kDefaultVariant2D] : v);
+    nodes += p.nx * p.ny;
     bytes += 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) * p.nx * p.ny;
     for (int i = 0; two && i < d[k].nitems; ++i) sg.push_back(make_int2(k, i));
     const int64_t n = batch_slots(v, p);
@@ -331,6 +339,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
   t.insert(t.end(), wv.begin(), wv.end());
   b->nitems = (int64_t)t.size();
   b->nsingles = (int64_t)sg.size();
+  b->beside = nodes > kRouteBeside;
   set_batch_route(b, 4, bytes);
   BCHK(b, hipMemcpyAsync(b->descs, d.data(), d.size() * sizeof(StepArgs),
                          hipMemcpyHostToDevice, b->stream));
@@ -339,7 +348,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
   if (two)
     BCHK(b, hipMemcpyAsync(b->singles, sg.data(), sg.size() * sizeof(int2),
                            hipMemcpyHostToDevice, b->stream));
-  if (two && !b->side) {
+  if (two && b->beside && !b->side) {
     BCHK(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
     BCHK(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
     BCHK(b, hipEventCreateWithFlags(&b->join, hipEventDisableTiming));
@@ -428,18 +437,20 @@ hipError_t advance_batch(const lbm_stefan_batch_t *b, hipStream_t stream,
       nsteps--;
       continue;
     }
-    e = hipEventRecord(b->fork, stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->fork, 0);
+    if (b->beside) e = hipEventRecord(b->fork, stream);
+    if (b->beside && e == hipSuccess)
+      e = hipStreamWaitEvent(b->side, b->fork, 0);
     int p = *parity, c = *parity;
     for (int64_t i = 0, left = n; i < m && e == hipSuccess; ++i, p ^= 1) {
       const int64_t k = (left + m - i - 1) / (m - i);
       e = launch_batch(b, stream, p, (int)k, b->route);
       for (int64_t j = 0; j < k && e == hipSuccess; ++j, c ^= 1)
-        e = launch_single(b, b->side, c, b->route);
+        e = launch_single(b, b->beside ? b->side : stream, c, b->route);
       left -= k;
     }
-    if (e == hipSuccess) e = hipEventRecord(b->join, b->side);
-    if (e == hipSuccess) e = hipStreamWaitEvent(stream, b->join, 0);
+    if (b->beside && e == hipSuccess) e = hipEventRecord(b->join, b->side);
+    if (b->beside && e == hipSuccess)
+      e = hipStreamWaitEvent(stream, b->join, 0);
     if (e != hipSuccess) break;
     // (units add up over the group's launches)
     route_decide_kernel<<<1, 1, 0, stream>>>(b->route, 0, b->chain_max,
