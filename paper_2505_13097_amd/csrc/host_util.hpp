@@ -112,14 +112,17 @@ constexpr size_t kTileLds = 64 * 1024;
 //   (k 4, side 8), 201^2 9.1 -> 6.2, 301^2 9.7 -> 7.8 (3, 10), 351^2 10.0 ->
 //   8.8 (2, 12), 401^2 10.4 -> 10.8.
 //   EEBM: no solve, so more steps: 101^2 4.5 -> 2.5 (6, 8), 201^2 4.8 -> 2.7
-//   (4, 8).  Above 60000 nodes only lattices too thin for a strip are left,
-//   and their tiles are mostly wall: single steps (22757 x 11 D2Q9 FP32 12.5
-//   in tiles of 14, 7.4 so, 27837 x 4 12.4 against 6.3).
+//   (4, 8); larger ones sweep.
+// Thin lattices take single steps above 60000 nodes (tiles / so: EEBM 22757 x
+// 11 D2Q9 FP32 12.5 / 7.4, 27837 x 4 12.4 / 6.3; IREBM 33 x 2946 melted 12.4 /
+// 9.0, 35 x 2878 freezing 11.4 / 10.5, 25812 x 4 12.1 / 10.9).
 inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
                           int64_t ny) {
   const int64_t n = nx * ny;
   int k = 0, side = 0;
-  if (!eebm) {
+  if (n > 60000 && (nx < 64 || ny < 64)) {
+    // thin lattices: tiles that are mostly wall
+  } else if (!eebm) {
     if (n <= 30000) k = 4, side = 8;
     else if (n <= 110000) k = 3, side = 10;
     else if (n <= 130000) k = 2, side = 12;
@@ -322,11 +325,12 @@ inline SweepPlan sweep_variant(const lbm_stefan_params &p, const Variant &v) {
 // per thread (kDefaultVariant2D) above, and where there are many rows: those
 // deal the columns at x = 0 out, so that a front there falls into one wave of
 // four rows instead of one a row (64 x 1 against 128 x 4: 215 x 1838 D2Q5 FP32
-// 11.5 / 9.2, 100 x 3000 11.8 / 10.4, 300 x 700 7.9 / 8.0; FP64 11 x 22757
-// D2Q9 56 / 42, 130 x 6000 43.7 / 39.0 freezing, 64 x 4000 17.3 / 18.8).
+// 11.5 / 9.2, 100 x 3000 11.8 / 10.4, 300 x 700 7.9 / 8.0, melted 9.0 / 8.6;
+// FP64 D2Q9 11 x 22757 56 / 42, 130 x 6000 43.7 / 39.0 freezing, 62 x 1951 15.9
+// / 13.8 freezing, 64 x 4000 17.3 / 18.8).
 inline int one_step_default(size_t s, int64_t nodes, int64_t ny) {
-  const bool small = s == 8 ? nodes <= 1200000 && ny <= 5000
-                            : nodes <= 350000 && ny <= 800;
+  const bool small = s == 8 ? nodes <= 1200000 && ny <= 1500
+                            : nodes <= 350000 && ny <= 600;
   return small ? 20 : kDefaultVariant2D;
 }
 

@@ -271,7 +271,7 @@ def _default_against(prob, name="128x4/npt2"):
 
 @pytest.mark.parametrize("nx,ny,q,storage", [
     (11, 22757, 5, "f32"), (11, 22757, 9, "f64"), (8, 33760, 5, "f32"),
-    (215, 1838, 5, "f32"), (40, 4700, 9, "f32")])
+    (215, 1838, 5, "f32"), (40, 4700, 9, "f32"), (62, 1951, 9, "f64")])
 def test_tall_lattices_take_tiles_of_several_rows(nx, ny, q, storage):
     """a hot wall along many rows: the default against 128 x 4 tiles, 1.2
     times those (a wave a row took 1.25 to 1.6 times)"""
@@ -288,4 +288,13 @@ def test_thin_lattices_of_the_explicit_scheme(nx, ny, q, storage):
     tiles, 1.2 times those (tiles in LDS took 1.3 to 1.7 times on the large)"""
     a, b = _default_against(_prob(nx, ny, q, storage, _field(
         nx, ny, 8)).with_(scheme="eebm"))
+    assert a <= 1.2 * b
+
+
+@pytest.mark.parametrize("nx,ny,q,storage,at", [
+    (33, 2946, 9, "f32", 60), (35, 2878, 5, "f32", 8), (25812, 4, 9, "f32", 60),
+    (20, 2900, 5, "f32", 8)])
+def test_thin_lattices(nx, ny, q, storage, at):
+    """the same with solves, melted and not, the last below the tiles' limit"""
+    a, b = _default_against(_prob(nx, ny, q, storage, _field(nx, ny, at)))
     assert a <= 1.2 * b

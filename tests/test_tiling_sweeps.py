@@ -216,6 +216,8 @@ def test_batch_lattices_of_tiles_alone(nx, ny, px):
 
 def tile_plan(q, eebm, nx, ny):
     n = nx * ny
+    if n > 60000 and min(nx, ny) < 64:
+        return None
     if eebm:
         k, side = ((6, 8) if n <= 15000 else (4, 8) if n <= 60000 else
                    (0, 0))
