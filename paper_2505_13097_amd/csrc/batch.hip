@@ -85,8 +85,15 @@ struct BLayout {
 };
 
 // work items (and statistics slots) of an instance under variant v
-int64_t batch_items(const Variant &v, const lbm_stefan_params &p) {
-  return v.tb ? batch_plan(p, v).slots() : items_for(v, p.nx, p.ny);
+int64_t batch_items(const Variant &v, const lbm_stefan_params &p,
+                    int64_t nodes) {
+  return v.tb ? batch_plan(p, v, nodes).slots() : items_for(v, p.nx, p.ny);
+}
+
+int64_t batch_nodes(const lbm_stefan_params *ps, int count) {
+  int64_t nodes = 0;
+  for (int k = 0; k < count; ++k) nodes += ps[k].nx * ps[k].ny;
+  return nodes;
 }
 
 // do batches of p sweep by groups (RouteCtl)?
@@ -94,9 +101,10 @@ bool routed(const Variant &v, const lbm_stefan_params &p) {
   return v.tb && p.scheme == LBM_SCHEME_IREBM;
 }
 // statistics slots of an instance under variant v
-int64_t batch_slots(const Variant &v, const lbm_stefan_params &p) {
+int64_t batch_slots(const Variant &v, const lbm_stefan_params &p,
+                    int64_t nodes) {
   int nv;
-  const int64_t n = batch_items(v, p);
+  const int64_t n = batch_items(v, p, nodes);
   if (!routed(v, p)) return n;
   return std::max(n, items_for(variants(p.q, &nv)[kDefaultVariant2D], p.nx,
                                p.ny));
@@ -113,10 +121,10 @@ int64_t batch_slots(const Variant &v, const lbm_stefan_params &p) {
 bool batch_sweeps(const lbm_stefan_params *ps, int count) {
   int nv;
   const Variant &v = variants(ps[0].q, &nv)[kSweepVariant2D];
-  double all = 0.0, strips = 0.0;
+  const int64_t all = batch_nodes(ps, count);
+  double strips = 0.0;
   for (int k = 0; k < count; ++k) {
-    const SweepPlan P = batch_plan(ps[k], v);
-    all += (double)ps[k].nx * ps[k].ny;
+    const SweepPlan P = batch_plan(ps[k], v, all);
     strips += (double)(P.xb - P.xa) * (P.yb - P.ya);
   }
   return all - strips <= (ps[0].scheme == LBM_SCHEME_EEBM ? 0.35 : 0.3) * all;
@@ -135,8 +143,7 @@ int run_variant(const lbm_stefan_params *ps, int count, int v) {
 // sweep_nodes, sweep_default)
 int default_variant(const lbm_stefan_params *ps, int count) {
   if (ps[0].q == 3) return kDefaultVariant1D;
-  int64_t nodes = 0;
-  for (int k = 0; k < count; ++k) nodes += ps[k].nx * ps[k].ny;
+  const int64_t nodes = batch_nodes(ps, count);
   if (ps[0].scheme == LBM_SCHEME_IREBM && nodes <= sweep_nodes(ps[0].storage))
     return kDefaultVariant2D;
   for (int k = 0; k < count; ++k) {
@@ -189,10 +196,11 @@ BLayout batch_layout(const lbm_stefan_params *ps, int32_t count) {
   const size_t s = ps[0].storage == LBM_STORE_F64 ? 8 : 4;
   int nv;
   const Variant *v = variants(ps[0].q, &nv);
+  const int64_t nodes = batch_nodes(ps, count);
   L.max_items = 0;
   for (int i = 0; i < nv; ++i) {
     int64_t t = 0;
-    for (int k = 0; k < count; ++k) t += batch_slots(v[i], ps[k]);
+    for (int k = 0; k < count; ++k) t += batch_slots(v[i], ps[k], nodes);
     L.max_items = std::max(L.max_items, t);
   }
   L.max_parts = 0;
@@ -299,7 +307,7 @@ int build_schedule(lbm_stefan_batch_t *b) {
   int64_t sbase = 0;
   b->nparts = 0;
   double bytes = 0.0;
-  int64_t nodes = 0;
+  const int64_t nodes = batch_nodes(b->ps.data(), b->count);
   for (int k = 0; k < b->count; ++k) {
     const lbm_stefan_params &p = b->ps[k];
     double *prof[4];
@@ -311,14 +319,13 @@ int build_schedule(lbm_stefan_batch_t *b) {
     d[k].src = b->state[0] + b->off[k];
     d[k].dst = b->state[1] + b->off[k];
     set_tiling(&d[k], two ? vt[kDefaultVariant2D] : v);
-    nodes += p.nx * p.ny;
     bytes += 2.0 * p.q * (p.storage == LBM_STORE_F64 ? 8 : 4) * p.nx * p.ny;
     for (int i = 0; two && i < d[k].nitems; ++i) sg.push_back(make_int2(k, i));
-    const int64_t n = batch_slots(v, p);
+    const int64_t n = batch_slots(v, p, nodes);
     d[k].slots = b->slots + sbase;
     b->first_item[k] = sbase;
     if (v.tb) {
-      pl[k] = batch_plan(p, v);
+      pl[k] = batch_plan(p, v, nodes);
       pl[k].ctl = two ? b->route : nullptr;
       for (int64_t i = 0; i < pl[k].tiles(); ++i)
         t.push_back(make_int2(k, (int)i));
@@ -822,6 +829,7 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
   int nv;
   const Variant *vt = variants(b->q, &nv);
   const int bpcs[] = {0, 2, 4, 8};
+  const int64_t nodes = batch_nodes(b->ps.data(), b->count);
   const int v0 = b->variant, bpc0 = b->blocks_per_cu;
   int best_v = v0, best_bpc = bpc0;
   float best_ms = -1.0f;
@@ -834,7 +842,8 @@ int lbm_stefan_batch_autotune(lbm_stefan_batch_t *b, void *scratch,
     // two-step variants differ by their segments' rows alone
     bool tried = false;
     for (int u = 0; u < v && vt[v].tb; ++u)
-      tried |= vt[u].tb && batch_rows(vt[u]) == batch_rows(vt[v]) &&
+      tried |= vt[u].tb &&
+               batch_rows(vt[u], nodes) == batch_rows(vt[v], nodes) &&
                vt[u].nt == vt[v].nt;
     if (tried) continue;
     if (v != b->variant) {

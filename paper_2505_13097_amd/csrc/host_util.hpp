@@ -285,14 +285,22 @@ inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   return P;
 }
 
-// An instance of a batch under a two-step variant: its plan, or tiles alone
-// where no strip fits.  Segments of at most 32 rows: 48 FP32 D2Q5 lattices of
-// 64^2 to 1024^2 take 505 us per four steps with 32 and 64 rows, 560 with 16
-// and 128 (two-step launches of step2_kernel, split by quiet and solving
-// items, took 1040).
-inline int batch_rows(const Variant &v) { return v.rows < 32 ? v.rows : 32; }
-inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v) {
-  SweepPlan P = sweep_plan(p, 4, batch_rows(v), 8, v.nt != 0);
+// Rows per segment in a batch of `nodes` nodes under a two-step variant: its
+// own, at most 32 (48 FP32 D2Q5 lattices of 64^2 to 1024^2 take 505 us per four
+// steps with 32 and 64 rows, 560 with 16 and 128; two-step launches of
+// step2_kernel, split by quiet and solving items, took 1040), and fewer in
+// small batches, which leave the chip short of waves otherwise (6 EEBM lattices
+// of 600 x 45, 9.0 us per step with 32 rows, 3.8 with 8, single steps 6.8).
+inline int batch_rows(const Variant &v, int64_t nodes) {
+  const int64_t most = nodes / 229376 / 4 * 4;   // (56 columns, 4096 waves)
+  const int64_t rows = most < 8 ? 8 : (most > 32 ? 32 : most);
+  return (int)(v.rows < rows ? v.rows : rows);
+}
+
+// An instance of such a batch: its plan, or tiles alone where no strip fits.
+inline SweepPlan batch_plan(const lbm_stefan_params &p, const Variant &v,
+                            int64_t nodes) {
+  SweepPlan P = sweep_plan(p, 4, batch_rows(v, nodes), 8, v.nt != 0);
   if (P.k > 0) return P;
   P.k = 4;
   P.tile = frame_tile(4);

@@ -298,3 +298,17 @@ def test_thin_lattices(nx, ny, q, storage, at):
     """the same with solves, melted and not, the last below the tiles' limit"""
     a, b = _default_against(_prob(nx, ny, q, storage, _field(nx, ny, at)))
     assert a <= 1.2 * b
+
+
+@pytest.mark.parametrize("scheme", ["irebm", "eebm"])
+def test_small_batches(scheme):
+    """few lattices: the default and a two-step variant against single steps,
+    1.25 times those (segments of 32 rows took 1.3 times)"""
+    names = variant_names(9, "f32")
+    probs = [p.with_(scheme=scheme, bc=(D, D, P, P))
+             for p in _batch([(600, 45)], 9, "f32", 8)] * 6
+    t = [_batch_us(probs, v) for v in (-1, names.index("128x2/t2s/r96/nt"),
+                                       names.index("128x4/npt2"))]
+    print(f"6 of 600 x 45 {scheme}: default {t[0]:.1f} us per step, two-step "
+          f"variant {t[1]:.1f}, single steps {t[2]:.1f}", flush=True)
+    assert max(t[:2]) <= 1.25 * t[2]
