@@ -310,10 +310,13 @@ __global__ __launch_bounds__(kTileThreads) void ilfbm_tile_kernel(
   }
 }
 
-// largest change and fluxes of a step, over its tiles in a fixed order
+// largest change and fluxes of a step, over its tiles in a fixed order; the
+// flags are clear again for the next step
 __global__ __launch_bounds__(256) void ilfbm_sum_kernel(const double *pend,
                                                         int64_t ntiles,
                                                         IlfCtrl *ctrl) {
+  if (threadIdx.x < kSets * kTileIt)
+    ctrl->open[threadIdx.x / kTileIt][threadIdx.x % kTileIt] = 0;
   double m = 0.0, fin = 0.0, fout = 0.0;
   for (int64_t b = threadIdx.x; b < ntiles; b += 256) {
     m = fmax(m, pend[3 * b]);
@@ -336,9 +339,11 @@ __global__ __launch_bounds__(256) void ilfbm_sum_kernel(const double *pend,
 // `nsteps` whole steps in one launch, block barriers in place of launches
 // and host reads.  (256 nodes, 48 iterations a step: 110 us per step either
 // way, 2000 nodes 280 here against 112 in tiles; a 2D iteration takes 14 us
-// here at any size, 24^2 D2Q9 1736 us per step against 486.)  Node updates and convergence decisions are those of
-// the multi-launch path (same ilfbm_node, exact max), so the states are
-// the same; only the flux sums are reduced in another order.  L[0] is the
+// here at any size, 24^2 D2Q9 1736 us per step against 486; only tiny ones that
+// take an iteration or two per step would be faster here, 45 x 20 19 us against
+// 36.)  Node updates and convergence decisions are those of the multi-launch
+// path (same ilfbm_node, exact max), so the states are the same; only the flux
+// sums are reduced in another order.  L[0] is the
 // state's l plane, L[1] and L[2] the inner-loop planes; planes and buffers
 // rotate in registers, and the final assignment and statistics are
 // written to `res` for the host.
@@ -446,9 +451,7 @@ __global__ __launch_bounds__(kResident) void ilfbm_resident_kernel(
   }
 }
 
-__global__ void ilfbm_reset_kernel(IlfCtrl *ctrl) {
-  ctrl->open[threadIdx.x / kTileIt][threadIdx.x % kTileIt] = 0;
-}
+static_assert(kSets * kTileIt <= 256, "ilfbm_sum_kernel clears the flags");
 
 int64_t tiles_of(int64_t n, int side) { return (n + side - 1) / side; }
 int64_t iter_tiles(const lbm_stefan_params *p, int kk = kTileIt) {
@@ -464,7 +467,7 @@ size_t irebm::ilfbm_bytes(const lbm_stefan_params *p) {
          align256(sizeof(IlfCtrl));
 }
 
-void irebm::ilfbm_attach(lbm_stefan_t *h, char *base) {
+hipError_t irebm::ilfbm_attach(lbm_stefan_t *h, char *base) {
   const int64_t n = h->p.nx * h->p.ny;
   const size_t plane = align256((size_t)n * 8);
   h->lf = (double *)base;
@@ -473,6 +476,7 @@ void irebm::ilfbm_attach(lbm_stefan_t *h, char *base) {
   h->pend = (double *)(base + 3 * plane);
   h->ctrl = base + 3 * plane + align256((size_t)iter_tiles(&h->p) * 24);
   ilfbm_reset_stats(h);
+  return zero_async(h->ctrl, sizeof(IlfCtrl), h->stream);
 }
 
 void irebm::ilfbm_reset_stats(lbm_stefan_t *h) {
@@ -589,16 +593,17 @@ hipError_t irebm::ilfbm_advance(lbm_stefan_t *h, int64_t nsteps) {
         return hipGetLastError();
       });
     };
-    ilfbm_reset_kernel<<<1, kSets * kTileIt, 0, h->stream>>>(ctrl);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
     int64_t kf = 0, jf = 0;          // the last iteration and its launch
     bool done = false;
     for (int64_t j = 0; e == hipSuccess && !done && kf < cap;) {
       const int64_t j0 = j;
-      // (one launch where the last step's iterations fit into it)
-      const int64_t burst = j == 0 && k0 < kTileIt ? 1 : kBurst;
+      // (one launch where the last step's iterations fit into it, and one
+      // more where they just did not: 300^2 D2Q9 that takes 3 and 2 in turn
+      // 96 us per step, 80 so)
+      const int64_t burst = j <= 1 && k0 < kTileIt ? 1 : kBurst;
       for (; j < j0 + burst && from(j) < cap && e == hipSuccess; ++j)
-        e = launch(j, (int)(from(j + 1) - from(j)), burst == 1);
+        e = launch(j, (int)(from(j + 1) - from(j)), j == 0 && k0 < kTileIt);
       if (e == hipSuccess) e = read();
       if (e != hipSuccess) break;
       take();

@@ -751,8 +751,10 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
     StepArgs A;
     fill_step_args(h, &A);
     A.dst = h->buf[0];
-    if (p->scheme == LBM_SCHEME_ILFBM) ilfbm_attach(h, ws + L.off_lf);
-    ie = init_async(p->q, p->storage, A, T0d, h->stream, h->lf);
+    ie = p->scheme == LBM_SCHEME_ILFBM ? ilfbm_attach(h, ws + L.off_lf)
+                                       : hipSuccess;
+    if (ie == hipSuccess)
+      ie = init_async(p->q, p->storage, A, T0d, h->stream, h->lf);
   }
   if (ie == hipSuccess)
     ie = zero_async(h->route, sizeof(RouteCtl), h->stream);

@@ -130,7 +130,7 @@ int read_stats(lbm_stefan_t *h, lbm_stefan_stats *st);
 // ILFBM (ilfbm.hip): workspace bytes beyond the common layout, the
 // handle's pointers into it, and nsteps steps of the inner-loop scheme
 size_t ilfbm_bytes(const lbm_stefan_params *p);
-void ilfbm_attach(lbm_stefan_t *h, char *base);
+hipError_t ilfbm_attach(lbm_stefan_t *h, char *base);
 hipError_t ilfbm_advance(lbm_stefan_t *h, int64_t nsteps);
 void ilfbm_reset_stats(lbm_stefan_t *h);
 
