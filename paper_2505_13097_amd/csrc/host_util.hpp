@@ -113,15 +113,19 @@ constexpr size_t kTileLds = 64 * 1024;
 //   8.8 (2, 12), 401^2 10.4 -> 10.8.
 //   EEBM: no solve, so more steps: 101^2 4.5 -> 2.5 (6, 8), 201^2 4.8 -> 2.7
 //   (4, 8); larger ones sweep.
-// Thin lattices take single steps above 60000 nodes (tiles / so: EEBM 22757 x
-// 11 D2Q9 FP32 12.5 / 7.4, 27837 x 4 12.4 / 6.3; IREBM 33 x 2946 melted 12.4 /
-// 9.0, 35 x 2878 freezing 11.4 / 10.5, 25812 x 4 12.1 / 10.9).
+// Lattices too thin for a strip, above 60000 nodes: their tiles are mostly
+// wall.  With solves single steps (tiles / so: 33 x 2946 melted 12.4 / 9.0, 35
+// x 2878 freezing 11.4 / 10.5, 25812 x 4 12.1 / 10.9); without, tiles of 14 a
+// side up to 100000 nodes in rows of the lattice's length (3250 x 20 D2Q9 FP32
+// 4.4 / 5.5, 6500 x 20 6.8 / 6.1, 22757 x 11 12.5 / 7.4) and to 200000 where
+// rows are short and a wave's loads with them (20 x 6500 8.7 / 9.9, 57 x 1136
+// 4.3 / 6.8, 30 x 10000 15.8 / 12.9).
 inline TilePlan tile_plan(int q, size_t s, bool eebm, int64_t nx,
                           int64_t ny) {
   const int64_t n = nx * ny;
   int k = 0, side = 0;
   if (n > 60000 && (nx < 64 || ny < 64)) {
-    // thin lattices: tiles that are mostly wall
+    if (eebm && n <= (nx < 64 ? 200000 : 100000)) k = 4, side = 14;
   } else if (!eebm) {
     if (n <= 30000) k = 4, side = 8;
     else if (n <= 110000) k = 3, side = 10;

@@ -282,13 +282,23 @@ def test_tall_lattices_take_tiles_of_several_rows(nx, ny, q, storage):
 
 @pytest.mark.parametrize("nx,ny,q,storage", [
     (22757, 11, 9, "f32"), (27837, 4, 9, "f64"), (64, 4000, 9, "f32"),
-    (5000, 4, 9, "f32"), (3000, 20, 5, "f64")])
+    (5000, 4, 9, "f32"), (3000, 20, 5, "f64"), (8400, 12, 9, "f64"),
+    (20, 9900, 5, "f32"), (20, 10100, 5, "f32")])
 def test_thin_lattices_of_the_explicit_scheme(nx, ny, q, storage):
     """too thin for a strip, large and small: the default against 128 x 4
     tiles, 1.2 times those (tiles in LDS took 1.3 to 1.7 times on the large)"""
     a, b = _default_against(_prob(nx, ny, q, storage, _field(
         nx, ny, 8)).with_(scheme="eebm"))
     assert a <= 1.2 * b
+
+
+@pytest.mark.parametrize("nx,ny,q,storage", [
+    (57, 1136, 9, "f32"), (3250, 20, 9, "f64"), (20, 6500, 5, "f32")])
+def test_thin_lattices_of_tiles(nx, ny, q, storage):
+    """the same where tiles are ahead, by 1.1 to 1.6 times"""
+    a, b = _default_against(_prob(nx, ny, q, storage, _field(
+        nx, ny, 8)).with_(scheme="eebm"))
+    assert a <= 0.95 * b
 
 
 @pytest.mark.parametrize("nx,ny,q,storage,at", [

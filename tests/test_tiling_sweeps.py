@@ -217,8 +217,9 @@ def test_batch_lattices_of_tiles_alone(nx, ny, px):
 def tile_plan(q, eebm, nx, ny):
     n = nx * ny
     if n > 60000 and min(nx, ny) < 64:
-        return None
-    if eebm:
+        k, side = ((4, 14) if eebm and n <= (200000 if nx < 64 else 100000)
+                   else (0, 0))
+    elif eebm:
         k, side = ((6, 8) if n <= 15000 else (4, 8) if n <= 60000 else
                    (0, 0))
     else:
@@ -231,13 +232,15 @@ def tile_plan(q, eebm, nx, ny):
 
 
 @pytest.mark.parametrize("nx,ny", [(3, 3), (4, 3), (9, 8), (17, 3), (8, 25),
-                                   (40, 33), (173, 173), (331, 331)])
+                                   (40, 33), (173, 173), (331, 331),
+                                   (57, 1136), (5000, 20)])
 @pytest.mark.parametrize("eebm", [False, True])
 def test_tile_kernel(nx, ny, eebm):
-    if eebm and nx * ny > 60000:
-        assert tile_plan(9, eebm, nx, ny) is None
+    plan = tile_plan(9, eebm, nx, ny)
+    if nx * ny > 60000 and eebm == (nx == ny):
+        assert plan is None
         return
-    k, ntx, nty, rx, ry = tile_plan(9, eebm, nx, ny)
+    k, ntx, nty, rx, ry = plan
     assert rx * ry <= 1024 and rx * ry * 9 * 8 <= 65536
     boxes = [(c * nx // ntx, (c + 1) * nx // ntx, r * ny // nty,
               (r + 1) * ny // nty) for r in range(nty) for c in range(ntx)]
