@@ -275,13 +275,22 @@ inline int sweep_rows(int64_t ny) {
 // traffic saved (801^2 D2Q5 21.2 -> 22.4).
 // Three steps instead of four on FP32 lattices that the memory-side cache
 // holds (2048^2 D2Q9 31.9 against 34.6).
+// With walls above and below, few rows are left between the tiles at them, and
+// below 56 rows in FP64, 96 in FP32, single steps are ahead (front in the
+// frame / so, D2Q9: FP64 700000 nodes in 48 rows 27.4 / 21.2, 2M in 48 70.2 /
+// 71.6, in 63 60.6 / 68.7; FP32 1.55M in 48 37.3 / 24.7, in 80 27.5 / 23.1, 4M
+// in 80 65.3 / 67.3, in 120 54.3 / 70.2).
 inline SweepPlan sweep_default(const lbm_stefan_params &p) {
   const int64_t n = p.nx * p.ny;
   if (p.dim != 2 || p.scheme == LBM_SCHEME_ILFBM) return SweepPlan();
   const bool eebm = p.scheme == LBM_SCHEME_EEBM;
   bool hot;
   front_walls(p, &hot);
-  if (n <= (eebm ? 30000 : sweep_nodes(p.storage)) || (!eebm && !hot)) return SweepPlan();
+  if (n <= (eebm ? 30000 : sweep_nodes(p.storage)) || (!eebm && !hot))
+    return SweepPlan();
+  if (!eebm && p.bc[2] != LBM_BC_PERIODIC &&
+      p.ny < (p.storage == LBM_STORE_F64 ? 56 : 96))
+    return SweepPlan();
   const int k = !eebm && p.storage == LBM_STORE_F32 && n < 6000000 ? 3 : 4;
   SweepPlan P = sweep_plan(p, k, sweep_rows(p.ny), sweep_rows(p.ny),
                            n > (1 << 24));

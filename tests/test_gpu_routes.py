@@ -303,9 +303,12 @@ def test_thin_lattices_of_tiles(nx, ny, q, storage):
 
 @pytest.mark.parametrize("nx,ny,q,storage,at", [
     (33, 2946, 9, "f32", 60), (35, 2878, 5, "f32", 8), (25812, 4, 9, "f32", 60),
-    (20, 2900, 5, "f32", 8)])
+    (20, 2900, 5, "f32", 8), (32201, 48, 9, "f32", 8), (14583, 48, 9, "f64", 8),
+    (19375, 80, 9, "f32", 8), (33334, 60, 9, "f64", 8)])
 def test_thin_lattices(nx, ny, q, storage, at):
-    """the same with solves, melted and not, the last below the tiles' limit"""
+    """the same with solves, melted and not, the fourth below the tiles'
+    limit, the last at few rows between walls, the first three of them single
+    steps, the fourth in sweeps"""
     a, b = _default_against(_prob(nx, ny, q, storage, _field(nx, ny, at)))
     assert a <= 1.2 * b
 
