@@ -238,9 +238,12 @@ int lbm_stefan_init(const lbm_stefan_params *p, const double *T0,
                     lbm_stefan_t **out);
 
 /*
- * Advance nsteps >= 0 time steps (one kernel launch per step on the
- * handle's stream, fewer where the variant or the library default takes
- * several steps per launch).  Asynchronous when stats is NULL and strict is off;
+ * Advance nsteps >= 0 time steps, ordered on the handle's stream: one kernel
+ * launch per step, fewer where the variant or the library default takes
+ * several steps per launch.  A lattice that goes by several steps per launch
+ * in some states only (lbm_stefan_launches) has both kinds of launches issued,
+ * those not wanted leaving at once; large ones issue part of them on a second
+ * stream between two events of the handle's, also under capture.  Asynchronous when stats is NULL and strict is off;
  * otherwise waits for the stream and fills *stats (the energy is
  * recomputed from the final state).  Errors: EINVAL (nsteps < 0),
  * ENOTCONV (strict), ENAN (the energy is not finite), EDEVICE.
@@ -292,12 +295,12 @@ int lbm_stefan_state_ptr(lbm_stefan_t *h, void **dev_state);
    sweeping at most m rows, and in the batched form always so (there w and b
    do not matter, nor m above 32), or, in a batch of small lattices, the
    default's single steps; a single trailing step then uses the default
-   variant, and a lattice with a Neumann wall runs the default variant; q = 5 and 9 also "0x0/npt1", the library's
-   own choice for the lattice (what params.variant = -1 takes); q = 3 also
-   "resident2048": D1Q3 lattices of
-   at most 2048 nodes with no Neumann wall run many steps per launch in one workgroup, both
-   states in LDS (others run the default variant; the batched form rejects
-   it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z
+   variant, and a lattice with a Neumann wall runs the default variant; q = 5
+   and 9 also "0x0/npt1", the library's own choice for the lattice (what
+   params.variant = -1 takes); q = 3 also "resident2048": D1Q3 lattices of at
+   most 2048 nodes with no Neumann wall run many steps per launch in one
+   workgroup, both states in LDS (others run the default variant; the batched
+   form rejects it); 3D lattices, q = 7 or 19: "<tile_x>x<tile_y>/npt<k>/z<c>[/nt]", c z
    slices swept by one block; those of one wave, "64x1/npt1/z1" and z2, run
    the default variant on lattices larger than those that take them by
    default); used by autotuners. */
@@ -454,8 +457,9 @@ int lbm_stefan_backward_tape(lbm_stefan_t *h, const double *dL_dfront,
 
 /* ---------------------------------------------------------------------
  * Batched form: many independent lattices with their own sizes and
- * parameters, advanced together by one persistent kernel launch per time
- * step (optionally replayed from a captured hipGraph).  Every instance is
+ * parameters, advanced together by one kernel launch per time step, or one
+ * per up to four steps where the batch suits that (optionally replayed from a
+ * captured hipGraph).  Every instance is
  * stepped by exactly the arithmetic of the single-lattice step (Algorithm
  * 3, Section 4.1; closures of Section 4.2): a batch member evolves
  * bit-identically to the same lattice run alone.  Instances must share
@@ -475,7 +479,8 @@ int lbm_stefan_batch_workspace_bytes(const lbm_stefan_params *params,
  * lbm_stefan_init.  T0: host, nullable array of `count` nullable host
  * arrays [ny_k][nx_k].  workspace: device, 256-byte aligned, >= the size
  * above, owned by the caller.  Default schedule: the library's default
- * variant, one block per work item (a stack of tiles), no graph.  Blocks
+ * variant, one block per work item (a stack of tiles, a frame tile, four
+ * sweeping waves), no graph.  Blocks
  * until built.
  */
 int lbm_stefan_batch_init(const lbm_stefan_params *params, int32_t count,

@@ -138,9 +138,9 @@ int run_variant(const lbm_stefan_params *ps, int count, int v) {
              : v;
 }
 
-// the variant a batch starts with (and -1 selects): sweeping waves, unless
-// the batch is small or of small lattices, or a member is an IREBM melt that freezes (see
-// sweep_nodes, sweep_default)
+// the variant a batch starts with (and -1 selects): sweeping waves, unless the
+// batch is small or of small lattices, or a member is an IREBM melt that
+// freezes (see sweep_nodes, sweep_default)
 int default_variant(const lbm_stefan_params *ps, int count) {
   if (ps[0].q == 3) return kDefaultVariant1D;
   const int64_t nodes = batch_nodes(ps, count);
@@ -275,10 +275,10 @@ void drop_graphs(lbm_stefan_batch_t *b) {
 // 64, at 0.9 it never does).  us per step, single steps / sweeps with the front
 // at column 8, 24, 64, 100, half way: 48 FP32 D2Q5 lattices of 64^2 to 1024^2
 // 272 / 121, 158, 213, 267, 310; 12 D2Q9 ones of 512^2 to 1024^2 150 / 65, 89,
-// 146, 171, 189; 400 D2Q5 ones of 64^2 to 256^2 188 to 231 / 178, 241, 361, 343,
-// 364; 24 FP64 D2Q9 ones of 64^2 to 1024^2 384 / 156, 167, 203, 288, 376; 43
-// FP64 D2Q5 ones of up to 753 x 690, half way, 245 / 313; 11 of about 1200 x 900
-// 235 / 280.
+// 146, 171, 189; 400 D2Q5 ones of 64^2 to 256^2 188 to 231 / 178, 241, 361,
+// 343, 364; 24 FP64 D2Q9 ones of 64^2 to 1024^2 384 / 156, 167, 203, 288, 376;
+// 43 FP64 D2Q5 ones of up to 753 x 690, half way, 245 / 313; 11 of about 1200
+// x 900 235 / 280.
 void set_batch_route(lbm_stefan_batch_t *b, int K, double bytes) {
   const double us = K * bytes / 4e6;
   // ns of a unit (route_units)

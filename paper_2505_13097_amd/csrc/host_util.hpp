@@ -218,11 +218,11 @@ inline SweepPlan sweep_plan(const lbm_stefan_params &p, int k, int rows,
 // sweep's own time: a chain of k rows + k (k - 1) of them per launch, against
 // k single steps that each pass over the state at 5 TB/s.  The sweep itself
 // takes 0.37 of those on lattices of 60 us a step and more, 0.5 to 0.6 below,
-// which leaves 0.16 and 0.105 rows for every us.  us per step, sweeps with the front in the
-// frame / at column 100 / half way / single steps, half way: 900 x 700 D2Q9
-// FP64 10 / 40 / 47 / 21, 2048^2 D2Q5 FP32 18 / 58 / 71 / 38, 4096^2 68 / 142
-// / 199 / 151, 2048^2 D2Q9 FP64 50 / 98 / 129 / 134, 8192^2 D2Q9 FP32 344 /
-// 464 / 601 / 925.  So a lattice on which such a chain costs more than the
+// which leaves 0.16 and 0.105 rows for every us.  us per step, sweeps with the
+// front in the frame / at column 100 / half way / single steps, half way: 900
+// x 700 D2Q9 FP64 10 / 40 / 47 / 21, 2048^2 D2Q5 FP32 18 / 58 / 71 / 38,
+// 4096^2 68 / 142 / 199 / 151, 2048^2 D2Q9 FP64 50 / 98 / 129 / 134, 8192^2
+// D2Q9 FP32 344 / 464 / 601 / 925.  So a lattice on which such a chain costs more than the
 // single steps leaves the sweeps where a wave holds more rows with solves
 // than they pay for (RouteCtl), and one on which it does not sweeps always.
 // The strip next to a wall where a front starts goes in segments of `frows`

@@ -7,8 +7,8 @@
 //                    bx * npt columns by by rows).  Blocks are remapped so
 //                    that each of the eight XCDs sweeps one contiguous
 //                    band of tile rows: the rows a tile pulls from its
-//                    neighbours then sit in that XCD's L2.  Interior tiles take a path with no bounds
-//                    checks.  Per-item Newton and flux statistics are
+//                    neighbours then sit in that XCD's L2.  Interior
+//                    tiles take a path with no bounds checks.  Per-item Newton and flux statistics are
 //                    accumulated by the owning block (no atomics).
 //   init_kernel      equilibrium state from a temperature field.
 //   temp_kernel      T = sum_i Omega_i (EEBM: Theta of that enthalpy).
@@ -212,10 +212,10 @@ __device__ __forceinline__ int xcd_item_front_first(int b, int per_xcd,
 // region that is right shrinks by one node a side and step (walls do not
 // shrink it).  Threads run along x, or along y (tall): a wave solves for as
 // long as any of its nodes does, so its nodes lie along the front (1001 x 777
-// D2Q9 FP64 heated at x = 0: 11.6 -> 10.8 us per step, sweeps included).  The nodes of the halo are computed by the neighbours as
-// well, from the same values by the same code (update_values), so the
-// states are those of k single steps bit for bit; statistics count the
-// tile's own nodes.  The mirror of a Neumann wall node reads two cells
+// D2Q9 FP64 heated at x = 0: 11.6 -> 10.8 us per step, sweeps included).  The
+// nodes of the halo are computed by the neighbours as well, from the same
+// values by the same code (update_values), so the states are those of k single
+// steps bit for bit; statistics count the tile's own nodes.  The mirror of a Neumann wall node reads two cells
 // inward, which the width of a tile (at least two nodes) keeps inside the
 // region.
 // mid: when given, step l < k of the own nodes is also stored at mid + l *
@@ -838,8 +838,8 @@ __global__ __launch_bounds__(256) void stats_kernel(const StatSlot *slots,
 
 // Statistics and energies of a batch: a launch of each of these two over all
 // instances (a pass of 60 steps of 48 lattices and their statistics 9.89 ms
-// with three launches each, 9.36 so).  parts: the instances' energy chunks, instance k from table[k].part
-// on; count entries and the end.
+// with three launches each, 9.36 so).  parts: the instances' energy chunks,
+// instance k from table[k].part on; count entries and the end.
 struct BatchQuery {
   int64_t part, nslots;
 };

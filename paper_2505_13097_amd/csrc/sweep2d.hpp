@@ -17,12 +17,17 @@
 // neighbouring waves compute as well: 64 - 2 K columns and the segment's
 // rows are stored and counted.
 //
-// The sweep knows no walls.  The frame (kFrame... columns and rows along
-// the walls of an axis that is not periodic) is advanced by blocks of the
-// same launch as tiles of 16 x 16 nodes with their halo (tile_body): the
-// closures stay out of the sweep's registers, and the front of a heated
-// wall, a Newton solve per row and level there, is worked on by many waves
-// at once instead of row after row by one.
+// The sweep knows no walls.  The frame (one or two tiles along the walls of an
+// axis that is not periodic) is advanced by blocks of the same launch as tiles
+// of 16 x 16 nodes with their halo (tile_body): the closures stay out of the
+// sweep's registers, and the front of a heated wall, a Newton solve per row
+// and level there, is worked on by many waves at once instead of row after row
+// by one.  A front that has left the frame is that serial chain again, and
+// more so the longer a wave's segment: on lattices where it costs more than
+// the traffic saved, a group of steps is issued as sweeps and as single steps,
+// and the device's RouteCtl, from what the last sweep (or a scan of the state)
+// held, says which of them leaves at once (900 x 700 D2Q9 FP64, front half
+// way: 47 us per step in sweeps, 24 so; route_lattice has the line).
 // Every update is the code and the operands of the one-step kernel, so the
 // states are those of K single steps bit for bit.
 #pragma once
