@@ -2,9 +2,9 @@
 
 A step is one IREBM time step (collision, pull streaming, boundary
 closures, local Newton solve, source and update, per-item Newton and flux
-statistics) over the whole lattice: one kernel launch, or half of one for
-the temporally blocked variants that advance two steps per launch.  Inputs
-are resident in HBM before the timed region.
+statistics) over the whole lattice: one kernel launch, or a part of one for
+the variants that advance several steps per launch.  Inputs are resident in
+HBM before the timed region.
 
 Default workload: the 8192 x 8192 D2Q9 cavity (FP32 populations, FP64
 per-node arithmetic), heated at x = 0, adiabatic y walls, Ste drawn from
@@ -17,12 +17,13 @@ both schemes), the paper's 2D freezing case and 1D case with
 the three schemes, the 512^3 cube on D3Q19 and D3Q7, and the freezing
 case taken to 3D.
 
-Prints one JSON line.  Roofline: algorithmic bytes per launch
-(2 q sizeof(population) per lattice update: each population read once and
-written once, times the updates one launch performs) over the average
-launch time measured with HIP events on the stream the kernels run on.  A
-two-step launch moves about half of those bytes (roofline.traffic, from
-the counter runs), so its achieved rate can exceed what HBM delivers.
+Prints one JSON line.  hbm_gbps_algorithmic: 2 q sizeof(population) bytes
+per lattice update (each population read once and written once per step), a
+rate that several steps per launch take past what HBM delivers.  Roofline:
+the bytes that a launch cannot be spared, one state read and one written
+however many steps lie between, over the average launch time measured with
+HIP events on the stream the kernels run on; roofline.traffic is what the
+counters saw a launch move.
 """
 import argparse
 import json
@@ -171,16 +172,23 @@ def time_plain(prob, steps, warmup, variant=-1, autotune=False):
     gpu_ms = ev0.elapsed_time(ev1)
     st = g.stats()
     front = g.front("integral")
+    kernel, spl, _ = g.launches()
     g.close()
     return {"wall_s": t1 - t0, "gpu_ms": gpu_ms, "stats": st,
             "front_mean": float(front.mean()), "variant": variant,
-            "tuned": tuned}
+            "tuned": tuned, "kernel": kernel, "steps_per_launch": spl}
+
+
+def library_variant(q, storage):
+    """index of what variant -1 of a 1D or 2D lattice runs as"""
+    return (variant_id(q, storage, "resident2048") if q == 3 else
+            variant_id(q, storage, "0x0/npt1"))
 
 
 def time_batched(probs, steps, warmup, autotune=False, graph_steps=100,
                  variant=-1, bpc=0):
-    """The batched form: all instances advanced by one persistent launch
-    per step, replayed from a captured hipGraph of graph_steps launches."""
+    """The batched form: all instances advanced together, replayed from a
+    captured hipGraph of graph_steps steps."""
     import torch
     from paper_2505_13097_amd import StefanBatch, variant_names
     b = StefanBatch(probs)
@@ -193,6 +201,7 @@ def time_batched(probs, steps, warmup, autotune=False, graph_steps=100,
         tuned = {"variant": variant_names(probs[0].q, probs[0].storage)[v],
                  "blocks_per_cu": bpc, "ms_per_step": round(ms, 4)}
     b.set_schedule(v, bpc, graph_steps)
+    kernel, spl, _ = b.launches()
     b.step(warmup)
     b.reset_stats()
     stream = torch.cuda.current_stream()
@@ -215,9 +224,11 @@ def time_batched(probs, steps, warmup, autotune=False, graph_steps=100,
         "instances": len(probs), "nodes": nodes, "steps": steps,
         "value": round(nodes * steps / (t1 - t0) / 1e6, 1), "unit": "MLUPS",
         "hbm_gbps_algorithmic": round(nodes * bpn * steps / (gpu_ms * 1e-3) / 1e9, 1),
-        "frac_of_peak": round(nodes * bpn * steps / (gpu_ms * 1e-3) / 1e9 /
-                              HBM_PEAK_GBPS, 4),
+        # of one state in and one out per launch
+        "frac_of_peak": round(nodes * bpn * steps / spl / (gpu_ms * 1e-3) /
+                              1e9 / HBM_PEAK_GBPS, 4),
         "ms_per_step": round(gpu_ms / steps, 4),
+        "kernel": kernel, "steps_per_launch": spl,
         "graph_steps": graph_steps, "autotune": tuned,
         "nonconverged": int(sum(s["nonconverged"] for s in st)),
         "max_newton_it": int(max(s["max_newton_it"] for s in st)),
@@ -235,19 +246,19 @@ def time_eebm(prob, steps, warmup, autotune, irebm_ms_per_step, variant=-1,
     if variant < 0 and not autotune and dflt:
         variant = variant_id(pe.q, pe.storage, dflt)
     r = time_plain(pe, steps, warmup, variant, autotune=autotune)
-    v = r["variant"] if r["variant"] >= 0 else (0 if pe.q == 3 else 3)
+    v = (r["variant"] if r["variant"] >= 0 else
+         library_variant(pe.q, pe.storage))
     vname = variant_names(pe.q, pe.storage)[v]
-    spl = steps_per_launch(vname)
-    launch_ms = r["gpu_ms"] / (steps // spl)
-    gbps = pe.nodes * bytes_per_node(pe) * spl / (launch_ms * 1e-3) / 1e9
+    gbps = pe.nodes * bytes_per_node(pe) * steps / (r["gpu_ms"] * 1e-3) / 1e9
     ms = r["wall_s"] * 1e3 / steps
     return {
         "workload": pe.name, "steps": steps,
         "value": round(pe.nodes * steps / r["wall_s"] / 1e6, 1),
         "unit": "MLUPS", "ms_per_step": round(ms, 4),
-        "kernel_variant": vname,
+        "kernel_variant": vname, "kernel": r["kernel"],
+        "steps_per_launch": r["steps_per_launch"],
         "hbm_gbps_algorithmic": round(gbps, 1),
-        "frac_of_peak": round(gbps / HBM_PEAK_GBPS, 4),
+        "frac_of_peak": round(gbps / r["steps_per_launch"] / HBM_PEAK_GBPS, 4),
         "time_ratio_irebm_to_eebm": round(irebm_ms_per_step / ms, 3),
     }
 
@@ -269,19 +280,21 @@ def time_planar(steps=10000, warmup=20, autotune=False):
             prob.q, prob.storage,
             DEFAULT_VARIANTS["planar" if scheme == "irebm" else "planar_eebm"])
         r = time_plain(prob, steps, warmup, v, autotune=autotune)
-        v = r["variant"] if r["variant"] >= 0 else 3
+        v = (r["variant"] if r["variant"] >= 0 else
+             library_variant(prob.q, prob.storage))
         vname = variant_names(prob.q, prob.storage)[v]
-        spl = steps_per_launch(vname)
-        launch_ms = r["gpu_ms"] / (steps // spl)
-        gbps = prob.nodes * bytes_per_node(prob) * spl / (launch_ms * 1e-3) / 1e9
+        spl = r["steps_per_launch"]
+        gbps = (prob.nodes * bytes_per_node(prob) * steps /
+                (r["gpu_ms"] * 1e-3) / 1e9)
         out[scheme] = {
             "workload": prob.name, "steps": steps,
             "value": round(prob.nodes * steps / r["wall_s"] / 1e6, 1),
             "unit": "MLUPS",
             "ms_per_step": round(r["gpu_ms"] / steps, 5),
-            "kernel_variant": vname,
+            "kernel_variant": vname, "kernel": r["kernel"],
+            "steps_per_launch": spl,
             "hbm_gbps_algorithmic": round(gbps, 1),
-            "frac_of_peak": round(gbps / HBM_PEAK_GBPS, 4),
+            "frac_of_peak": round(gbps / spl / HBM_PEAK_GBPS, 4),
             "newton_max_it": r["stats"]["max_newton_it"],
             "nonconverged": r["stats"]["nonconverged"],
             "front_mean": round(r["front_mean"], 6),
@@ -721,27 +734,39 @@ def steps_per_launch(variant_name, steps=1):
 
 def traffic_sweep(prob):
     """For counter runs: every kernel variant of the workload's lattice for
-    SWEEP_STEPS steps each, in table order (the summary maps the step-kernel
-    dispatches to variants by that order: SWEEP_STEPS launches of a
-    one-step variant, SWEEP_STEPS / 2 of a two-step one)."""
+    SWEEP_STEPS steps each, in table order.  Returns (name, kernel, steps per
+    launch) of each; the summary maps the dispatches to variants by them."""
     import torch
     from paper_2505_13097_amd import Stefan, variant_names
     g = Stefan(prob)
     names = variant_names(prob.q, prob.storage)
-    for v in range(len(names)):
+    out = []
+    for v, name in enumerate(names):
         g.set_variant(v)
+        out.append((name,) + g.launches()[:2])
         g.step(SWEEP_STEPS)
     torch.cuda.synchronize()
     g.close()
-    return names
+    return out
 
 
-BATCH_PROFILE = "batch_step2_kernel_batch512_d2q5_f32.md"
+BATCH_PROFILE = "batch_sweep_kernel_batch512_d2q5_f32.md"
+BATCH_STEPS_PER_LAUNCH = 4    # of a two-step variant in the batched form
+
+
+def batch_roles(vname, mode=0):
+    """Trace names of the kernels one batched launch of four steps (a
+    two-step variant) or one runs under variant vname (IREBM mode 0, EEBM
+    mode 2), by role."""
+    if "/t2" in vname:
+        return {"sweep": f"batch_sweep_kernel<5, float, {mode}, "
+                         f"{BATCH_STEPS_PER_LAUNCH}>"}
+    return batch_kernels(vname, mode)
 
 
 def batch_kernels(vname, mode=0):
-    """Trace names of the kernels one batched launch runs under variant
-    vname (IREBM mode 0, EEBM mode 2), by role."""
+    """As batch_roles; two-step variants in traces of libraries whose batches
+    took two steps per launch."""
     if "/t2" in vname:
         m = re.fullmatch(r"(\d+)x(\d+)/t2s?(/r\d+)?(/nt)?", vname)
         win, by = int(m.group(1)), int(m.group(2))
@@ -788,7 +813,7 @@ def summarize_profiles(run, args):
     def step_kernel_of(k, mode):
         """k is a single-lattice step kernel of this lattice in node-update
         mode `mode` (0: IREBM safeguarded Newton, 2: EEBM)."""
-        return re.match(rf"(step2_kernel<{prob.q}, float, {mode},|"
+        return re.match(rf"((?:sweep|step2)_kernel<{prob.q}, float, {mode},|"
                         rf"step_kernel<{prob.q}, float, \d, {mode},)", k)
 
     def db(sub):
@@ -801,7 +826,12 @@ def summarize_profiles(run, args):
     bnames = variant_names(5, "f32")
     V, BV, BB = args.variant, args.batch_variant, args.batch_bpc
     vname, bvname = names[V], bnames[BV]
-    spl = steps_per_launch(vname)
+    # (name, kernel, steps per launch) of the variants, as the counter run
+    # printed them
+    with open(os.path.join(run, "sweep.json")) as f:
+        swept = json.loads(f.read().strip().splitlines()[-1])["variants"]
+    of = {nm: (k, n) for nm, k, n in swept}
+    kname, spl = of[vname]
     launches = args.steps // spl
 
     c = db("prof_all")
@@ -812,17 +842,23 @@ def summarize_profiles(run, args):
     for name, d in c.execute("select name, duration from kernels "
                              "order by dispatch_id"):
         by[short(name)].append(d / 1000.0)          # ns -> us
-    kname = "step2_kernel" if spl == 2 else "step_kernel"
-    step_us = by[[k for k in by if step_kernel_of(k, 0) and
-                  k.startswith(kname + "<")][0]]
+
+    def timed(mode):
+        """the traced kernel of the timed launches (sweeps: of spl steps)"""
+        ks = [k for k in by if step_kernel_of(k, mode) and
+              k.startswith(kname + "<") and
+              (kname != "sweep_kernel" or f", {mode}, {spl}, " in k)]
+        return ks[:1]
+    step_us = by[timed(0)[0]]
     # the timed launches are the last ones of the step kernel
     step_avg = sum(step_us[-launches:]) / launches
-    eebm_k = [k for k in by if step_kernel_of(k, 2) and
-              k.startswith(kname + "<")]
+    eebm_k = timed(2)
     eebm_avg = (sum(by[eebm_k[0]][-launches:]) / launches
                 if eebm_k and len(by[eebm_k[0]]) >= launches else None)
-    bkern = batch_kernels(bvname)
-    blaunch = args.batch_steps // steps_per_launch(bvname)
+    bkern = batch_roles(bvname)
+    bspl = BATCH_STEPS_PER_LAUNCH if "/t2" in bvname else 1
+    # (some launches of a graph take fewer steps: those of bspl are timed)
+    blaunch = args.batch_steps // bspl * 3 // 4
     bwall = batch_walls(c, short, bkern)[-blaunch:]
     bat_avg = sum(bwall) / len(bwall)          # wall time per launch
     bk_avg = {role: sum(by[k][-blaunch:]) / blaunch
@@ -843,26 +879,26 @@ def summarize_profiles(run, args):
         return step_kernel_of(k, 0) is not None
     sf = [v for k, v in F if is_step(k)]
     sw = [v for k, v in W if is_step(k)]
-    counts = [SWEEP_STEPS // steps_per_launch(nm) for nm in names]
+    counts = [SWEEP_STEPS // n for _, _, n in swept]
     if len(sf) != sum(counts) or len(sw) != sum(counts):
         raise SystemExit(f"expected {sum(counts)} step-kernel dispatches, "
                          f"found {len(sf)} / {len(sw)}")
     alg = prob.nodes * bytes_per_node(prob)      # per lattice update
     per_var = {}
     o = 0
-    for nm, n in zip(names, counts):
+    for (nm, _, k), n in zip(swept, counts):
         fk = sum(sf[o:o + n]) / n
         wk = sum(sw[o:o + n]) / n
         o += n
         b = fk * 1024 * fs + wk * 1024 * ws
-        per_var[nm] = {"steps_per_launch": steps_per_launch(nm),
+        per_var[nm] = {"steps_per_launch": k,
                        "fetch_kib_per_dispatch": round(fk, 1),
                        "write_kib_per_dispatch": round(wk, 1),
                        "bytes_per_launch": round(b),
                        "bytes_per_lattice_update": round(
-                           b / prob.nodes / steps_per_launch(nm), 3),
+                           b / prob.nodes / k, 3),
                        "ratio_to_algorithmic": round(
-                           b / (alg * steps_per_launch(nm)), 4)}
+                           b / (alg * k), 4)}
     # counters of the batch's last launch in the sweep (IREBM comes first)
     def last_launch(C):
         out = {}
@@ -875,7 +911,6 @@ def summarize_profiles(run, args):
     bf, bw = sum(bF.values()), sum(bW.values())
     bprobs = synth.batch_table(count=args.batch_count, nsteps=args.batch_steps)
     bnodes = sum(p.nodes for p in bprobs)
-    bspl = steps_per_launch(bvname)
     balg = bnodes * 40 * bspl
     bfb, bwb = bf * 1024 * fs, bw * 1024 * ws
     src = kernel_source_hash()
@@ -886,7 +921,7 @@ def summarize_profiles(run, args):
                  f" --batch-steps {args.batch_steps}"
                  f" --batch-variant {BV} --batch-bpc {BB}")
     pmc_cmd = ("rocprofv3 --pmc {C} -d gpurun_out/{D} -o {O} -- python bench.py"
-               f" --traffic-sweep --batch-steps 4 --batch-variant {BV}"
+               f" --traffic-sweep --batch-steps 8 --batch-variant {BV}"
                f" --batch-bpc {BB}")
     out = os.path.join(ROOT, "profiles")
     cav = step_avg
@@ -949,12 +984,6 @@ def summarize_profiles(run, args):
         f"1024^2), FP32, variant {bvname} (blocks per CU {BB})", "",
         f"Same kernel trace as {fn} (the bench's batched form:",
         f"{args.batch_steps} steps replayed from hipGraphs of 100 steps).", ""]
-    if "front" in bkern:
-        blines += [
-            "Split two-step schedule, per launch of two steps: the front "
-            "strips (batch_front_kernel, on a stream of its own) beside the "
-            "quiet pass (batch_step2_kernel<..., 1>), then the full pass over "
-            "flagged items (batch_step2_kernel<..., 2>).", ""]
     blines += ["| kernel | role | average us per launch |", "|---|---|---|"]
     for role, k in bkern.items():
         if role in bk_avg:
@@ -987,7 +1016,8 @@ def summarize_profiles(run, args):
              "| kernel | calls | total us | average us |", "|---|---|---|---|"] +
             [f"| {r[0]} | {r[1]} | {r[2]:.0f} | {r[3]:.2f} |" for r in adj] + [""]))
     with open(TRAFFIC_JSON, "w") as f:
-        json.dump({"kernel": "step_kernel / step2_kernel", "workload": prob.name,
+        json.dump({"kernel": "step_kernel / step2_kernel / sweep_kernel",
+                   "workload": prob.name,
                    "sources_sha256": src, "fetch_scale": fs, "write_scale": ws,
                    "algorithmic_bytes_per_launch": alg, "variants": per_var,
                    "source": "profiles/" + fn}, f, indent=1)
@@ -1016,16 +1046,16 @@ def summarize_sq(run, args, db, short):
     bnames = variant_names(5, "f32")
     bv = bnames[args.batch_variant]
     kinds = [(f"batched IREBM, {role}", k)
-             for role, k in batch_kernels(bv, 0).items()]
+             for role, k in batch_roles(bv, 0).items()]
     kinds += [(f"batched EEBM, {role}", k)
-              for role, k in batch_kernels(bv, 2).items()]
+              for role, k in batch_roles(bv, 2).items()]
     lines = ["# SQ counters — batched form (512 D2Q5 instances, FP32, variant "
              f"{bv}) in IREBM and EEBM", "",
              "    rocprofv3 --pmc " + " ".join(SQ_COUNTERS) +
              " -d gpurun_out/pmc_sq -o sq -- python bench.py --traffic-sweep"
-             f" --batch-steps 4 --batch-variant {args.batch_variant}"
+             f" --batch-steps 8 --batch-variant {args.batch_variant}"
              f" --batch-bpc {args.batch_bpc}", "",
-             "Averages per dispatch (the sweep's 4 steps of each).", "",
+             "Averages per dispatch (8 steps of each).", "",
              "| kernel | dispatches | " + " | ".join(SQ_COUNTERS) +
              " | VALU per wave | wave cycles per wave |",
              "|---|---|" + "---|" * (len(SQ_COUNTERS) + 2)]
@@ -1054,7 +1084,7 @@ def summarize_sq(run, args, db, short):
                   " busy cycles "
                   f"{tot['SQ_BUSY_CYCLES'][0] / tot['SQ_BUSY_CYCLES'][1]:.2f}x."]
     lines.append("")
-    fn = "batch_step2_kernel_sq_counters_batch512_d2q5_f32.md"
+    fn = "batch_sweep_kernel_sq_counters_batch512_d2q5_f32.md"
     with open(os.path.join(ROOT, "profiles", fn), "w") as f:
         f.write("\n".join(lines))
     print(f"wrote profiles/{fn}")
@@ -1108,7 +1138,7 @@ def summarize_rdreq(run):
              "2D step kernels and the batched form", "",
              "    rocprofv3 --pmc " + " ".join(RDREQ_COUNTERS) +
              " -d gpurun_out/pmc_rdreq -o rdreq -- python bench.py "
-             "--traffic-sweep --batch-steps 4 --batch-variant 35 "
+             "--traffic-sweep --batch-steps 8 --batch-variant 35 "
              "--batch-bpc 0", "",
              "Bytes read = 128 x (128-byte requests) + 64 x (64-byte) + 32 "
              "x (32-byte), no calibration; beside it FETCH_SIZE (same "
@@ -1118,7 +1148,7 @@ def summarize_rdreq(run):
              "share | other requests | FETCH_SIZE x scale, GB | ratio |",
              "|---|---|---|---|---|---|---|"]
     for k, rs in by.items():
-        if not (k.startswith("step") or k.startswith("batch") or
+        if not (k.startswith(("step", "sweep", "batch")) or
                 "copyBuffer" in k):
             continue
         b = sum(r[0] for r in rs) / len(rs)
@@ -1363,22 +1393,21 @@ def main():
           flush=True)
     ms_per_step = r["wall_s"] * 1e3 / args.steps
     mlups = prob.nodes * args.steps / r["wall_s"] / 1e6
-    v = r["variant"] if r["variant"] >= 0 else (0 if prob.q == 3 else 3)
+    v = (r["variant"] if r["variant"] >= 0 else
+         library_variant(prob.q, prob.storage))
     vname = variant_names(prob.q, prob.storage)[v]
-    resident = vname.startswith("resident")
-    spl = steps_per_launch(vname, args.steps)
-    if args.steps % 2 and spl == 2:
+    resident = r["kernel"] == "resident1d_kernel"
+    if args.steps % 2 and steps_per_launch(vname) == 2:
         raise SystemExit("--steps must be even for a two-step variant")
-    # two-step variants sweep lattices of this width, four steps a launch
-    sweeps = spl == 2 and prob.nx >= 128 and prob.ny >= 128
-    if sweeps:
-        spl = 4
+    spl = min(r["steps_per_launch"], args.steps)
     launches = -(-args.steps // spl)
     launch_ms = r["gpu_ms"] / launches
     bpn = bytes_per_node(prob)
-    # algorithmic bytes per launch: 2 q s per lattice update, times the
-    # updates one launch performs (the same rate over the whole run)
-    achieved = prob.nodes * bpn * args.steps / (r["gpu_ms"] * 1e-3) / 1e9
+    # the metric's algorithmic bytes, 2 q s per lattice update; and what HBM
+    # cannot be spared: each launch reads one state and writes one, however
+    # many steps lie between
+    algorithmic = prob.nodes * bpn * args.steps / (r["gpu_ms"] * 1e-3) / 1e9
+    achieved = prob.nodes * bpn * launches / (r["gpu_ms"] * 1e-3) / 1e9
 
     if args.copy_probe:
         a = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
@@ -1414,7 +1443,7 @@ def main():
             "kernel_variant_id": v,
             "autotuned": r["tuned"] is not None,
         },
-        "hbm_gbps_algorithmic": round(achieved, 1),
+        "hbm_gbps_algorithmic": round(algorithmic, 1),
         "roofline": {
             "bound": "hbm",
             "achieved": round(achieved, 1),
@@ -1422,9 +1451,7 @@ def main():
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": measured_traffic(prob.name, vname),
-            "kernel": ("resident1d_kernel" if resident else
-                       "sweep_kernel" if sweeps else
-                       "step2_kernel" if spl == 2 else "step_kernel"),
+            "kernel": r["kernel"],
             "steps_per_launch": spl,
             "bytes_per_lattice_update": bpn,
             "avg_launch_us": round(launch_ms * 1e3, 2),
@@ -1438,8 +1465,7 @@ def main():
     traffic = out["roofline"]["traffic"]
     if traffic:
         # what HBM actually moved: the counter bytes of one launch of this
-        # variant over the same launch time (a two-step launch moves about
-        # half of its algorithmic bytes)
+        # variant over the same launch time
         dram = traffic / (launch_ms * 1e-3) / 1e9
         out["roofline"]["dram_gbps"] = round(dram, 1)
         out["roofline"]["dram_frac"] = round(dram / HBM_PEAK_GBPS, 4)
@@ -1447,9 +1473,9 @@ def main():
     out["roofline"]["copy_kernel_gbps"] = copy_gbps()
     if resident:
         out["roofline"]["note"] = (
-            "the state stays in LDS between steps: the rate is the "
-            "metric's algorithmic bytes, HBM is touched once per launch; "
-            "the per-step latency of one workgroup bounds this kernel")
+            "the state stays in LDS between steps, HBM is touched once per "
+            "launch; the per-step latency of one workgroup bounds this "
+            "kernel")
     forms = {}
     if "batched" in args.forms.split(","):
         import synth as S
