@@ -470,11 +470,11 @@ def summarize_profiles3(run, args):
                        "ratio_to_algorithmic": round(b / alg, 4)}
         lattices[p.name] = rec
     vname = {q: vdefault(q) for q in (19, 7)}
-    trace_cmd = (f"rocprofv3 --kernel-trace --stats -d gpurun_out/prof3d -o p3"
+    trace_cmd = (f"rocprofv3 --kernel-trace --stats -d run/prof3d -o p3"
                  f" -- python bench.py --cube3d-only"
                  + (f" --variant3d {args.variant3d}" if args.variant3d >= 0
                     else "") + f" --steps3d {steps}")
-    pmc_cmd = ("rocprofv3 --pmc {C} -d gpurun_out/{D} -o {O} -- python "
+    pmc_cmd = ("rocprofv3 --pmc {C} -d run/{D} -o {O} -- python "
                "bench.py --traffic-sweep-3d")
     lines = [f"# step3_kernel — {args.cube3d_n}^3 cube heated at one face, "
              "D3Q19 and D3Q7, FP32 populations", "",
@@ -915,12 +915,12 @@ def summarize_profiles(run, args):
     bfb, bwb = bf * 1024 * fs, bw * 1024 * ws
     src = kernel_source_hash()
 
-    trace_cmd = (f"rocprofv3 --kernel-trace --stats -d gpurun_out/prof_all -o all"
+    trace_cmd = (f"rocprofv3 --kernel-trace --stats -d run/prof_all -o all"
                  f" -- python bench.py --steps {args.steps} --warmup 5 --variant {V}"
                  f" --no-cpu-baseline --forms batched,adjoint,eebm"
                  f" --batch-steps {args.batch_steps}"
                  f" --batch-variant {BV} --batch-bpc {BB}")
-    pmc_cmd = ("rocprofv3 --pmc {C} -d gpurun_out/{D} -o {O} -- python bench.py"
+    pmc_cmd = ("rocprofv3 --pmc {C} -d run/{D} -o {O} -- python bench.py"
                f" --traffic-sweep --batch-steps 8 --batch-variant {BV}"
                f" --batch-bpc {BB}")
     out = os.path.join(ROOT, "profiles")
@@ -1052,7 +1052,7 @@ def summarize_sq(run, args, db, short):
     lines = ["# SQ counters — batched form (512 D2Q5 instances, FP32, variant "
              f"{bv}) in IREBM and EEBM", "",
              "    rocprofv3 --pmc " + " ".join(SQ_COUNTERS) +
-             " -d gpurun_out/pmc_sq -o sq -- python bench.py --traffic-sweep"
+             " -d run/pmc_sq -o sq -- python bench.py --traffic-sweep"
              f" --batch-steps 8 --batch-variant {args.batch_variant}"
              f" --batch-bpc {args.batch_bpc}", "",
              "Averages per dispatch (8 steps of each).", "",
@@ -1137,7 +1137,7 @@ def summarize_rdreq(run):
     lines = ["# HBM read bytes by request size — the counter sweep of the "
              "2D step kernels and the batched form", "",
              "    rocprofv3 --pmc " + " ".join(RDREQ_COUNTERS) +
-             " -d gpurun_out/pmc_rdreq -o rdreq -- python bench.py "
+             " -d run/pmc_rdreq -o rdreq -- python bench.py "
              "--traffic-sweep --batch-steps 8 --batch-variant 35 "
              "--batch-bpc 0", "",
              "Bytes read = 128 x (128-byte requests) + 64 x (64-byte) + 32 "
